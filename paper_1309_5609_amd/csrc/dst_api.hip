@@ -19,6 +19,7 @@
 #include <vector>
 
 #include "dst.h"
+#include "dst_bucket.h"
 #include "dst_comp.h"
 #include "dst_group.h"
 #include "dst_internal.h"
@@ -251,20 +252,14 @@ int setup_pixels(dst_ctx* ctx, const dst_problem* prob, Setup& S, double* blocks
   return DST_OK;
 }
 
-int run_setup(dst_ctx* ctx, const dst_problem* prob, Setup& S, bool baselines, double* blocks_out, hipStream_t st) {
+int run_setup(dst_ctx* ctx, const dst_problem* prob, Setup& S, double* blocks_out, hipStream_t st) {
   const View& v = S.v;
   DST_TRY(ws(ctx, "hits", v.n_pix, &S.hits));
   DST_TRY(ws(ctx, "M4", 4 * v.n_pix, &S.M4));
   DST_TRY(ws(ctx, "Minv4", 4 * v.n_pix, &S.Minv4));
   DST_TRY(ws(ctx, "valid", v.n_pix, &S.valid));
   DST_TRY(ws(ctx, "counts", 4, &S.counts));
-  DST_TRY(setup_pixels(ctx, prob, S, blocks_out, st));
-  if (baselines) {
-    DST_TRY(ws(ctx, "nvalid", 2 * v.n_b, &S.nvalid));
-    DST_TRY(ws(ctx, "J", (size_t)v.n_streams * v.n_b, &S.J));
-    HIP_TRY(dst::launch_baseline_counts(v, S.valid, S.nvalid, S.J, S.counts + 2, st));
-  }
-  return DST_OK;
+  return setup_pixels(ctx, prob, S, blocks_out, st);
 }
 
 // Wait for the stream and report a pixel index out of range found by any
@@ -296,6 +291,49 @@ hipError_t copy4to3(double* dst3, const double* src4, int64_t n_pix, hipStream_t
                           hipMemcpyDeviceToDevice, st);
 }
 
+// One-shot binning of x = tod + bsign F base (either NULL) into the outputs of
+// `o` through the pixel buckets.  A map beyond their range leaves *done false, and the caller takes the atomic form.
+// The records are held for as much of the timeline as the workspace takes: a
+// stream under capture, where nothing can be allocated, and a full device use
+// what the context has and take more pieces.
+int bucket_pass(dst_ctx* ctx, const dst_problem* prob, const View& v, const void* tod, const double* base,
+                double bsign, const dst::BucketOut& o, hipStream_t st, bool* done) {
+  *done = dst::buckets_fit(v);
+  if (!*done) return DST_OK;
+  dst::BucketWork W;
+  const dst::BucketBytes need = dst::bucket_bytes(v, tod || base);
+  DST_TRY(ws_get(ctx, "bk_acc_hits", need.acc_hits, reinterpret_cast<void**>(&W.acc_hits)));
+  DST_TRY(ws_get(ctx, "bk_acc", need.acc, reinterpret_cast<void**>(&W.acc)));
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &cap) != hipSuccess) (void)hipGetLastError();
+  struct Part {
+    const char* name;
+    size_t per;
+    void* ptr;
+  } parts[3] = {{"bk_off", need.off, nullptr}, {"bk_rec", need.rec, nullptr}, {"bk_rec2", need.rec2, nullptr}};
+  W.n_chunks = need.best_chunks;
+  for (Part& p : parts) {
+    if (p.per == 0) continue;
+    if (cap != hipStreamCaptureStatusNone) {
+      const int64_t held = (int64_t)(ctx->ws[ctx->ws_prefix + p.name].bytes / p.per);
+      W.n_chunks = std::max<int64_t>(1, std::min(W.n_chunks, held));
+    }
+    // at least kBucketReserve bytes, so that a later call on a longer timeline can run in pieces without growing
+    for (;; W.n_chunks = (W.n_chunks + 1) / 2) {
+      const int rc = ws_get(ctx, p.name, std::max((size_t)W.n_chunks * p.per, dst::kBucketReserve), &p.ptr);
+      if (rc == DST_OK) break;
+      if (W.n_chunks == 1) return rc;
+    }
+  }
+  ctx->err.clear();
+  W.off = static_cast<uint16_t*>(parts[0].ptr);
+  W.rec = parts[1].ptr;
+  W.rec2 = static_cast<double*>(parts[2].ptr);
+  HIP_TRY(dst::launch_buckets(v, prob->psi_dtype == DST_F32, tod, prob->tod_dtype == DST_F32, base, bsign,
+                              prob->rcond_cut, W, o, ctx->err_dev, st));
+  return DST_OK;
+}
+
 int check_bin_args(dst_ctx* ctx, const dst_problem* prob, uint32_t flags, const double* map_out, View& v) {
   DST_TRY(check_problem(ctx, prob, (flags & DST_BIN_USE_TOD) != 0, v));
   if (v.iqu) return fail(ctx, DST_EINVAL, "DST_IQU streams are not supported by this entry point");
@@ -313,9 +351,9 @@ int bin_pass(dst_ctx* ctx, const dst_problem* prob, const Setup& S, const double
   HIP_TRY(dst::launch_fill(s4, 4 * v.n_pix, 0.0, st));
   if (use_tod || baselines)
     HIP_TRY(dst::launch_bin(v, S.psi_f32, use_tod ? prob->tod : nullptr, S.tod_f32, baselines, -1.0, S.valid, s4,
-                            S.err, nullptr, st));
+                            S.err, st));
   if (flags & DST_BIN_MAP) {
-    HIP_TRY(dst::launch_apply(v.n_pix, s4, S.Minv4, map_out, 3, nullptr, nullptr, st));
+    HIP_TRY(dst::launch_apply(v.n_pix, s4, S.Minv4, map_out, 3, st));
   } else {
     HIP_TRY(copy4to3(map_out, s4, v.n_pix, st));
   }
@@ -350,21 +388,19 @@ void carve_scratch(unsigned char* base, int64_t n_pix, Setup& S, double** s4) {
 }
 
 
-// out = F^T Z x with x = tod + bsign * F base (either may be NULL).
-int operator_pass(dst_ctx* ctx, Setup& S, const void* tod, const double* base, double bsign, double* out,
-                  hipStream_t st) {
+// m4 = M^-1 A^T W (tod + bsign F base) and the validity of every pixel, by the
+// atomic form.
+int operator_map(dst_ctx* ctx, const dst_problem* prob, Setup& S, const void* tod, const double* base, double bsign,
+                 double* m4, hipStream_t st) {
   const View& v = S.v;
-  double *s4 = nullptr, *m4 = nullptr;
+  DST_TRY(run_setup(ctx, prob, S, nullptr, st));
+  double* s4 = nullptr;
   DST_TRY(ws(ctx, "s4", 4 * v.n_pix, &s4));
-  DST_TRY(ws(ctx, "m4", 4 * v.n_pix, &m4));
   HIP_TRY(dst::launch_fill(s4, 4 * v.n_pix, 0.0, st));
-  if (tod || base) HIP_TRY(dst::launch_bin(v, S.psi_f32, tod, S.tod_f32, base, bsign, S.valid, s4, S.err, nullptr, st));
-  HIP_TRY(dst::launch_apply(v.n_pix, s4, S.Minv4, m4, 4, nullptr, nullptr, st));
-  HIP_TRY(dst::launch_unbin_reduce(v, S.psi_f32, tod, S.tod_f32, base, bsign, m4, S.valid, S.nvalid, out, nullptr,
-                                   nullptr, st));
+  if (tod || base) HIP_TRY(dst::launch_bin(v, S.psi_f32, tod, S.tod_f32, base, bsign, S.valid, s4, S.err, st));
+  HIP_TRY(dst::launch_apply(v.n_pix, s4, S.Minv4, m4, 4, st));
   return DST_OK;
 }
-
 
 // Solver setup: the pixel-major transpose of the pointing with compact pixel
 // ids, per-pixel blocks from it (no atomics), and the per-baseline counts and
@@ -1454,9 +1490,16 @@ int dst_pixel_setup(dst_ctx* ctx, const dst_problem* prob, int32_t* hits_out, do
   ctx->err.clear();
   DeviceGuard g(ctx->device);
   hipStream_t st = static_cast<hipStream_t>(stream);
+  dst::BucketOut o;
+  o.hits = hits_out;
+  o.blocks = blocks_out;
+  o.valid = valid_out;
+  bool done = false;
+  DST_TRY(bucket_pass(ctx, prob, v, nullptr, nullptr, 0.0, o, st, &done));
+  if (done) return issued(ctx);
   Setup S;
   S.v = v;
-  DST_TRY(run_setup(ctx, prob, S, false, blocks_out, st));
+  DST_TRY(run_setup(ctx, prob, S, blocks_out, st));
   if (hits_out) HIP_TRY(hipMemcpyAsync(hits_out, S.hits, v.n_pix * sizeof(int32_t), hipMemcpyDeviceToDevice, st));
   if (valid_out) HIP_TRY(hipMemcpyAsync(valid_out, S.valid, v.n_pix, hipMemcpyDeviceToDevice, st));
   return issued(ctx);
@@ -1469,9 +1512,15 @@ int dst_bin(dst_ctx* ctx, const dst_problem* prob, const double* baselines, uint
   ctx->err.clear();
   DeviceGuard g(ctx->device);
   hipStream_t st = static_cast<hipStream_t>(stream);
+  dst::BucketOut o;
+  o.hits = hits_out;
+  ((flags & DST_BIN_MAP) ? o.map3 : o.sum3) = map_out;
+  bool done = false;
+  DST_TRY(bucket_pass(ctx, prob, v, (flags & DST_BIN_USE_TOD) ? prob->tod : nullptr, baselines, -1.0, o, st, &done));
+  if (done) return issued(ctx);
   Setup S;
   S.v = v;
-  DST_TRY(run_setup(ctx, prob, S, false, nullptr, st));
+  DST_TRY(run_setup(ctx, prob, S, nullptr, st));
   double* s4 = nullptr;
   DST_TRY(ws(ctx, "s4", 4 * v.n_pix, &s4));
   return bin_pass(ctx, prob, S, baselines, flags, s4, map_out, hits_out, st);
@@ -1519,7 +1568,12 @@ int dst_baseline_reduce(dst_ctx* ctx, const dst_problem* prob, const void* x, do
   hipStream_t st = static_cast<hipStream_t>(stream);
   Setup S;
   S.v = v;
-  DST_TRY(run_setup(ctx, prob, S, false, nullptr, st));
+  dst::BucketOut o;
+  DST_TRY(ws(ctx, "valid", v.n_pix, &S.valid));
+  o.valid = S.valid;
+  bool done = false;
+  DST_TRY(bucket_pass(ctx, prob, v, nullptr, nullptr, 0.0, o, st, &done));
+  if (!done) DST_TRY(run_setup(ctx, prob, S, nullptr, st));
   HIP_TRY(dst::launch_reduce(v, x, prob->tod_dtype == DST_F32, S.valid, out, st));
   return issued(ctx);
 }
@@ -1535,8 +1589,17 @@ int dst_residual(dst_ctx* ctx, const dst_problem* prob, const double* a, double*
   hipStream_t st = static_cast<hipStream_t>(stream);
   Setup S;
   S.v = v;
-  DST_TRY(run_setup(ctx, prob, S, true, nullptr, st));
-  DST_TRY(operator_pass(ctx, S, prob->tod, a, -1.0, out, st));
+  double* m4 = nullptr;
+  dst::BucketOut o;
+  DST_TRY(ws(ctx, "valid", v.n_pix, &S.valid));
+  DST_TRY(ws(ctx, "m4", 4 * v.n_pix, &m4));
+  o.valid = S.valid;
+  o.map4 = m4;
+  bool done = false;
+  DST_TRY(bucket_pass(ctx, prob, v, prob->tod, a, -1.0, o, st, &done));
+  if (!done) DST_TRY(operator_map(ctx, prob, S, prob->tod, a, -1.0, m4, st));
+  HIP_TRY(dst::launch_unbin_reduce(v, prob->psi_dtype == DST_F32, prob->tod, prob->tod_dtype == DST_F32, a, -1.0, m4,
+                                   S.valid, out, st));
   return issued(ctx);
 }
 

@@ -65,6 +65,51 @@ __device__ __forceinline__ void block_sum(T (&v)[N], T* lds) {
   __syncthreads();
 }
 
+// Four consecutive elements from p (aligned to its element only) as 16-byte
+// accesses.
+template <typename T>
+struct Wide {
+  typedef T type __attribute__((ext_vector_type(16 / sizeof(T)), aligned(sizeof(T))));
+};
+template <typename T>
+__device__ __forceinline__ void load4(const T* p, T (&o)[4]) {
+  using V = typename Wide<T>::type;
+  constexpr int N = 16 / sizeof(T);
+#pragma unroll
+  for (int k = 0; k < 4; k += N) {
+    const V v = *reinterpret_cast<const V*>(p + k);
+#pragma unroll
+    for (int j = 0; j < N; ++j) o[k + j] = v[j];
+  }
+}
+
+// v of the next (previous) lane; lane 63 (0) keeps its own.
+__device__ __forceinline__ int next_lane(int v) {
+  return __builtin_amdgcn_update_dpp(v, v, 0x130, 0xf, 0xf, false);  // wave_shl:1
+}
+__device__ __forceinline__ int prev_lane(int v) {
+  return __builtin_amdgcn_update_dpp(v, v, 0x138, 0xf, 0xf, false);  // wave_shr:1
+}
+__device__ __forceinline__ double next_lane(double v) {
+  return __hiloint2double(next_lane(__double2hiint(v)), next_lane(__double2loint(v)));
+}
+
+// Inverse (QQ, QU, UU) of a pixel's QU block [[a, b], [b, d]]; false, with inv
+// untouched, unless its smaller eigenvalue is positive and at least rcond_cut
+// times the larger.
+__device__ __forceinline__ bool qu_block_inverse(double a, double b, double d, double rcond_cut, double* inv) {
+  const double half = 0.5 * (a - d);
+  const double rad = sqrt(half * half + b * b);
+  const double lmax = 0.5 * (a + d) + rad;
+  const double det = a * d - b * b;
+  const double lmin = lmax > 0.0 ? det / lmax : 0.0;
+  if (!(lmax > 0.0 && lmin > 0.0 && lmin >= rcond_cut * lmax)) return false;
+  inv[0] = d / det;
+  inv[1] = -b / det;
+  inv[2] = a / det;
+  return true;
+}
+
 // Copies n 4-byte words from global memory to a wavefront's own LDS range
 // through the LDS-direct load path (one word per lane and instruction; lane l
 // writes dst + 4 (i + l)), so a whole stage is in flight at once with no

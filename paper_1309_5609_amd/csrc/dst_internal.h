@@ -54,19 +54,16 @@ enum { DONE_RUNNING = 0, DONE_CONVERGED = 1, DONE_BREAKDOWN = 2, DONE_NAN = 3, D
 hipError_t launch_pointing(const View& v, int psi_f32, int32_t* hits, double* M4, int* err, hipStream_t st);
 hipError_t launch_invert(const View& v, const int32_t* hits, const double* M4, double rcond_cut, double* Minv4,
                          uint8_t* valid, double* blocks_out, unsigned long long* counts, hipStream_t st);
-hipError_t launch_baseline_counts(const View& v, const uint8_t* valid, int32_t* nvalid, double* jacobi,
-                                  unsigned long long* counts, hipStream_t st);
 // s[p] += sum_k w_k A_k^T x_k over valid samples, x = tod (if tod) + base_sign * F base (if base)
 hipError_t launch_bin(const View& v, int psi_f32, const void* tod, int tod_f32, const double* base, double base_sign,
-                      const uint8_t* valid, double* s4, int* err, const CgCtl* gate, hipStream_t st);
-// m[p] = Minv[p] s[p]; optional clearing of s; m_stride 3 (user layout) or 4
-hipError_t launch_apply(int64_t n_pix, const double* s4, const double* Minv4, double* m, int m_stride, double* s_clear,
-                        const CgCtl* gate, hipStream_t st);
+                      const uint8_t* valid, double* s4, int* err, hipStream_t st);
+// m[p] = Minv[p] s[p]; m_stride 3 (user layout) or 4
+hipError_t launch_apply(int64_t n_pix, const double* s4, const double* Minv4, double* m, int m_stride,
+                        hipStream_t st);
 // out_k[b] = sum_{t in b} v_k(t) w_k (x_k(t) - A_k(t) . m[p(t)]), x as in launch_bin.
-// With ctl: also the CG step (alpha, mu) from p.q with base = p.
 hipError_t launch_unbin_reduce(const View& v, int psi_f32, const void* tod, int tod_f32, const double* base,
-                               double base_sign, const double* m4, const uint8_t* valid, const int32_t* nvalid,
-                               double* out, CgCtl* ctl, double* partials, hipStream_t st);
+                               double base_sign, const double* m4, const uint8_t* valid, double* out,
+                               hipStream_t st);
 hipError_t launch_scan(const View& v, int psi_f32, const double* map3, double* out, int* err, hipStream_t st);
 hipError_t launch_reduce(const View& v, const void* x, int x_f32, const uint8_t* valid, double* out, hipStream_t st);
 

@@ -223,40 +223,6 @@ __global__ void __launch_bounds__(kBlock) k_invert(View v, const int32_t* __rest
   }
 }
 
-// Valid samples per baseline and stream class, and the Jacobi diagonal
-// 1/(w_k n_valid) of F^T W F (0 for baselines without valid samples).
-__global__ void __launch_bounds__(kBlock) k_baseline_counts(View v, const uint8_t* __restrict__ valid,
-                                                            int32_t* __restrict__ nvalid, double* __restrict__ J,
-                                                            unsigned long long* __restrict__ counts) {
-  __shared__ int lds[2 * 16];
-  const int64_t b = blockIdx.x;
-  const int64_t t0 = b * v.L;
-  const int64_t t1 = min(t0 + v.L, v.n_t);
-  int c[2] = {0, 0};
-  for (int64_t t = t0 + threadIdx.x; t < t1; t += blockDim.x) {
-    const int p = v.pix[t];
-    if (p >= 0 && p < v.n_pix) {
-      const uint8_t f = valid[p];
-      c[0] += f & 1;
-      c[1] += (f >> 1) & 1;
-    }
-  }
-  block_sum<2>(c, lds);
-  if (threadIdx.x == 0) {
-    nvalid[b] = c[0];
-    nvalid[v.n_b + b] = c[1];
-    if (v.rowT >= 0) J[v.rowT * v.n_b + b] = c[0] ? 1.0 / (v.w[0] * c[0]) : 0.0;
-    if (v.rowQ >= 0) {
-      J[v.rowQ * v.n_b + b] = c[1] ? 1.0 / (v.w[1] * c[1]) : 0.0;
-      J[v.rowU * v.n_b + b] = c[1] ? 1.0 / (v.w[2] * c[1]) : 0.0;
-    }
-    if (counts) {
-      atomicAdd(&counts[0], (unsigned long long)c[0]);
-      atomicAdd(&counts[1], (unsigned long long)c[1]);
-    }
-  }
-}
-
 // ---------------------------------------------------------------- operators
 
 // s[p] += sum over valid samples of sum_k w_k A_k(t)^T x_k(t),
@@ -264,9 +230,7 @@ __global__ void __launch_bounds__(kBlock) k_baseline_counts(View v, const uint8_
 template <typename PT, typename TT, bool USE_TOD, bool USE_BASE>
 __global__ void __launch_bounds__(kBlock) k_bin(View v, const TT* __restrict__ tod, const double* __restrict__ base,
                                                 double bsign, const uint8_t* __restrict__ valid,
-                                                double* __restrict__ s4, int* __restrict__ err,
-                                                const CgCtl* __restrict__ gate) {
-  if (gate && gate->done) return;
+                                                double* __restrict__ s4, int* __restrict__ err) {
   const int lane = lane_id();
   const int64_t wave = (int64_t)blockIdx.x * kWaves + (threadIdx.x >> 6);
   const int64_t nw = (int64_t)gridDim.x * kWaves;
@@ -323,9 +287,7 @@ __global__ void __launch_bounds__(kBlock) k_bin(View v, const TT* __restrict__ t
 
 __global__ void __launch_bounds__(kBlock) k_apply(int64_t n_pix, const double* __restrict__ s4,
                                                   const double* __restrict__ Minv4, double* __restrict__ m,
-                                                  int m_stride, double* __restrict__ s_clear,
-                                                  const CgCtl* __restrict__ gate) {
-  if (gate && gate->done) return;
+                                                  int m_stride) {
   for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < n_pix;
        p += (int64_t)gridDim.x * blockDim.x) {
     const double2* sp = reinterpret_cast<const double2*>(s4 + 4 * p);
@@ -344,35 +306,23 @@ __global__ void __launch_bounds__(kBlock) k_apply(int64_t n_pix, const double* _
       m[3 * p + 1] = mQ;
       m[3 * p + 2] = mU;
     }
-    if (s_clear) {
-      double2* sc = reinterpret_cast<double2*>(s_clear + 4 * p);
-      sc[0] = make_double2(0.0, 0.0);
-      sc[1] = make_double2(0.0, 0.0);
-    }
   }
 }
 
 // One workgroup per baseline:
 //   out_k[b] = w_k * sum_{t in b, valid_k} (x_k(t) - A_k(t) . m[p(t)])
-// With CG, base is the search direction p (bsign = +1) and the last block
-// computes mu (projection of the T part) and alpha = r.z / p.(P K p).
-template <typename PT, typename TT, bool USE_TOD, bool USE_BASE, bool CG>
+template <typename PT, typename TT, bool USE_TOD, bool USE_BASE>
 __global__ void __launch_bounds__(kBlock) k_unbin_reduce(View v, const TT* __restrict__ tod,
                                                          const double* __restrict__ base, double bsign,
                                                          const double* __restrict__ m4,
-                                                         const uint8_t* __restrict__ valid,
-                                                         const int32_t* __restrict__ nvalid,
-                                                         double* __restrict__ out, CgCtl* __restrict__ ctl,
-                                                         double* __restrict__ partials) {
-  if (CG && ctl->done) return;
-  __shared__ double lds[4 * 16];
-  __shared__ bool last;
+                                                         const uint8_t* __restrict__ valid, double* __restrict__ out) {
+  __shared__ double lds[5 * 16];
   const PT* psi = static_cast<const PT*>(v.psi);
   const int64_t b = blockIdx.x;
   const int64_t t0 = b * v.L;
   const int64_t t1 = min(t0 + v.L, v.n_t);
   const int64_t n_t = v.n_t, n_b = v.n_b;
-  double acc[3] = {0.0, 0.0, 0.0};
+  double acc[5] = {0.0, 0.0, 0.0, 0.0, 0.0};  // T, q, u; valid samples of T and of q/u
   for (int64_t t = t0 + threadIdx.x; t < t1; t += blockDim.x) {
     const int p = v.pix[t];
     if (p < 0 || p >= v.n_pix) continue;
@@ -384,6 +334,7 @@ __global__ void __launch_bounds__(kBlock) k_unbin_reduce(View v, const TT* __res
       double x = 0.0;
       if (USE_TOD) x = (double)tod[v.rowT * n_t + t];
       acc[0] += x - m01.x;
+      acc[3] += 1.0;
     }
     if (f & 2) {
       const double mU = mp[1].x;
@@ -396,63 +347,25 @@ __global__ void __launch_bounds__(kBlock) k_unbin_reduce(View v, const TT* __res
       }
       acc[1] += xq - (c * m01.y + s * mU);
       acc[2] += xu - (c * mU - s * m01.y);
+      acc[4] += 1.0;
     }
   }
-  block_sum<3>(acc, lds);
+  block_sum<5>(acc, lds);
   if (threadIdx.x == 0) {
-    const int nT = nvalid[b], nQ = nvalid[n_b + b];
-    double pq = 0.0, eq = 0.0, ep = 0.0;
     if (v.rowT >= 0) {
       double a = acc[0];
-      double pb = 0.0;
-      if (USE_BASE) {
-        pb = base[v.rowT * n_b + b];
-        a += bsign * pb * (double)nT;
-      }
-      const double o = v.w[0] * a;
-      out[v.rowT * n_b + b] = o;
-      pq += pb * o;
-      if (nT > 0) {
-        eq = o;
-        ep = pb;
-      }
+      if (USE_BASE) a += bsign * base[v.rowT * n_b + b] * acc[3];
+      out[v.rowT * n_b + b] = v.w[0] * a;
     }
     if (v.rowQ >= 0) {
       double aq = acc[1], au = acc[2];
-      double pbq = 0.0, pbu = 0.0;
       if (USE_BASE) {
-        pbq = base[v.rowQ * n_b + b];
-        pbu = base[v.rowU * n_b + b];
-        aq += bsign * pbq * (double)nQ;
-        au += bsign * pbu * (double)nQ;
+        aq += bsign * base[v.rowQ * n_b + b] * acc[4];
+        au += bsign * base[v.rowU * n_b + b] * acc[4];
       }
-      const double oq = v.w[1] * aq, ou = v.w[2] * au;
-      out[v.rowQ * n_b + b] = oq;
-      out[v.rowU * n_b + b] = ou;
-      pq += pbq * oq + pbu * ou;
+      out[v.rowQ * n_b + b] = v.w[1] * aq;
+      out[v.rowU * n_b + b] = v.w[2] * au;
     }
-    if (CG) {
-      partials[b] = pq;
-      partials[n_b + b] = eq;
-      partials[2 * n_b + b] = ep;
-    }
-  }
-  if (!CG) return;
-  if (!arrive_last(&ctl->counter[0], &last)) return;
-  double tot[3];
-  sum_partials<3>(partials, n_b, tot, lds);
-  if (threadIdx.x == 0) {
-    const double mu = ctl->n_e > 0.0 ? tot[1] / ctl->n_e : 0.0;
-    const double pkp = tot[0] - mu * tot[2];
-    ctl->mu = mu;
-    if (!isfinite(pkp)) {
-      ctl->done = DONE_NAN;
-    } else if (pkp <= 0.0) {
-      ctl->done = DONE_BREAKDOWN;
-    } else {
-      ctl->alpha = ctl->rz / pkp;
-    }
-    ctl->counter[0] = 0;
   }
 }
 
@@ -742,87 +655,69 @@ hipError_t launch_invert(const View& v, const int32_t* hits, const double* M4, d
   return hipGetLastError();
 }
 
-hipError_t launch_baseline_counts(const View& v, const uint8_t* valid, int32_t* nvalid, double* J,
-                                  unsigned long long* counts, hipStream_t st) {
-  hipLaunchKernelGGL(k_baseline_counts, dim3((unsigned)v.n_b), dim3(kBlock), 0, st, v, valid, nvalid, J, counts);
-  return hipGetLastError();
-}
-
 template <typename PT, typename TT>
 static void bin_dispatch(const View& v, const void* tod, const double* base, double bsign, const uint8_t* valid,
-                         double* s4, int* err, const CgCtl* gate, hipStream_t st) {
+                         double* s4, int* err, hipStream_t st) {
   const unsigned g = grid_for(v.n_t, kBlock, kStreamGrid);
   const TT* x = static_cast<const TT*>(tod);
   if (tod && base)
-    hipLaunchKernelGGL((k_bin<PT, TT, true, true>), dim3(g), dim3(kBlock), 0, st, v, x, base, bsign, valid, s4, err,
-                       gate);
+    hipLaunchKernelGGL((k_bin<PT, TT, true, true>), dim3(g), dim3(kBlock), 0, st, v, x, base, bsign, valid, s4, err);
   else if (tod)
-    hipLaunchKernelGGL((k_bin<PT, TT, true, false>), dim3(g), dim3(kBlock), 0, st, v, x, base, bsign, valid, s4,
-                       err, gate);
+    hipLaunchKernelGGL((k_bin<PT, TT, true, false>), dim3(g), dim3(kBlock), 0, st, v, x, base, bsign, valid, s4, err);
   else if (base)
-    hipLaunchKernelGGL((k_bin<PT, TT, false, true>), dim3(g), dim3(kBlock), 0, st, v, x, base, bsign, valid, s4,
-                       err, gate);
+    hipLaunchKernelGGL((k_bin<PT, TT, false, true>), dim3(g), dim3(kBlock), 0, st, v, x, base, bsign, valid, s4, err);
 }
 
 hipError_t launch_bin(const View& v, int psi_f32, const void* tod, int tod_f32, const double* base, double bsign,
-                      const uint8_t* valid, double* s4, int* err, const CgCtl* gate, hipStream_t st) {
+                      const uint8_t* valid, double* s4, int* err, hipStream_t st) {
   if (psi_f32) {
     if (tod_f32)
-      bin_dispatch<float, float>(v, tod, base, bsign, valid, s4, err, gate, st);
+      bin_dispatch<float, float>(v, tod, base, bsign, valid, s4, err, st);
     else
-      bin_dispatch<float, double>(v, tod, base, bsign, valid, s4, err, gate, st);
+      bin_dispatch<float, double>(v, tod, base, bsign, valid, s4, err, st);
   } else {
     if (tod_f32)
-      bin_dispatch<double, float>(v, tod, base, bsign, valid, s4, err, gate, st);
+      bin_dispatch<double, float>(v, tod, base, bsign, valid, s4, err, st);
     else
-      bin_dispatch<double, double>(v, tod, base, bsign, valid, s4, err, gate, st);
+      bin_dispatch<double, double>(v, tod, base, bsign, valid, s4, err, st);
   }
   return hipGetLastError();
 }
 
-hipError_t launch_apply(int64_t n_pix, const double* s4, const double* Minv4, double* m, int m_stride, double* s_clear,
-                        const CgCtl* gate, hipStream_t st) {
+hipError_t launch_apply(int64_t n_pix, const double* s4, const double* Minv4, double* m, int m_stride,
+                        hipStream_t st) {
   const unsigned g = grid_for(n_pix, kBlock, 4096);
-  hipLaunchKernelGGL(k_apply, dim3(g), dim3(kBlock), 0, st, n_pix, s4, Minv4, m, m_stride, s_clear, gate);
+  hipLaunchKernelGGL(k_apply, dim3(g), dim3(kBlock), 0, st, n_pix, s4, Minv4, m, m_stride);
   return hipGetLastError();
 }
 
 template <typename PT, typename TT>
 static void unbin_dispatch(const View& v, const void* tod, const double* base, double bsign, const double* m4,
-                           const uint8_t* valid, const int32_t* nvalid, double* out, CgCtl* ctl, double* partials,
-                           hipStream_t st) {
+                           const uint8_t* valid, double* out, hipStream_t st) {
   const dim3 g((unsigned)v.n_b), blk(kBlock);
   const TT* x = static_cast<const TT*>(tod);
-  if (ctl)
-    hipLaunchKernelGGL((k_unbin_reduce<PT, TT, false, true, true>), g, blk, 0, st, v, x, base, bsign, m4, valid,
-                       nvalid, out, ctl, partials);
-  else if (tod && base)
-    hipLaunchKernelGGL((k_unbin_reduce<PT, TT, true, true, false>), g, blk, 0, st, v, x, base, bsign, m4, valid,
-                       nvalid, out, ctl, partials);
+  if (tod && base)
+    hipLaunchKernelGGL((k_unbin_reduce<PT, TT, true, true>), g, blk, 0, st, v, x, base, bsign, m4, valid, out);
   else if (tod)
-    hipLaunchKernelGGL((k_unbin_reduce<PT, TT, true, false, false>), g, blk, 0, st, v, x, base, bsign, m4, valid,
-                       nvalid, out, ctl, partials);
+    hipLaunchKernelGGL((k_unbin_reduce<PT, TT, true, false>), g, blk, 0, st, v, x, base, bsign, m4, valid, out);
   else if (base)
-    hipLaunchKernelGGL((k_unbin_reduce<PT, TT, false, true, false>), g, blk, 0, st, v, x, base, bsign, m4, valid,
-                       nvalid, out, ctl, partials);
+    hipLaunchKernelGGL((k_unbin_reduce<PT, TT, false, true>), g, blk, 0, st, v, x, base, bsign, m4, valid, out);
   else
-    hipLaunchKernelGGL((k_unbin_reduce<PT, TT, false, false, false>), g, blk, 0, st, v, x, base, bsign, m4, valid,
-                       nvalid, out, ctl, partials);
+    hipLaunchKernelGGL((k_unbin_reduce<PT, TT, false, false>), g, blk, 0, st, v, x, base, bsign, m4, valid, out);
 }
 
 hipError_t launch_unbin_reduce(const View& v, int psi_f32, const void* tod, int tod_f32, const double* base,
-                               double bsign, const double* m4, const uint8_t* valid, const int32_t* nvalid,
-                               double* out, CgCtl* ctl, double* partials, hipStream_t st) {
+                               double bsign, const double* m4, const uint8_t* valid, double* out, hipStream_t st) {
   if (psi_f32) {
     if (tod_f32)
-      unbin_dispatch<float, float>(v, tod, base, bsign, m4, valid, nvalid, out, ctl, partials, st);
+      unbin_dispatch<float, float>(v, tod, base, bsign, m4, valid, out, st);
     else
-      unbin_dispatch<float, double>(v, tod, base, bsign, m4, valid, nvalid, out, ctl, partials, st);
+      unbin_dispatch<float, double>(v, tod, base, bsign, m4, valid, out, st);
   } else {
     if (tod_f32)
-      unbin_dispatch<double, float>(v, tod, base, bsign, m4, valid, nvalid, out, ctl, partials, st);
+      unbin_dispatch<double, float>(v, tod, base, bsign, m4, valid, out, st);
     else
-      unbin_dispatch<double, double>(v, tod, base, bsign, m4, valid, nvalid, out, ctl, partials, st);
+      unbin_dispatch<double, double>(v, tod, base, bsign, m4, valid, out, st);
   }
   return hipGetLastError();
 }

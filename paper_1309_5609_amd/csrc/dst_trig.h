@@ -18,12 +18,8 @@
 
 namespace dst {
 
-__host__ __device__ __forceinline__ void fast_sincos(double x, double* s_out, double* c_out) {
-  if (!(fabs(x) <= 1.0e5)) {
-    *s_out = sin(x);
-    *c_out = cos(x);
-    return;
-  }
+// fast_sincos for |x| <= 1e5 (any other x: unspecified values).
+__host__ __device__ __forceinline__ void fast_sincos_small(double x, double* s_out, double* c_out) {
   constexpr double kTwoOverPi = 0.6366197723675814;
   constexpr double C1 = 1.5707963267341256;
   constexpr double C2 = 6.077100506303966e-11;
@@ -61,6 +57,34 @@ __host__ __device__ __forceinline__ void fast_sincos(double x, double* s_out, do
   const double c = (q & 1) ? sr : cr;
   *s_out = (q & 2) ? -s : s;
   *c_out = ((q + 1) & 2) ? -c : c;
+}
+
+__host__ __device__ __forceinline__ void fast_sincos(double x, double* s_out, double* c_out) {
+  if (!(fabs(x) <= 1.0e5)) {
+    *s_out = sin(x);
+    *c_out = cos(x);
+    return;
+  }
+  fast_sincos_small(x, s_out, c_out);
+}
+
+// Four at once: no branch between them unless an argument is large, so that
+// their chains interleave.
+__host__ __device__ __forceinline__ void fast_sincos4(const double (&x)[4], double (&s)[4], double (&c)[4]) {
+  bool large = false;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    fast_sincos_small(x[k], &s[k], &c[k]);
+    large |= !(fabs(x[k]) <= 1.0e5);
+  }
+  if (large) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if (fabs(x[k]) <= 1.0e5) continue;
+      s[k] = sin(x[k]);
+      c[k] = cos(x[k]);
+    }
+  }
 }
 
 }  // namespace dst
