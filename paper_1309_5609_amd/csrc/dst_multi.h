@@ -125,11 +125,20 @@ hipError_t launch_multi_canonicalise(const View& v, const Multi& mu, double* a, 
 hipError_t launch_multi_resid(const View& v, const Multi& mu, const double* b, const double* ka, const double* J,
                               MultiCtl* ctl, double* partials, hipStream_t st);
 
-// Column ri of a multi vector -> [n_streams][n_b].
-hipError_t launch_multi_extract(const View& v, const Multi& mu, int ri, const double* x, double* out,
-                                hipStream_t st);
-// Column ri of the maps -> full-sky user map [n_pix][3]: md - m (m may be NULL), zero where unobserved.
-hipError_t launch_multi_scatter(const View& full, const View& vc, const int32_t* cid, const Multi& mu, int ri,
-                                const double* md, const double* m, double* out3, hipStream_t st);
+// User arrays of every right-hand side r: baselines [n_streams][n_b] (never
+// NULL); destriped and binned maps [n_pix][3] and hits [n_pix] (any may be
+// NULL; any_pixel: not all of them are).
+struct MultiOut {
+  double* baselines[kMaxRhs];
+  double* maps[kMaxRhs];
+  double* binned[kMaxRhs];
+  int32_t* hits[kMaxRhs];
+  int any_pixel;
+};
+// Baselines a, binned map md, destriped map md - m (0 where unobserved) and
+// hits of every right-hand side into the user arrays.
+hipError_t launch_multi_outputs(const View& full, const View& vc, const int32_t* cid, const int32_t* chits,
+                                const Multi& mu, const double* a, const double* md, const double* m,
+                                const MultiOut& out, hipStream_t st);
 
 }  // namespace dst
