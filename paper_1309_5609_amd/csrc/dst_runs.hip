@@ -1314,22 +1314,29 @@ __global__ void __launch_bounds__(kBlock) k_unbin_runs(View v, const uint32_t* _
                                                        partials, blockIdx.x, gridDim.x);
 }
 
-// Stable sort of the runs by pixel: onesweep passes of ten bits, so the
+// Stable sort of the runs by pixel in onesweep passes of ten bits, so the
 // 20-bit pixel indices of N_side 256 take two passes where the library's
 // eight-bit passes take three (setup 6.29 -> 6.09 ms on the 30-day workload;
-// eleven bits: 6.12 ms).
-constexpr unsigned kRunSortBits = 10;
+// eleven bits: 6.12 ms).  Indices of 21 and 22 bits (N_side 512) take eleven:
+// two passes instead of three.
+template <unsigned BITS>
 using RunSortConfig = rocprim::radix_sort_config<
     rocprim::default_config, rocprim::default_config,
-    rocprim::radix_sort_onesweep_config<rocprim::kernel_config<1024, 16>, rocprim::kernel_config<1024, 16>,
-                                        kRunSortBits, rocprim::block_radix_rank_algorithm::match>>;
-// Pixels by first visit (keys 0..n_t): the same passes, also below the
+    rocprim::radix_sort_onesweep_config<rocprim::kernel_config<1024, 16>, rocprim::kernel_config<1024, 16>, BITS,
+                                        rocprim::block_radix_rank_algorithm::match>>;
+template <typename Keys, typename Vals>
+hipError_t sort_runs(void* tmp, size_t& bytes, Keys& keys, Vals& vals, size_t n, unsigned bits, hipStream_t st) {
+  if (bits > 20 && bits <= 22)
+    return rocprim::radix_sort_pairs<RunSortConfig<11>>(tmp, bytes, keys, vals, n, 0u, bits, st);
+  return rocprim::radix_sort_pairs<RunSortConfig<10>>(tmp, bytes, keys, vals, n, 0u, bits, st);
+}
+// Pixels by first visit (keys 0..n_t): ten-bit passes, also below the
 // library's merge-sort limit (its merge sort took about 130 us for the
 // 786,432 pixels of N_side 256).
 using PixSortConfig = rocprim::radix_sort_config<
     rocprim::default_config, rocprim::default_config,
-    rocprim::radix_sort_onesweep_config<rocprim::kernel_config<1024, 16>, rocprim::kernel_config<1024, 16>,
-                                        kRunSortBits, rocprim::block_radix_rank_algorithm::match>,
+    rocprim::radix_sort_onesweep_config<rocprim::kernel_config<1024, 16>, rocprim::kernel_config<1024, 16>, 10u,
+                                        rocprim::block_radix_rank_algorithm::match>,
     0>;
 
 // Key bits to sort: keys run over 0..n_pix - 1.
@@ -1357,7 +1364,7 @@ hipError_t runs_tmp_bytes(int64_t n_t, int64_t n_pix, int64_t n_b, size_t* bytes
   {
     rocprim::double_buffer<uint32_t> keys(nullptr, nullptr);
     rocprim::double_buffer<uint32_t> vals(nullptr, nullptr);
-    DST_CHECK(rocprim::radix_sort_pairs<RunSortConfig>(nullptr, b, keys, vals, (size_t)n_t, 0u, key_bits(n_pix)));
+    DST_CHECK(sort_runs(nullptr, b, keys, vals, (size_t)n_t, key_bits(n_pix), nullptr));
   }
   size_t d = 0;
   {
@@ -1477,7 +1484,7 @@ hipError_t runs_build(const View& v, int psi_f32, const void* tod, int tod_f32, 
     rocprim::double_buffer<uint32_t> keys(W.keys[0], W.keys[1]);
     rocprim::double_buffer<uint32_t> vals(W.vals[0], W.vals[1]);
     size_t tmp = W.tmp_bytes;
-    DST_CHECK(rocprim::radix_sort_pairs<RunSortConfig>(W.tmp, tmp, keys, vals, (size_t)R, 0u, key_bits(n_pix), st));
+    DST_CHECK(sort_runs(W.tmp, tmp, keys, vals, (size_t)R, key_bits(n_pix), st));
     W.rperm = vals.current();
     hipLaunchKernelGGL(k_key_segments, dim3(gr), dim3(kBlock), 0, st, keys.current(), R, W.seg);
     DST_CHECK(hipGetLastError());
