@@ -297,7 +297,7 @@ int dst_pointing_expand(dst_ctx* ctx, const dst_scan* scan, int64_t nside, int64
  *   out [n_samples] of out_dtype (DST_F32 or DST_F64); with flags
  *       DST_NOISE_ACCUMULATE the noise is added to what out holds.
  * Stream-ordered; the call waits for its stream before returning.  Work
- * memory: two buffers of up to 256 MiB in the context. */
+ * memory: a buffer of 512 MiB (or one pair of segments) at most in the context. */
 enum { DST_NOISE_ACCUMULATE = 1u };
 int dst_noise_generate(dst_ctx* ctx, uint64_t seed, uint64_t stream_id, int64_t n_samples, int64_t segment,
                        double sample_rate_hz, double sigma, double fknee_hz, double alpha, void* out,

@@ -1988,14 +1988,12 @@ int dst_noise_generate(dst_ctx* ctx, uint64_t seed, uint64_t stream_id, int64_t 
   ctx->err.clear();
   DeviceGuard g(ctx->device);
   hipStream_t st = static_cast<hipStream_t>(stream);
-  const size_t nbuf = (size_t)dst::noise_pairs_per_chunk(segment) * (size_t)segment;
-  double2 *b0 = nullptr, *b1 = nullptr;
-  DST_TRY(ws(ctx, "noise_b0", nbuf, &b0));
-  DST_TRY(ws(ctx, "noise_b1", nbuf, &b1));
+  double2* buf = nullptr;
+  DST_TRY(ws(ctx, "noise_buf", (size_t)dst::noise_buffer_count(segment), &buf));
   double2* tw = nullptr;
   DST_TRY(ws(ctx, "noise_tw", (size_t)dst::noise_twiddle_count(segment), &tw));
   HIP_TRY(dst::launch_noise(seed, stream_id, n_samples, segment, sample_rate_hz, sigma, fknee_hz, alpha, out,
-                            out_dtype == DST_F32, (flags & DST_NOISE_ACCUMULATE) ? 1 : 0, b0, b1, tw, st));
+                            out_dtype == DST_F32, (flags & DST_NOISE_ACCUMULATE) ? 1 : 0, buf, tw, st));
   HIP_TRY(hipStreamSynchronize(st));
   return DST_OK;
 }

@@ -10,21 +10,21 @@
 //   u1 in (0, 1], u2 in [0, 1): sqrt(-2 ln u1) (cos 2 pi u2, sin 2 pi u2).
 // * Filter: segments of S = 2^m samples; two real segments travel as the real
 //   and imaginary parts of one complex transform (the gain is real and even
-//   in frequency, so it acts on each part separately); self-sorting
-//   Stockham passes of radix up to 256, each computed in LDS (see fft), gain
+//   in frequency, so it acts on each part separately): forward transform, gain
 //   sqrt(1 + (f_k / |f|)^alpha) with the zero-frequency bin kept, inverse
 //   transform, 1/S.  The last segment is drawn at full length and cut.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
+#include <type_traits>
 
 #include "dst_internal.h"
 
 namespace dst {
 namespace {
 
-constexpr int kBlock = 256;
 constexpr uint64_t kM0 = 0xD2E7470EE14C6C93ull, kM1 = 0xCA5A826395121157ull;
 constexpr uint64_t kW0 = 0x9E3779B97F4A7C15ull, kW1 = 0xBB67AE8584CAA73Bull;
 
@@ -62,121 +62,313 @@ __device__ __forceinline__ void normals4(uint64_t seed, uint64_t stream, uint64_
   }
 }
 
-// buf[p][k] = sigma (white(seg 2 (p0 + p), k), white(seg 2 (p0 + p) + 1, k)); imaginary part 0 past n_seg.
-__global__ void __launch_bounds__(kBlock) k_white_pairs(uint64_t seed, uint64_t stream, int64_t p0, int64_t n_pairs,
-                                                        int64_t n_seg, int64_t S, double sigma,
-                                                        double2* __restrict__ buf) {
-  const int64_t nb = S / 4;
-  for (int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; g < n_pairs * nb;
-       g += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t p = g / nb, b = g - p * nb;
-    const int64_t sa = 2 * (p0 + p), sb = sa + 1;
-    double za[4], zb[4] = {0.0, 0.0, 0.0, 0.0};
-    normals4(seed, stream, (uint64_t)sa, (uint64_t)b, za);
-    if (sb < n_seg) normals4(seed, stream, (uint64_t)sb, (uint64_t)b, zb);
-    double2* o = buf + p * S + 4 * b;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) o[i] = make_double2(sigma * za[i], sigma * zb[i]);
-  }
-}
-
 __device__ __forceinline__ double2 cmul(double2 a, double2 b) {
   return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
 }
+__device__ __forceinline__ double2 cadd(double2 a, double2 b) { return make_double2(a.x + b.x, a.y + b.y); }
+__device__ __forceinline__ double2 csub(double2 a, double2 b) { return make_double2(a.x - b.x, a.y - b.y); }
 
 // ---------------------------------------------------------------- FFT
-// Self-sorting (Stockham) transform of length S = 2^m in passes of radix
-// R = 2^r (r <= kFftMaxLog, the bits of m spread evenly over the passes).
-// Pass with span Ns (the product of the earlier radices), for column j of
-// each transform (0 <= j < T = S / R, k = j mod Ns):
-//   v_r = x[j + r T] w^{r k},  w = exp(sign 2 pi i / (Ns R)),
-//   X_q = sum_r v_r exp(sign 2 pi i r q / R),
-//   y[(j / Ns) Ns R + k + q Ns] = X_q.
-// A workgroup holds TC = kFftElems / R columns in LDS (loaded so that
-// neighbouring lanes touch neighbouring addresses) and computes their
-// length-R transforms there by the same recursion with radices 2 and 4, so a
-// pass reads and writes each value once.  Twiddles: w^E for E in units of
-// 1 / S of a turn, from two tables, hi[E >> h] lo[E mod 2^h], made once per
-// length with sincospi.
-constexpr int kFftElems = 2048;  // complex values per workgroup
-constexpr int kFftMaxLog = 8;
+// In place, in tiles of kElems values held by one workgroup, kPer per thread.
+//
+// S = R_1 .. R_P C.  Forward, pass p takes every block of length S' = S / (R_1
+// .. R_{p-1}) as R = R_p rows of M = S' / R values: the columns' length-R
+// transforms, times w_S'^(k q) (column k, row q), stored where they were, so
+// that row q is the next pass's block.  The blocks of C contiguous values left
+// at the end are transformed whole; bin f = q_1 + R_1 (q_2 + R_2 f') of the
+// spectrum sits at place f' of block (q_1, q_2).  The gain is applied there,
+// and the inverse transform undoes the passes in the opposite order, so the
+// spectrum is never brought into order.  Nothing is stored between drawing
+// the normals and the first pass, around the gain, or between the last pass
+// and the output: for segments of 2^13 to 2^22 samples a value moves through
+// memory five times (three kernels, 80 bytes per complex value with the
+// output), up to 2^12 not at all.  (Separate kernels for normals, three passes
+// each way between two buffers, and output moved 240 bytes.)  43 M samples
+// accumulated, before and now: segments of 2^17 (FP32) 1.49 and 0.61 ms, 2^20
+// 1.60 and 0.70, 2^22 2.06 and 0.96; 130 M samples in segments of 2^24 5.9 and
+// 2.7 ms.  The first kernel is bound by the generator's integer and FP64
+// operations, the others by memory traffic.
+//
+// Inside a tile: self-sorting stages of radix 8 (and one of 2 or 4) between
+// LDS exchanges, the first from and the last to registers.
+constexpr int kLogElems = 12;
+constexpr int kElems = 1 << kLogElems;  // complex values per workgroup
+constexpr int kThreads = 512;
+constexpr int kPer = kElems / kThreads;
+// Complex values of the buffer (512 MiB): 43 M samples in segments of 2^22 take
+// 0.93 ms; with a quarter, which stays in the last-level cache, 1.08 (shorter
+// launches), with twice as many 0.93.
+constexpr int kLogChunk = 25;
+// Largest radix of a column pass: 4 columns (64 bytes) side by side, of which
+// the neighbouring tile completes the cache lines.  Segments of 2^22 take 0.93
+// ms with one pass of 2^10 and 1.1 with two of 2^5.
+constexpr int kLogCol = 10;
+static_assert(kPer == 8, "one radix-8 butterfly per thread");
 
+// LDS place of value i of a tile: one value of padding after every eight, so
+// that the strided writes of a stage spread over the banks.
+__device__ __forceinline__ int pad(int i) { return i + (i >> 3); }
+constexpr int kLds = kElems + kElems / 8;
+
+// exp(-2 pi i E / S) from two tables: hi[a] = exp(-2 pi i a 2^h / S), lo[b] =
+// exp(-2 pi i b / S); W[i] = exp(-2 pi i i / kElems) serves the tiles.
 struct Twiddles {
-  const double2* hi;  // exp(-2 pi i a 2^h / S), a < S / 2^h
-  const double2* lo;  // exp(-2 pi i b / S), b < 2^h
+  const double2* hi;
+  const double2* lo;
+  const double2* W;
   int h;
   int64_t S;
 };
-
-// exp(sign 2 pi i E / S)
-__device__ __forceinline__ double2 twiddle(const Twiddles& t, int64_t E, double sign) {
-  E &= t.S - 1;
-  double2 w = cmul(t.hi[E >> t.h], t.lo[E & (((int64_t)1 << t.h) - 1)]);
-  if (sign > 0.0) w.y = -w.y;
-  return w;
+__device__ __forceinline__ double2 twiddle(const Twiddles& t, uint32_t E) {
+  E &= (uint32_t)t.S - 1u;
+  return cmul(t.hi[E >> t.h], t.lo[E & ((1u << t.h) - 1u)]);
+}
+template <int DIR>
+__device__ __forceinline__ double2 toward(double2 w) {
+  return DIR < 0 ? w : make_double2(w.x, -w.y);
 }
 
-__global__ void __launch_bounds__(kBlock) k_twiddles(double2* __restrict__ hi, double2* __restrict__ lo, int h,
-                                                     int m) {
-  const int64_t nh = (int64_t)1 << (m - h), nl = (int64_t)1 << h;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nh + nl; i += (int64_t)gridDim.x * blockDim.x) {
-    // angle -2 pi x, x = a / nh or b / S, as sincospi of -2x (exact arguments)
+__global__ void __launch_bounds__(256) k_twiddles(double2* __restrict__ hi, double2* __restrict__ lo,
+                                                  double2* __restrict__ W, int h, int m) {
+  const int nh = 1 << (m - h), nl = 1 << h;
+  for (int i = (int)(blockIdx.x * blockDim.x + threadIdx.x); i < nh + nl + kElems; i += (int)(gridDim.x * blockDim.x)) {
+    // angle -2 pi x as sincospi of -2x (exact arguments)
+    const double x = i < nh ? (double)i / (double)nh
+                            : (i < nh + nl ? (double)(i - nh) / ((double)nh * (double)nl)
+                                           : (double)(i - nh - nl) / (double)kElems);
     double s, c;
-    if (i < nh) {
-      sincospi(-2.0 * (double)i / (double)nh, &s, &c);
-      hi[i] = make_double2(c, s);
-    } else {
-      sincospi(-2.0 * (double)(i - nh) / (double)(nh * nl), &s, &c);
-      lo[i - nh] = make_double2(c, s);
+    sincospi(-2.0 * x, &s, &c);
+    (i < nh ? hi[i] : (i < nh + nl ? lo[i - nh] : W[i - nh - nl])) = make_double2(c, s);
+  }
+}
+
+// w[q] = w_S^(b + q e) (DIR < 0) or its conjugate, from table entries for b, e,
+// 2 e and 4 e, at most three products deep.
+template <int RAD, int DIR>
+__device__ __forceinline__ void powers(const Twiddles& t, uint32_t b, uint32_t e, double2 (&w)[RAD]) {
+  w[0] = toward<DIR>(twiddle(t, b));
+  w[1] = cmul(w[0], toward<DIR>(twiddle(t, e)));
+  if constexpr (RAD >= 4) {
+    const double2 s2 = toward<DIR>(twiddle(t, 2 * e));
+    w[2] = cmul(w[0], s2);
+    w[3] = cmul(w[1], s2);
+    if constexpr (RAD == 8) {
+      const double2 s4 = toward<DIR>(twiddle(t, 4 * e));
+#pragma unroll
+      for (int q = 0; q < 4; ++q) w[4 + q] = cmul(w[q], s4);
     }
   }
 }
 
-// One radix-RAD stage of the in-LDS transforms of length R (columns of
-// stride LS), span ns; WR[i] = exp(sign 2 pi i i / R).
-template <int RAD>
-__device__ __forceinline__ void lds_stage(double2* L, int R, int LS, int ns, const double2* WR, double sign) {
-  constexpr int PER = kFftElems / RAD / kBlock;  // butterflies per thread
-  const int nbf = R / RAD;
-  double2 v[PER][RAD];
+template <int DIR>
+__device__ __forceinline__ double2 times_i(double2 a) {  // DIR i a
+  return DIR < 0 ? make_double2(a.y, -a.x) : make_double2(-a.y, a.x);
+}
+template <int RAD, int DIR>
+__device__ __forceinline__ void butterfly(double2* v) {
+  if constexpr (RAD == 2) {
+    const double2 a = v[0];
+    v[0] = cadd(a, v[1]);
+    v[1] = csub(a, v[1]);
+  } else if constexpr (RAD == 4) {
+    const double2 t0 = cadd(v[0], v[2]), t1 = csub(v[0], v[2]);
+    const double2 t2 = cadd(v[1], v[3]), t3 = times_i<DIR>(csub(v[1], v[3]));
+    v[0] = cadd(t0, t2);
+    v[1] = cadd(t1, t3);
+    v[2] = csub(t0, t2);
+    v[3] = csub(t1, t3);
+  } else {
+    double2 a[4] = {v[0], v[2], v[4], v[6]}, b[4] = {v[1], v[3], v[5], v[7]};
+    butterfly<4, DIR>(a);
+    butterfly<4, DIR>(b);
+    constexpr double h = 0.70710678118654752440;
+    const double2 i1 = times_i<DIR>(b[1]), i3 = times_i<DIR>(b[3]);
+    b[1] = make_double2(h * (b[1].x + i1.x), h * (b[1].y + i1.y));
+    b[2] = times_i<DIR>(b[2]);
+    b[3] = make_double2(h * (i3.x - b[3].x), h * (i3.y - b[3].y));
 #pragma unroll
-  for (int i = 0; i < PER; ++i) {
-    const int idx = threadIdx.x + kBlock * i;
-    const int c = idx / nbf, j = idx - c * nbf;
-#pragma unroll
-    for (int q = 0; q < RAD; ++q) v[i][q] = L[c * LS + j + q * nbf];
-  }
-  __syncthreads();
-#pragma unroll
-  for (int i = 0; i < PER; ++i) {
-    const int idx = threadIdx.x + kBlock * i;
-    const int c = idx / nbf, j = idx - c * nbf;
-    const int k = j & (ns - 1);
-    if (ns > 1) {
-      const int unit = R / (ns * RAD);
-#pragma unroll
-      for (int q = 1; q < RAD; ++q) v[i][q] = cmul(v[i][q], WR[q * k * unit]);
+    for (int q = 0; q < 4; ++q) {
+      v[q] = cadd(a[q], b[q]);
+      v[q + 4] = csub(a[q], b[q]);
     }
-    double2 X[RAD];
-    if (RAD == 2) {
-      X[0] = make_double2(v[i][0].x + v[i][1].x, v[i][0].y + v[i][1].y);
-      X[1] = make_double2(v[i][0].x - v[i][1].x, v[i][0].y - v[i][1].y);
-    } else {
-      const double2 t0 = make_double2(v[i][0].x + v[i][2].x, v[i][0].y + v[i][2].y);
-      const double2 t1 = make_double2(v[i][0].x - v[i][2].x, v[i][0].y - v[i][2].y);
-      const double2 t2 = make_double2(v[i][1].x + v[i][3].x, v[i][1].y + v[i][3].y);
-      const double2 d = make_double2(v[i][1].x - v[i][3].x, v[i][1].y - v[i][3].y);
-      const double2 t3 = make_double2(-sign * d.y, sign * d.x);  // (sign i) d
-      X[0] = make_double2(t0.x + t2.x, t0.y + t2.y);
-      X[2] = make_double2(t0.x - t2.x, t0.y - t2.y);
-      X[1] = make_double2(t1.x + t3.x, t1.y + t3.y);
-      X[3] = make_double2(t1.x - t3.x, t1.y - t3.y);
-    }
-    const int o = (j / ns) * ns * RAD + k;
-#pragma unroll
-    for (int q = 0; q < RAD; ++q) L[c * LS + o + q * ns] = X[q];
   }
-  __syncthreads();
+}
+
+// Stage of span 2^LOGNS of a length-2^LOGR transform in direction DIR: its log
+// radix.  The odd stage comes first forward and last backward, so that the
+// forward transform ends, and the backward one starts, with the same radix.
+template <int LOGR, int DIR>
+__host__ __device__ constexpr int log_radix(int log_ns) {
+  return LOGR < 3 ? LOGR
+                  : (DIR < 0 ? (log_ns == 0 && LOGR % 3 ? LOGR % 3 : 3) : (LOGR - log_ns >= 3 ? 3 : LOGR - log_ns));
+}
+
+// Transforms of the tile's 2^(kLogElems - LOGR) columns.  Thread values v[i
+// RAD + q]: butterfly i = column c, j with (c, j) = column(i) holds rows j + q
+// R / RAD on entry (RAD of the first stage) and on return (of the last).
+template <int LOGR>
+__device__ __forceinline__ void column(int i, int& c, int& j) {
+  const int idx = (int)threadIdx.x + kThreads * i;
+  c = idx & ((kElems >> LOGR) - 1);
+  j = idx >> (kLogElems - LOGR);
+}
+template <int LOGR, int DIR, int LOGNS = 0>
+__device__ __forceinline__ void fft_tile(double2 (&v)[kPer], double2* L, const double2* __restrict__ W) {
+  constexpr int LR = log_radix<LOGR, DIR>(LOGNS), RAD = 1 << LR, LOGTC = kLogElems - LOGR;
+#pragma unroll
+  for (int i = 0; i < kPer / RAD; ++i) {
+    int c, j;
+    column<LOGR>(i, c, j);
+    if constexpr (LOGNS > 0) {
+      // powers s^q of the butterfly's factor: 1, 2 and 4 from the table, the
+      // others at most two products deep (as many roundings as a product of two
+      // table entries for every power)
+      const int e = (j & ((1 << LOGNS) - 1)) << (kLogElems - LR - LOGNS);
+      double2 w[8];
+      w[1] = toward<DIR>(W[e]);
+      if constexpr (RAD >= 4) {
+        w[2] = toward<DIR>(W[2 * e]);
+        w[3] = cmul(w[2], w[1]);
+      }
+      if constexpr (RAD == 8) {
+        w[4] = toward<DIR>(W[4 * e]);
+#pragma unroll
+        for (int q = 1; q < 4; ++q) w[4 + q] = cmul(w[4], w[q]);
+      }
+#pragma unroll
+      for (int q = 1; q < RAD; ++q) v[i * RAD + q] = cmul(v[i * RAD + q], w[q]);
+    }
+    butterfly<RAD, DIR>(v + i * RAD);
+  }
+  if constexpr (LOGNS + LR < LOGR) {
+    constexpr int LR2 = log_radix<LOGR, DIR>(LOGNS + LR), RAD2 = 1 << LR2;
+    __syncthreads();  // the values of the exchange before are read
+#pragma unroll
+    for (int i = 0; i < kPer / RAD; ++i) {
+      int c, j;
+      column<LOGR>(i, c, j);
+      const int row = ((j >> LOGNS) << (LOGNS + LR)) + (j & ((1 << LOGNS) - 1));
+#pragma unroll
+      for (int q = 0; q < RAD; ++q) L[pad(((row + (q << LOGNS)) << LOGTC) + c)] = v[i * RAD + q];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kPer / RAD2; ++i) {
+      int c, j;
+      column<LOGR>(i, c, j);
+#pragma unroll
+      for (int q = 0; q < RAD2; ++q) v[i * RAD2 + q] = L[pad(((j + (q << (LOGR - LR2))) << LOGTC) + c)];
+    }
+    fft_tile<LOGR, DIR, LOGNS + LR>(v, L, W);
+  }
+}
+
+// What the first pass draws and the last pass writes.
+struct Draw {
+  uint64_t seed = 0, stream = 0;
+  int64_t p0 = 0, n_seg = 0;  // first segment pair of the chunk, segments in all
+  double sigma = 0.0;
+};
+struct Out {
+  void* out = nullptr;
+  int64_t n = 0;
+  double inv_s = 0.0;
+  int accumulate = 0;
+};
+
+// Normals 4 b .. 4 b + 3 of pair p (sigma times; imaginary part 0 past n_seg).
+__device__ __forceinline__ void draw_pair(const Draw& d, int64_t p, int64_t b, double2 (&z)[4]) {
+  const int64_t sa = 2 * (d.p0 + p), sb = sa + 1;
+  double za[4], zb[4] = {0.0, 0.0, 0.0, 0.0};
+  normals4(d.seed, d.stream, (uint64_t)sa, (uint64_t)b, za);
+  if (sb < d.n_seg) normals4(d.seed, d.stream, (uint64_t)sb, (uint64_t)b, zb);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) z[i] = make_double2(d.sigma * za[i], d.sigma * zb[i]);
+}
+// Value k of pair p to the timeline.
+template <typename OT>
+__device__ __forceinline__ void emit(const Out& o, const Draw& d, int64_t S, int64_t p, int64_t k, double2 v) {
+  OT* out = static_cast<OT*>(o.out);
+  const int64_t ta = 2 * (d.p0 + p) * S + k, tb = ta + S;
+  if (ta < o.n) out[ta] = o.accumulate ? (OT)((double)out[ta] + v.x * o.inv_s) : (OT)(v.x * o.inv_s);
+  if (tb < o.n) out[tb] = o.accumulate ? (OT)((double)out[tb] + v.y * o.inv_s) : (OT)(v.y * o.inv_s);
+}
+
+// Workgroups of one XCD (workgroup i runs on XCD i mod 8) take neighbouring
+// tiles, whose rows share cache lines.
+__device__ __forceinline__ int64_t tile_of(int64_t n) {
+  const int64_t i = blockIdx.x;
+  return n % 8 == 0 ? (i & 7) * (n / 8) + (i >> 3) : i;
+}
+
+// Column pass of radix 2^LOGR over blocks of length 2^log_s.  FIRST (forward):
+// the values are drawn instead of read; LAST (backward): they go to the
+// timeline instead.
+enum { COL_READ = 0, COL_FIRST = 1, COL_LAST = 2 };
+template <int LOGR, int DIR, int MODE, typename OT>
+__global__ void __launch_bounds__(kThreads) k_columns(double2* __restrict__ x, int log_s, int64_t n_tiles, Twiddles tw,
+                                                      Draw d, Out o) {
+  constexpr int LOGTC = kLogElems - LOGR;
+  constexpr int LR0 = log_radix<LOGR, DIR>(0), RAD0 = 1 << LR0;
+  constexpr int LRZ = DIR < 0 ? log_radix<LOGR, DIR>(LOGR - log_radix<LOGR, 1>(0)) : (LOGR % 3 && LOGR > 3 ? LOGR % 3 : LR0);
+  constexpr int RADZ = 1 << LRZ;
+  __shared__ double2 L[kLds];
+  const int log_m = log_s - LOGR;
+  const int64_t g0 = tile_of(n_tiles) << LOGTC;  // first column
+  const int64_t blk = g0 >> log_m;
+  const uint32_t k0 = (uint32_t)(g0 & (((int64_t)1 << log_m) - 1));
+  double2* base = x + (blk << log_s) + k0;
+  const uint32_t unit = (uint32_t)(tw.S >> log_s);  // w_S' in units of w_S
+  double2 v[kPer];
+  if constexpr (MODE == COL_FIRST) {
+#pragma unroll
+    for (int t = 0; t < kElems / 4 / kThreads; ++t) {
+      const int i = 4 * ((int)threadIdx.x + kThreads * t), row = i >> LOGTC, c = i & ((1 << LOGTC) - 1);
+      double2 z[4];
+      draw_pair(d, blk, (((int64_t)row << log_m) + k0 + c) >> 2, z);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) L[pad(i + k)] = z[k];
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int i = 0; i < kPer / RAD0; ++i) {
+    int c, j;
+    column<LOGR>(i, c, j);
+#pragma unroll
+    for (int q = 0; q < RAD0; ++q) {
+      const int row = j + (q << (LOGR - LR0));
+      v[i * RAD0 + q] = MODE == COL_FIRST ? L[pad((row << LOGTC) + c)] : base[((int64_t)row << log_m) + c];
+    }
+    if constexpr (DIR > 0) {  // undo the forward pass's factors
+      const uint32_t k = (k0 + c) * unit;
+      double2 w[RAD0];
+      powers<RAD0, DIR>(tw, k * j, k << (LOGR - LR0), w);
+#pragma unroll
+      for (int q = 0; q < RAD0; ++q) v[i * RAD0 + q] = cmul(v[i * RAD0 + q], w[q]);
+    }
+  }
+  fft_tile<LOGR, DIR>(v, L, tw.W);
+#pragma unroll
+  for (int i = 0; i < kPer / RADZ; ++i) {
+    int c, j;
+    column<LOGR>(i, c, j);
+    if constexpr (DIR < 0) {
+      const uint32_t k = (k0 + c) * unit;
+      double2 w[RADZ];
+      powers<RADZ, DIR>(tw, k * j, k << (LOGR - LRZ), w);
+#pragma unroll
+      for (int q = 0; q < RADZ; ++q) v[i * RADZ + q] = cmul(v[i * RADZ + q], w[q]);
+    }
+#pragma unroll
+    for (int q = 0; q < RADZ; ++q) {
+      const int64_t at = ((int64_t)(j + (q << (LOGR - LRZ))) << log_m) + c;
+      if constexpr (MODE == COL_LAST)
+        emit<OT>(o, d, tw.S, blk, k0 + at, v[i * RADZ + q]);
+      else
+        base[at] = v[i * RADZ + q];
+    }
+  }
 }
 
 // The gain of Eq. 1's filter at bin k of a length-S transform:
@@ -186,90 +378,79 @@ struct Gain {
 };
 __device__ __forceinline__ double gain_at(const Gain& G, int64_t k, int64_t S) {
   const int64_t kk = k <= S / 2 ? k : S - k;
-  if (kk == 0) return 1.0;
+  if (kk == 0 || !(G.fknee > 0.0)) return 1.0;
   return sqrt(1.0 + pow(G.fknee / ((double)kk * G.df), G.alpha));
 }
 
-// One pass of radix R = 2^LOGR over `batch` transforms of length S, span Ns;
-// with G.fknee > 0 (first pass only) the inputs are first scaled by the gain
-// of their bin.
-template <int LOGR>
-__global__ void __launch_bounds__(kBlock) k_fft_lds(const double2* __restrict__ in, double2* __restrict__ out,
-                                                    int64_t S, int64_t Ns, int64_t batch, double sign, Twiddles tw,
-                                                    Gain G) {
-  constexpr int R = 1 << LOGR, TC = kFftElems / R, LS = R + 1;  // LS: padded column stride
-  __shared__ double2 L[TC * LS];
-  __shared__ double2 WR[R];
-  for (int i = threadIdx.x; i < R; i += kBlock) WR[i] = twiddle(tw, (int64_t)i * (S / R), sign);
-  const int64_t T = S / R, ncol = batch * T;
-  const bool in_cfast = T >= TC, out_cfast = Ns >= TC;  // lane order that keeps accesses contiguous
-  for (int64_t g0 = (int64_t)blockIdx.x * TC; g0 < ncol; g0 += (int64_t)gridDim.x * TC) {
-#pragma unroll 4
-    for (int i = 0; i < kFftElems / kBlock; ++i) {
-      const int idx = threadIdx.x + kBlock * i;
-      const int c = in_cfast ? idx % TC : idx / R, r = in_cfast ? idx / TC : idx % R;
-      const int64_t g = g0 + c;
-      double2 x = make_double2(0.0, 0.0);
-      if (g < ncol) {
-        const int64_t bt = g / T, j = g - bt * T;
-        x = in[bt * S + j + r * T];
-        const int64_t k = j & (Ns - 1);
-        if (Ns > 1 && r > 0) x = cmul(x, twiddle(tw, (int64_t)r * k * (S / (Ns * R)), sign));
-      }
-      L[c * LS + r] = x;
-    }
-    __syncthreads();
-    if (G.fknee > 0.0) {  // first pass (Ns = 1): element (c, r) is bin j + r T
-      for (int idx = threadIdx.x; idx < kFftElems; idx += kBlock) {
-        const int c = idx / R, r = idx % R;
-        const int64_t g = g0 + c;
-        if (g >= ncol) continue;
-        const int64_t j = g % T;
-        const double h = gain_at(G, j + r * T, S);
-        L[c * LS + r] = make_double2(L[c * LS + r].x * h, L[c * LS + r].y * h);
+// Blocks of 2^LOGR contiguous values: forward transform, gain, backward
+// transform.  WHOLE: the block is the whole segment (several pairs per tile),
+// drawn here and written to the timeline; else one block (q_1, q_2) of every
+// gridDim.y-th pair in turn, so that a thread's gains serve several pairs.
+template <int LOGR, bool WHOLE, typename OT>
+__global__ void __launch_bounds__(kThreads) k_blocks(double2* __restrict__ x, int log_s, int log_r1, int log_r2,
+                                                     int64_t batch, Twiddles tw, Gain G, Draw d, Out o) {
+  constexpr int LOGTC = kLogElems - LOGR;
+  constexpr int LR = log_radix<LOGR, 1>(0), RAD = 1 << LR;  // last stage forward, first backward
+  constexpr int LR0 = log_radix<LOGR, -1>(0), RAD0 = 1 << LR0;
+  constexpr int LRZ = LOGR % 3 && LOGR > 3 ? LOGR % 3 : LR, RADZ = 1 << LRZ;
+  static_assert(WHOLE || LOGR == kLogElems, "blocks of a longer segment fill a tile");
+  __shared__ double2 L[kLds];
+  const int64_t S = tw.S;
+  const int64_t blk = blockIdx.x;  // WHOLE: tile of pairs
+  // bin of place f' of the block: f0 + f' 2^(log_r1 + log_r2)
+  const int64_t f0 = WHOLE ? 0 : (blk >> log_r2) + ((blk & (((int64_t)1 << log_r2) - 1)) << log_r1);
+  double g[kPer];
+#pragma unroll
+  for (int i = 0; i < kPer / RAD; ++i) {
+    int c, j;
+    column<LOGR>(i, c, j);
+#pragma unroll
+    for (int q = 0; q < RAD; ++q)
+      g[i * RAD + q] = gain_at(G, f0 + ((int64_t)(j + (q << (LOGR - LR))) << (log_r1 + log_r2)), S);
+  }
+  const int64_t first = WHOLE ? blk << LOGTC : blockIdx.y, step = WHOLE ? batch : gridDim.y;
+  for (int64_t p = first; p < batch; p += step) {
+    double2* base = x + (p << log_s) + (blk << LOGR);
+    double2 v[kPer];
+    if constexpr (WHOLE) {
+#pragma unroll
+      for (int t = 0; t < kElems / 4 / kThreads; ++t) {
+        const int i = (int)threadIdx.x + kThreads * t, c = i & ((1 << LOGTC) - 1), b = i >> LOGTC;
+        double2 z[4] = {};
+        if (p + c < batch) draw_pair(d, p + c, b, z);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) L[pad(((4 * b + k) << LOGTC) + c)] = z[k];
       }
       __syncthreads();
     }
-    int ns = 1;
-    if (LOGR & 1) {
-      lds_stage<2>(L, R, LS, ns, WR, sign);
-      ns = 2;
-    }
-#pragma unroll 1
-    for (; ns < R; ns *= 4) lds_stage<4>(L, R, LS, ns, WR, sign);
-#pragma unroll 4
-    for (int i = 0; i < kFftElems / kBlock; ++i) {
-      const int idx = threadIdx.x + kBlock * i;
-      const int c = out_cfast ? idx % TC : idx / R, q = out_cfast ? idx / TC : idx % R;
-      const int64_t g = g0 + c;
-      if (g < ncol) {
-        const int64_t bt = g / T, j = g - bt * T;
-        out[bt * S + (j / Ns) * Ns * R + (j & (Ns - 1)) + q * Ns] = L[c * LS + q];
+#pragma unroll
+    for (int i = 0; i < kPer / RAD0; ++i) {
+      int c, j;
+      column<LOGR>(i, c, j);
+#pragma unroll
+      for (int q = 0; q < RAD0; ++q) {
+        const int row = j + (q << (LOGR - LR0));
+        v[i * RAD0 + q] = WHOLE ? L[pad((row << LOGTC) + c)] : base[row];
       }
     }
-    __syncthreads();  // the next column group reuses L
+    fft_tile<LOGR, -1>(v, L, tw.W);
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) v[k] = make_double2(v[k].x * g[k], v[k].y * g[k]);
+    fft_tile<LOGR, 1>(v, L, tw.W);
+#pragma unroll
+    for (int i = 0; i < kPer / RADZ; ++i) {
+      int c, j;
+      column<LOGR>(i, c, j);
+#pragma unroll
+      for (int q = 0; q < RADZ; ++q) {
+        const int row = j + (q << (LOGR - LRZ));
+        if constexpr (!WHOLE)
+          base[row] = v[i * RADZ + q];
+        else if (p + c < batch)
+          emit<OT>(o, d, S, p + c, row, v[i * RADZ + q]);
+      }
+    }
   }
-}
-
-template <typename OT>
-__global__ void __launch_bounds__(kBlock) k_unpack(const double2* __restrict__ buf, int64_t p0, int64_t n_pairs,
-                                                   int64_t S, int64_t n, double inv_s, int accumulate,
-                                                   OT* __restrict__ out) {
-  for (int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; g < n_pairs * S;
-       g += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t p = g / S, k = g - p * S;
-    const int64_t ta = 2 * (p0 + p) * S + k, tb = ta + S;
-    const double2 v = buf[g];
-    if (ta < n) out[ta] = accumulate ? (OT)((double)out[ta] + v.x * inv_s) : (OT)(v.x * inv_s);
-    if (tb < n) out[tb] = accumulate ? (OT)((double)out[tb] + v.y * inv_s) : (OT)(v.y * inv_s);
-  }
-}
-
-unsigned grid_for(int64_t n) {
-  int64_t g = (n + kBlock - 1) / kBlock;
-  if (g > 65536) g = 65536;
-  if (g < 1) g = 1;
-  return (unsigned)g;
 }
 
 int log2_of(int64_t S) {
@@ -278,83 +459,114 @@ int log2_of(int64_t S) {
   return m;
 }
 
-// Transform of `batch` segments through the two buffers (a holds the input);
-// returns the buffer holding the result.
-double2* fft(double2* a, double2* b, int64_t S, int64_t batch, double sign, const Twiddles& tw, const Gain& gain,
-             hipStream_t st) {
-  const int m = log2_of(S);
-  const int P = (m + kFftMaxLog - 1) / kFftMaxLog;  // passes
-  int64_t Ns = 1;
-  for (int p = 0; p < P; ++p) {
-    const int r = m / P + (p < m % P ? 1 : 0);
-    const int64_t groups = (batch * (S >> r) + (kFftElems >> r) - 1) / (kFftElems >> r);
-    const unsigned g = (unsigned)(groups < 65536 ? groups : 65536);
-    const Gain G = p == 0 ? gain : Gain{};
-    switch (r) {
-      case 1: hipLaunchKernelGGL(k_fft_lds<1>, dim3(g), dim3(kBlock), 0, st, a, b, S, Ns, batch, sign, tw, G); break;
-      case 2: hipLaunchKernelGGL(k_fft_lds<2>, dim3(g), dim3(kBlock), 0, st, a, b, S, Ns, batch, sign, tw, G); break;
-      case 3: hipLaunchKernelGGL(k_fft_lds<3>, dim3(g), dim3(kBlock), 0, st, a, b, S, Ns, batch, sign, tw, G); break;
-      case 4: hipLaunchKernelGGL(k_fft_lds<4>, dim3(g), dim3(kBlock), 0, st, a, b, S, Ns, batch, sign, tw, G); break;
-      case 5: hipLaunchKernelGGL(k_fft_lds<5>, dim3(g), dim3(kBlock), 0, st, a, b, S, Ns, batch, sign, tw, G); break;
-      case 6: hipLaunchKernelGGL(k_fft_lds<6>, dim3(g), dim3(kBlock), 0, st, a, b, S, Ns, batch, sign, tw, G); break;
-      case 7: hipLaunchKernelGGL(k_fft_lds<7>, dim3(g), dim3(kBlock), 0, st, a, b, S, Ns, batch, sign, tw, G); break;
-      default: hipLaunchKernelGGL(k_fft_lds<8>, dim3(g), dim3(kBlock), 0, st, a, b, S, Ns, batch, sign, tw, G); break;
-    }
-    double2* t = a;
-    a = b;
-    b = t;
-    Ns <<= r;
+// f(integral_constant<int, n>) for lo <= n <= hi.
+template <int LO, int HI, typename F>
+void by_int(int n, F&& f) {
+  if constexpr (LO <= HI) {
+    if (n == LO)
+      f(std::integral_constant<int, LO>{});
+    else
+      by_int<LO + 1, HI>(n, f);
   }
-  return a;
+}
+template <typename F>
+void by_type(int f32, F&& f) {
+  if (f32)
+    f(float{});
+  else
+    f(double{});
 }
 
 }  // namespace
 
 int64_t noise_twiddle_count(int64_t S) {
   const int m = log2_of(S), h = (m + 1) / 2;
-  return ((int64_t)1 << (m - h)) + ((int64_t)1 << h);
+  return ((int64_t)1 << (m - h)) + ((int64_t)1 << h) + kElems;
 }
 
+// Pairs filtered at a time: 2^kLogChunk complex values at most, or one pair.
 int64_t noise_pairs_per_chunk(int64_t S) {
-  const int64_t cap = (int64_t)1 << 24;  // complex values per buffer (256 MiB)
+  const int64_t cap = (int64_t)1 << kLogChunk;
   return S >= cap ? 1 : cap / S;
 }
 
+// The buffer holds whole segments only when they are longer than a tile.
+int64_t noise_buffer_count(int64_t S) { return S <= kElems ? 1 : noise_pairs_per_chunk(S) * S; }
+
 hipError_t launch_noise(uint64_t seed, uint64_t stream, int64_t n, int64_t S, double rate, double sigma, double fknee,
-                        double alpha, void* out, int out_f32, int accumulate, double2* buf0, double2* buf1,
-                        double2* twbuf, hipStream_t st) {
+                        double alpha, void* out, int out_f32, int accumulate, double2* buf, double2* twbuf,
+                        hipStream_t st) {
   if (S < 4 || (S & (S - 1))) return hipErrorInvalidValue;
   const int m = log2_of(S), h = (m + 1) / 2;
   Twiddles tw;
-  tw.hi = twbuf;
-  tw.lo = twbuf + ((int64_t)1 << (m - h));
+  double2 *hi = twbuf, *lo = hi + ((int64_t)1 << (m - h)), *W = lo + ((int64_t)1 << h);
+  tw.hi = hi;
+  tw.lo = lo;
+  tw.W = W;
   tw.h = h;
   tw.S = S;
-  hipLaunchKernelGGL(k_twiddles, dim3(grid_for(noise_twiddle_count(S))), dim3(kBlock), 0, st, twbuf,
-                     twbuf + ((int64_t)1 << (m - h)), h, m);
-  const int64_t n_seg = (n + S - 1) / S;
-  const int64_t n_pairs = (n_seg + 1) / 2;
+  hipLaunchKernelGGL(k_twiddles, dim3((unsigned)((noise_twiddle_count(S) + 255) / 256)), dim3(256), 0, st, hi, lo, W,
+                     h, m);
+  Gain gain;
+  if (fknee > 0.0) {
+    gain.fknee = fknee;
+    gain.alpha = alpha;
+    gain.df = rate / (double)S;
+  }
+  Draw d;
+  d.seed = seed;
+  d.stream = stream;
+  d.n_seg = (n + S - 1) / S;
+  d.sigma = sigma;
+  Out o;
+  o.out = out;
+  o.n = n;
+  o.inv_s = 1.0 / (double)S;
+  o.accumulate = accumulate;
+  const int64_t n_pairs = (d.n_seg + 1) / 2;
+  if (m <= kLogElems) {
+    const int64_t tiles = (n_pairs + (kElems >> m) - 1) / (kElems >> m);
+    if (tiles > 0x7fffffff) return hipErrorInvalidValue;
+    by_int<2, kLogElems>(m, [&](auto lr) {
+      by_type(out_f32, [&](auto ot) {
+        hipLaunchKernelGGL((k_blocks<decltype(lr)::value, true, decltype(ot)>), dim3((unsigned)tiles), dim3(kThreads),
+                           0, st, nullptr, m, 0, 0, n_pairs, tw, gain, d, o);
+      });
+    });
+    return hipGetLastError();
+  }
+  // column bits in one pass up to 2^kLogCol, else in two
+  const int bits = m - kLogElems;
+  const int r1 = bits <= kLogCol ? bits : (bits + 1) / 2, r2 = bits - r1;
   const int64_t chunk = noise_pairs_per_chunk(S);
   for (int64_t p0 = 0; p0 < n_pairs; p0 += chunk) {
     const int64_t np = n_pairs - p0 < chunk ? n_pairs - p0 : chunk;
-    hipLaunchKernelGGL(k_white_pairs, dim3(grid_for(np * (S / 4))), dim3(kBlock), 0, st, seed, stream, p0, np, n_seg,
-                       S, sigma, buf0);
-    double2* x = fft(buf0, buf1, S, np, -1.0, tw, Gain{}, st);
-    // the filter is applied as the inverse transform reads the spectrum
-    Gain gain;
-    if (fknee > 0.0) {
-      gain.fknee = fknee;
-      gain.alpha = alpha;
-      gain.df = rate / (double)S;
-    }
-    double2* other = x == buf0 ? buf1 : buf0;
-    x = fft(x, other, S, np, 1.0, tw, gain, st);
-    if (out_f32)
-      hipLaunchKernelGGL(k_unpack<float>, dim3(grid_for(S * np)), dim3(kBlock), 0, st, x, p0, np, S, n,
-                         1.0 / (double)S, accumulate, static_cast<float*>(out));
-    else
-      hipLaunchKernelGGL(k_unpack<double>, dim3(grid_for(S * np)), dim3(kBlock), 0, st, x, p0, np, S, n,
-                         1.0 / (double)S, accumulate, static_cast<double*>(out));
+    const int64_t tiles = np << (m - kLogElems);
+    d.p0 = p0;
+    by_int<1, kLogCol>(r1, [&](auto lr) {
+      hipLaunchKernelGGL((k_columns<decltype(lr)::value, -1, COL_FIRST, double>), dim3((unsigned)tiles),
+                         dim3(kThreads), 0, st, buf, m, tiles, tw, d, o);
+    });
+    if (r2 > 0)
+      by_int<1, kLogCol>(r2, [&](auto lr) {
+        hipLaunchKernelGGL((k_columns<decltype(lr)::value, -1, COL_READ, double>), dim3((unsigned)tiles),
+                           dim3(kThreads), 0, st, buf, m - r1, tiles, tw, d, o);
+      });
+    // at least 2048 workgroups (two fit a CU), as far as there are pairs
+    const unsigned split = (unsigned)std::min<int64_t>(np, bits < 11 ? 1 << (11 - bits) : 1);
+    hipLaunchKernelGGL((k_blocks<kLogElems, false, double>), dim3(1u << bits, split), dim3(kThreads), 0, st, buf, m,
+                       r1, r2, np, tw, gain, d, o);
+    if (r2 > 0)
+      by_int<1, kLogCol>(r2, [&](auto lr) {
+        hipLaunchKernelGGL((k_columns<decltype(lr)::value, 1, COL_READ, double>), dim3((unsigned)tiles),
+                           dim3(kThreads), 0, st, buf, m - r1, tiles, tw, d, o);
+      });
+    by_int<1, kLogCol>(r1, [&](auto lr) {
+      by_type(out_f32, [&](auto ot) {
+        hipLaunchKernelGGL((k_columns<decltype(lr)::value, 1, COL_LAST, decltype(ot)>), dim3((unsigned)tiles),
+                           dim3(kThreads), 0, st, buf, m, tiles, tw, d, o);
+      });
+    });
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
