@@ -19,6 +19,17 @@ namespace dst {
 
 enum GroupKind { GK_T = 0, GK_QU = 1, GK_TQU = 2, GK_IQU = 3 };
 
+// What the LDS form of the binning reads (dst_lds.hip): the pixel-order runs,
+// and the pixels part[g] .. part[g + 1] of workgroup g.
+struct LdsRuns {
+  int n_b = 0;
+  int nb = 0;  // length bits of the packed keys (baseline << nb | length - 1)
+  const int64_t* pstart = nullptr;
+  const uint32_t* part = nullptr;
+  const uint32_t* key = nullptr;
+  const void* cs = nullptr;
+};
+
 // One problem of a group, in device memory.  All arrays are the problem's
 // own (compact pixel space, packed run keys).
 struct GroupProblem {
@@ -45,7 +56,21 @@ struct GroupProblem {
   double* part_unbin;   // [3][unbin_n]
   double* part_update;  // [2][vec_n]
   CompView cv;
+  LdsRuns lds;  // the LDS form of the binning (slices with `lds` set)
 };
+
+// Problem of workgroup b: the i with start[i] <= b < start[i + 1].
+__device__ __forceinline__ int group_of(const uint32_t* start, int n, uint32_t b) {
+  int lo = 0, hi = n;
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) >> 1;
+    if (start[mid] <= b)
+      lo = mid;
+    else
+      hi = mid;
+  }
+  return lo;
+}
 
 // The group's launches.  Problems are ordered by kind; the binning and the
 // rescan take one launch per kind present (the slice of problems of that
@@ -59,6 +84,7 @@ struct GroupSlice {
   uint32_t bin_total = 0, unbin_total = 0;
   int lpp = 32;  // lanes per pixel of the binning (4, 8, 16 or 32)
   int bpw = 4;   // baselines per wavefront of the rescan (1, 2, 4 or 8)
+  int lds = 0;   // 1: every problem of the slice has the LDS form of the binning
 };
 struct GroupLaunch {
   const GroupProblem* prob = nullptr;  // device [n]

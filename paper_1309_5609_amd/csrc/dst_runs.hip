@@ -23,6 +23,7 @@
 #include <type_traits>
 
 #include "dst_internal.h"
+#include "dst_lds.h"
 #include "dst_runs.h"
 #include "dst_cg.h"
 #include "dst_group.h"
@@ -1676,19 +1677,6 @@ hipError_t launch_unbin_runs(const View& vc, const Runs& W, const double* m4, co
 
 namespace {
 
-// Problem of workgroup b: the i with start[i] <= b < start[i + 1].
-__device__ __forceinline__ int group_of(const uint32_t* start, int n, uint32_t b) {
-  int lo = 0, hi = n;
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (start[mid] <= b)
-      lo = mid;
-    else
-      hi = mid;
-  }
-  return lo;
-}
-
 template <typename RT, int KIND, int LPP>
 __global__ void __launch_bounds__(kBlock) k_group_bin(GroupLaunch G) {
   constexpr bool HT = KIND != GK_QU, HQ = KIND == GK_QU || KIND == GK_TQU, HI = KIND == GK_IQU;
@@ -1778,6 +1766,10 @@ hipError_t launch_group_phase(const GroupLaunch& G, int phase, hipStream_t st) {
           case 8: hipLaunchKernelGGL((k_group_unbin<RT, K, 8>), dim3(S.unbin_total), dim3(kBlock), 0, st, G); break;
           default: hipLaunchKernelGGL((k_group_unbin<RT, K, 4>), dim3(S.unbin_total), dim3(kBlock), 0, st, G); break;
         }
+        return;
+      }
+      if (S.lds) {
+        (void)launch_group_bin_lds(G, K, st);  // its launch error is reported below
         return;
       }
       switch (S.lpp) {
