@@ -116,7 +116,9 @@ int dst_version(void);
 /* Create a context on HIP device `device`.  *ctx receives the handle.
  * Launch shapes of the run-form iteration kernels may be overridden by the
  * environment at creation: DST_BIN_LPP (lanes per pixel in the binning: 64,
- * 32 = default, 16, or -64 for 64 with a software pipeline over pixels) and
+ * 32 = default, 16, or -64 for 64 with a software pipeline over pixels),
+ * DST_BIN_FORM (form of the binning: 0 plain, 1 baseline values in LDS where
+ * they fit, 2 pipelined gathers; by default by the problem's sizes) and
  * DST_UNBIN_BPW (baselines per wavefront in the rescan: 1, 2, 4 = default,
  * 8).  DST_RUN_SPLIT_BITS = k splits runs of consecutive samples on one
  * pixel at 2^k samples at most (runs are split anyway where a pixel id and a

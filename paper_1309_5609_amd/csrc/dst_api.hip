@@ -21,9 +21,9 @@
 #include "dst.h"
 #include "dst_bucket.h"
 #include "dst_comp.h"
+#include "dst_forms.h"
 #include "dst_group.h"
 #include "dst_internal.h"
-#include "dst_lds.h"
 #include "dst_multi.h"
 #include "dst_pixel.h"
 #include "dst_runs.h"
@@ -68,9 +68,9 @@ struct dst_ctx {
   hipStream_t cap = nullptr;  // private stream on which iteration graphs are captured
   int unbin_bpw = 4;          // launch shape of the run rescan (baselines per wavefront)
   int bin_lpp = 0;            // launch shape of the run binning (lanes per pixel; 0: default 32)
-  int bin_lds = -1;           // LDS form of the run binning (1 always, 0 never, -1 by size)
+  int bin_form = -1;          // form of the run binning (dst_forms.h; -1 by size)
   int run_split_bits = 0;     // > 0: longest run 2^bits samples (runs split beyond; results unchanged)
-  // launch shapes chosen by the autotuner, per problem shape: lanes per pixel of the binning (0: the LDS form),
+  // launch shapes chosen by the autotuner, per problem shape: lanes per pixel of the binning (0: its other form),
   // baselines per wavefront of the rescan
   std::map<std::tuple<int64_t, int64_t, int, int>, std::pair<int, int>> tuned;
 };
@@ -417,8 +417,8 @@ struct Plan {
   dst::Runs W;            // run form
   double* m4 = nullptr;   // per-iteration map (zero on invalid pixels)
   double* pw4 = nullptr;  // weighted interleaved baseline vector
-  dst::LdsShape lds;      // LDS form of the run binning (blocks 0: not used)
-  dst::LdsRuns lruns;
+  dst::BinShape bin;      // form of the run binning
+  dst::BinRuns bruns;
   int lpp = 0;            // launch shapes of the run binning (0: default) and rescan
   int bpw = 4;
   dst::Comp C;            // components of the baseline-pixel graph (streams with a T-like row)
@@ -606,13 +606,12 @@ int build_sample_plan(dst_ctx* ctx, const dst_problem* prob, Plan& P, const void
   return build_components(ctx, P, T.n_obs, T.cstart, T.sb, cs, st);
 }
 
-// The LDS form of the binning where it is the faster one.
-int build_lds(dst_ctx* ctx, Plan& P, hipStream_t st) {
-  P.lds = dst::lds_shape(P.S.v, P.W, ctx->bin_lpp != 0 ? 0 : ctx->bin_lds);
-  if (P.lds.blocks == 0) return DST_OK;
+// The form of the binning for the plan's sizes.
+int build_bin(dst_ctx* ctx, Plan& P, hipStream_t st) {
+  P.bin = dst::bin_shape(P.S.v, P.W, ctx->bin_lpp != 0 ? (int)dst::BIN_PLAIN : ctx->bin_form);
   uint32_t* part = nullptr;
-  DST_TRY(ws(ctx, "lds_part", P.lds.blocks + 1, &part));
-  HIP_TRY(dst::lds_build(P.S.v, P.W, P.lds, part, &P.lruns, st));
+  if (P.bin.form == dst::BIN_LDS) DST_TRY(ws(ctx, "bin_part", P.bin.blocks + 1, &part));
+  HIP_TRY(dst::bin_build(P.S.v, P.W, P.bin, part, &P.bruns, st));
   return DST_OK;
 }
 
@@ -633,8 +632,8 @@ int build_plan(dst_ctx* ctx, const dst_problem* prob, Plan& P, const void* tod, 
 // q = F^T W (F p - A m) (time order).  With ctl, the CG partials.
 int plan_bin(dst_ctx* ctx, Plan& P, const CgCtl* gate, hipStream_t st) {
   Setup& S = P.S;
-  if (P.runs && P.lds.blocks)
-    HIP_TRY(dst::launch_bin_lds(S.v, P.lruns, P.lds, P.W.f32, P.pw4, S.Minv4, S.valid, P.m4, gate, st));
+  if (P.runs && P.bin.form)
+    HIP_TRY(dst::launch_bin_form(S.v, P.bruns, P.bin, P.W.f32, P.pw4, S.Minv4, S.valid, P.m4, gate, st));
   else if (P.runs)
     HIP_TRY(dst::launch_bin_runs(S.v, P.W, P.pw4, S.Minv4, S.valid, P.m4, gate, P.lpp, st));
   else
@@ -1028,7 +1027,7 @@ int solve_uneven(dst_ctx* ctx, const dst_problem* problems, const std::vector<in
     DST_TRY(ws(ctx, "cg_b", N, &m.b));
     DST_TRY(build_runs_plan(ctx, &pr, m.P, pr.tod, &m.sd4, &m.md4, m.b, st));
     if (m.P.W.nb <= 0) return fail(ctx, DST_EHIP, "problem %d: run keys do not pack (internal)", idx[k]);
-    DST_TRY(build_lds(ctx, m.P, st));
+    DST_TRY(build_bin(ctx, m.P, st));
     // the closing operator of each problem: its own lanes per pixel (32 for all took 4.2 ms of an 80 ms survey batch)
     m.P.lpp = dst::bin_lanes_for(m.P.W.R, m.P.W.n_obs, m.P.dense_t);
     DST_TRY(ws(ctx, "cg_a", N, &m.a));
@@ -1108,7 +1107,7 @@ int solve_uneven(dst_ctx* ctx, const dst_problem* problems, const std::vector<in
     g.part_unbin = m.part;
     g.part_update = m.part2;
     g.cv = m.P.cv();
-    g.lds = m.P.lruns;
+    g.bin = m.P.bruns;
     if (g.kind != dst::GK_T) {
       if (f32 >= 0 && f32 != (int)W.f32) return fail(ctx, DST_EINVAL, "internal: mixed angle precision in a group");
       f32 = (int)W.f32;
@@ -1123,15 +1122,22 @@ int solve_uneven(dst_ctx* ctx, const dst_problem* problems, const std::vector<in
     if (sl.count == 0) continue;
     // lanes per pixel of the kind's binning from its runs per observed pixel
     int64_t runs = 0, obs = 0;
-    sl.lds = 1;
+    bool lds = true;
     for (int j = 0; j < sl.count; ++j) {
       runs += n_runs[sl.first + j];
       obs += gp[sl.first + j].v.n_pix;
-      if (M[order[sl.first + j]].P.lds.blocks == 0) sl.lds = 0;
+      lds = lds && M[order[sl.first + j]].P.bin.form == dst::BIN_LDS;
     }
     sl.lpp = dst::bin_lanes_for(runs, obs, K == dst::GK_T);
     sl.bpw = group_bpw(ctx, K);
-    if (sl.lds) sl.lpp = dst::lds_lanes_for(runs, obs, K == dst::GK_T);
+    // one form for the slice: LDS where every problem has it, else by the runs per pixel (or as the context says)
+    const bool angles = K == dst::GK_QU || K == dst::GK_TQU;
+    if (lds)
+      sl.form = dst::BIN_LDS;
+    else if (ctx->bin_lpp == 0 && angles &&
+             (ctx->bin_form == dst::BIN_PIPE || (ctx->bin_form < 0 && dst::bin_sparse(runs, obs, angles))))
+      sl.form = dst::BIN_PIPE;
+    if (sl.form) sl.lpp = dst::bin_form_lanes(runs, obs, K == dst::GK_T);
     if (ctx->bin_lpp == 4 || ctx->bin_lpp == 8 || ctx->bin_lpp == 16 || ctx->bin_lpp == 32) sl.lpp = ctx->bin_lpp;
     roff[K] = ranges.size();
     ranges.resize(ranges.size() + 2 * (sl.count + 1), 0u);
@@ -1139,7 +1145,10 @@ int solve_uneven(dst_ctx* ctx, const dst_problem* problems, const std::vector<in
     uint32_t* us = bs + sl.count + 1;
     for (int j = 0; j < sl.count; ++j) {
       const dst::GroupProblem& g = gp[sl.first + j];
-      bs[j + 1] = bs[j] + (sl.lds ? M[order[sl.first + j]].P.lds.blocks : dst::group_bin_blocks(g.v.n_pix, sl.lpp));
+      const uint32_t blocks = sl.form == dst::BIN_LDS    ? M[order[sl.first + j]].P.bin.blocks
+                              : sl.form == dst::BIN_PIPE ? dst::bin_pipe_blocks(g.v.n_pix, sl.lpp)
+                                                         : dst::group_bin_blocks(g.v.n_pix, sl.lpp);
+      bs[j + 1] = bs[j] + blocks;
       us[j + 1] = us[j] + g.unbin_n;
     }
     sl.bin_total = bs[sl.count];
@@ -1412,9 +1421,9 @@ int autotune(dst_ctx* ctx, Plan& P, const double* p, double* scratch, hipStream_
         best_lpp = lpp;
       }
     }
-    if (P.lds.blocks) {
+    if (P.bin.form) {
       const float t = time_of([&] {
-        return dst::launch_bin_lds(S.v, P.lruns, P.lds, P.W.f32, P.pw4, S.Minv4, S.valid, P.m4, nullptr, st);
+        return dst::launch_bin_form(S.v, P.bruns, P.bin, P.W.f32, P.pw4, S.Minv4, S.valid, P.m4, nullptr, st);
       });
       if (t < 0.f) return fail(ctx, DST_EHIP, "autotuner: a bin launch failed");
       if (t < tb) best_lpp = 0;
@@ -1433,7 +1442,7 @@ int autotune(dst_ctx* ctx, Plan& P, const double* p, double* scratch, hipStream_
   }
   if (it->second.first != 0) {
     P.lpp = it->second.first;
-    P.lds.blocks = 0;
+    P.bin.form = dst::BIN_PLAIN;
   }
   P.bpw = it->second.second;
   return DST_OK;
@@ -1455,7 +1464,7 @@ int dst_create(dst_ctx** out, int device) {
   ctx->device = device;
   if (const char* e = std::getenv("DST_UNBIN_BPW")) ctx->unbin_bpw = std::atoi(e);
   if (const char* e = std::getenv("DST_BIN_LPP")) ctx->bin_lpp = std::atoi(e);
-  if (const char* e = std::getenv("DST_BIN_LDS")) ctx->bin_lds = std::atoi(e);
+  if (const char* e = std::getenv("DST_BIN_FORM")) ctx->bin_form = std::atoi(e);
   if (const char* e = std::getenv("DST_RUN_SPLIT_BITS")) ctx->run_split_bits = std::atoi(e);
   DeviceGuard g(device);
   if (hipHostMalloc(reinterpret_cast<void**>(&ctx->ctl_host), sizeof(CgCtl), hipHostMallocDefault) != hipSuccess ||
@@ -1699,7 +1708,7 @@ int dst_solve(dst_ctx* ctx, const dst_problem* prob, const dst_solve_opts* opts_
   P.full = v;
   P.runs = !(opts.flags & DST_SOLVE_PER_SAMPLE);
   DST_TRY(build_plan(ctx, prob, P, prob->tod, &sd4, &md4, b, st));
-  if (P.runs) DST_TRY(build_lds(ctx, P, st));
+  if (P.runs) DST_TRY(build_bin(ctx, P, st));
   Setup& S = P.S;
   const View& vc = S.v;
   DST_TRY(ws(ctx, "cg_a", N, &a));

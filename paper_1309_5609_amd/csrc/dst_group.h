@@ -19,9 +19,10 @@ namespace dst {
 
 enum GroupKind { GK_T = 0, GK_QU = 1, GK_TQU = 2, GK_IQU = 3 };
 
-// What the LDS form of the binning reads (dst_lds.hip): the pixel-order runs,
-// and the pixels part[g] .. part[g + 1] of workgroup g.
-struct LdsRuns {
+// What the binning forms of dst_forms.hip read: the pixel-order runs, and for
+// BIN_LDS the pixels part[g] .. part[g + 1] of workgroup g.
+struct BinRuns {
+  int64_t n_obs = 0;
   int n_b = 0;
   int nb = 0;  // length bits of the packed keys (baseline << nb | length - 1)
   const int64_t* pstart = nullptr;
@@ -56,7 +57,7 @@ struct GroupProblem {
   double* part_unbin;   // [3][unbin_n]
   double* part_update;  // [2][vec_n]
   CompView cv;
-  LdsRuns lds;  // the LDS form of the binning (slices with `lds` set)
+  BinRuns bin;  // the runs for the binning forms of dst_forms.hip
 };
 
 // Problem of workgroup b: the i with start[i] <= b < start[i + 1].
@@ -84,7 +85,7 @@ struct GroupSlice {
   uint32_t bin_total = 0, unbin_total = 0;
   int lpp = 32;  // lanes per pixel of the binning (4, 8, 16 or 32)
   int bpw = 4;   // baselines per wavefront of the rescan (1, 2, 4 or 8)
-  int lds = 0;   // 1: every problem of the slice has the LDS form of the binning
+  int form = 0;  // form of the binning (dst_forms.h; 0: the plain one)
 };
 struct GroupLaunch {
   const GroupProblem* prob = nullptr;  // device [n]

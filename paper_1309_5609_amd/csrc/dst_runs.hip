@@ -22,8 +22,8 @@
 #include <cstdint>
 #include <type_traits>
 
+#include "dst_forms.h"
 #include "dst_internal.h"
-#include "dst_lds.h"
 #include "dst_runs.h"
 #include "dst_cg.h"
 #include "dst_group.h"
@@ -1768,8 +1768,8 @@ hipError_t launch_group_phase(const GroupLaunch& G, int phase, hipStream_t st) {
         }
         return;
       }
-      if (S.lds) {
-        (void)launch_group_bin_lds(G, K, st);  // its launch error is reported below
+      if (S.form) {
+        (void)launch_group_bin_form(G, K, st);  // its launch error is reported below
         return;
       }
       switch (S.lpp) {

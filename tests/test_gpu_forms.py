@@ -1,10 +1,11 @@
-"""The binning with baseline values in LDS (one band and several) against the FP64 oracle and the plain form.
+"""The other forms of the iterations' binning (baseline values in LDS; pipelined gathers) against the FP64 oracle.
 
-DST_BIN_LDS=1 makes every solve take it.  A band holds 20224 doubles: 20224
-baselines of one stream, 10112 of q/u, 6741 of T/q/u, so one-sample baselines
-split small problems into two and three bands.  Bars as for the plain form:
-baselines and maps within 1e-9 of the oracle at tolerance 1e-13, equal
-iteration counts (+-1), graph replay with the bits of launches one by one.
+DST_BIN_FORM=1 keeps the baseline values in LDS wherever they fit (20224
+doubles: 20224 baselines of one stream, 10112 of q/u, 6741 of T/q/u),
+DST_BIN_FORM=2 gathers them in the pipelined form wherever there are q/u
+streams, 0 is the plain form.  Bars as for the plain form: baselines and maps
+within 1e-9 of the oracle at tolerance 1e-13, equal iteration counts (+-1),
+graph replay with the bits of launches one by one.
 """
 import numpy as np
 import pytest
@@ -20,13 +21,13 @@ def rel(a, b):
     return np.linalg.norm(a - b) / max(np.linalg.norm(b), 1e-300)
 
 
-def context(monkeypatch, lds):
+def context(monkeypatch, form):
     from paper_1309_5609_amd import dst
-    monkeypatch.setenv("DST_BIN_LDS", str(lds))
+    monkeypatch.setenv("DST_BIN_FORM", str(form))
     return dst.Context(0)
 
 
-ONE_BAND = {
+VARIANTS = {
     "plain": dict(),
     "masked": dict(mask_fraction=0.07),
     "unequal": dict(weights=(2.0e6, 5.0e6, 0.7e6)),
@@ -38,11 +39,12 @@ ONE_BAND = {
 }
 
 
-@pytest.mark.parametrize("name", list(ONE_BAND))
-def test_one_band(monkeypatch, name):
+@pytest.mark.parametrize("form", [1, 2])
+@pytest.mark.parametrize("name", list(VARIANTS))
+def test_form(monkeypatch, name, form):
     from paper_1309_5609_amd import dst
-    p = toy(**ONE_BAND[name])
-    c = context(monkeypatch, 1)
+    p = toy(**VARIANTS[name])
+    c = context(monkeypatch, form)
     dp = dst.to_device(p)
     out = dst.dst_solve(c, dp, tol=1e-13, max_iter=3000)
     eager = dst.dst_solve(c, dp, tol=1e-13, max_iter=3000, flags=dst.DST_SOLVE_NO_GRAPH)
@@ -56,12 +58,12 @@ def test_one_band(monkeypatch, name):
     c.close()
 
 
-@pytest.mark.parametrize("streams,n,dtype", [("T", 20224, "float64"), ("T", 20225, "float64"), ("T", 45000, "float32"),
-                                             ("QU", 21000, "float64"), ("TQU", 6742, "float64"),
-                                             ("TQU", 15000, "float32"), ("TQU", 15000, "float64"),
-                                             ("IQU", 25000, "float64")])
-def test_bands(monkeypatch, streams, n, dtype):
-    """One-sample baselines: 1 to 3 bands, against the plain form (same sums in another order).
+@pytest.mark.parametrize("form", [1, 2])
+@pytest.mark.parametrize("streams,n,dtype", [("T", 20224, "float64"), ("T", 20225, "float64"), ("QU", 10112, "float32"),
+                                             ("QU", 10113, "float64"), ("TQU", 6741, "float64"),
+                                             ("TQU", 6742, "float32"), ("IQU", 20224, "float64")])
+def test_around_the_lds_limit(monkeypatch, form, streams, n, dtype):
+    """One-sample baselines, as many as LDS holds and one more, against the plain form (same sums in another order).
 
     One iteration: with one-sample T baselines K is a multiple of a projector, so a second step divides by rounding.
     """
@@ -69,8 +71,8 @@ def test_bands(monkeypatch, streams, n, dtype):
     p = toy(n_samples=n, L=1, nside=4, streams=streams, mask_fraction=0.03)
     dp = dst.to_device(p, tod_dtype=dtype, psi_dtype=dtype)
     res = []
-    for lds in (1, 0):
-        c = context(monkeypatch, lds)
+    for f in (form, 0):
+        c = context(monkeypatch, f)
         res.append(dst.dst_solve(c, dp, tol=1e-30, max_iter=1))
         c.close()
     for k in ("baselines", "destriped_map", "binned_map"):
@@ -78,11 +80,12 @@ def test_bands(monkeypatch, streams, n, dtype):
         assert rel(res[0][k].cpu().numpy(), res[1][k].cpu().numpy()) < 1e-10, k
 
 
-def test_group(monkeypatch):
-    """An uneven batch whose problems all take the LDS form, with one and two bands."""
+@pytest.mark.parametrize("form", [1, 2])
+def test_group(monkeypatch, form):
+    """An uneven batch whose problems all take the form."""
     from paper_1309_5609_amd import dst
-    c = context(monkeypatch, 1)
-    probs = [toy(n_samples=30000, L=300, nside=16, cfg=330), toy(n_samples=7000, L=1, nside=4, cfg=331),
+    c = context(monkeypatch, form)
+    probs = [toy(n_samples=30000, L=300, nside=16, cfg=330), toy(n_samples=6000, L=5, nside=4, cfg=331),
              toy(n_samples=12011, L=211, cfg=332, streams="T"), toy(n_samples=20000, L=400, cfg=333, streams="IQU"),
              toy(n_samples=20000, L=500, nside=16, cfg=334, streams="QU")]
     dps = [dst.to_device(p) for p in probs]
