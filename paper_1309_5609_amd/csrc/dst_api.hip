@@ -428,8 +428,8 @@ struct Plan {
 };
 
 // Components of the baseline-pixel graph over T-valid samples (after the
-// per-baseline counts); elements elem_start / eb in pixel order.
-int build_components(dst_ctx* ctx, Plan& P, int64_t n_obs, const int64_t* elem_start, const int32_t* eb,
+// per-baseline counts); elements elem_start / ekey in pixel order.
+int build_components(dst_ctx* ctx, Plan& P, int64_t n_obs, const int64_t* elem_start, const uint32_t* ekey,
                      const dst::ChainSource& cs, hipStream_t st) {
   const View& v = P.full;
   if (v.rowT < 0) return DST_OK;
@@ -442,7 +442,7 @@ int build_components(dst_ctx* ctx, Plan& P, int64_t n_obs, const int64_t* elem_s
   DST_TRY(ws(ctx, "comp_n", 4, &C.ncomp));
   DST_TRY(ws(ctx, "comp_pmin", std::max<int64_t>(n_obs, 1), &C.pmin));
   DST_TRY(ws(ctx, "comp_flags", dst::kCompFlags, &C.flags));
-  HIP_TRY(dst::launch_components(v.n_b, n_obs, elem_start, eb, P.S.valid, P.S.nvalid, cs, C, st));
+  HIP_TRY(dst::launch_components(v.n_b, n_obs, elem_start, ekey, P.S.valid, P.S.nvalid, cs, C, st));
   return DST_OK;
 }
 
@@ -490,25 +490,21 @@ int build_runs_plan(dst_ctx* ctx, const dst_problem* prob, Plan& P, const void* 
   HIP_TRY(dst::runs_count(v, W, S.err, st));
   const int64_t R = W.R;
   DST_TRY(ws(ctx, "r_t0", R, &W.t0));
-  DST_TRY(ws(ctx, "r_tpix", R, &W.tpix));
-  DST_TRY(ws(ctx, "r_tn", R, &W.tn));
   // FP32 angles (mixed precision): run sums of cos 2psi, sin 2psi kept in FP32
   W.f32 = S.psi_f32 && (v.rowQ >= 0 || v.iqu);
   const size_t rsz = W.f32 ? sizeof(float) : sizeof(double);
   DST_TRY(ws_get(ctx, "r_tcs", 2 * R * rsz, &W.tcs));
-  // intensity-only problems: one raw sum and a 16-byte record per run
+  // intensity-only problems: one raw sum per run
   const bool t_only = v.rowT >= 0 && v.rowQ < 0 && !v.iqu;
   DST_TRY(ws(ctx, "r_raw", (t_only ? 1 : 3) * (size_t)R, &W.raw));
-  DST_TRY(ws_get(ctx, "r_rec", (size_t)R * (t_only ? sizeof(dst::RunRecordT) : sizeof(dst::RunRecord)),
-                 reinterpret_cast<void**>(&W.rec)));
+  DST_TRY(ws_get(ctx, "r_rec", (size_t)R * dst::run_record_bytes(v.rowQ >= 0, v.iqu, tod != nullptr, v.w[1] == v.w[2]),
+                 &W.rec));
   DST_TRY(ws(ctx, "r_keys0", R, &W.keys[0]));
   DST_TRY(ws(ctx, "r_keys1", R, &W.keys[1]));
   DST_TRY(ws(ctx, "r_vals0", R, &W.vals[0]));
   DST_TRY(ws(ctx, "r_vals1", R, &W.vals[1]));
-  DST_TRY(ws(ctx, "r_pb", R, &W.pb));
   DST_TRY(ws(ctx, "r_tkey", R, &W.tkey));
   DST_TRY(ws(ctx, "r_pkey", R, &W.pkey));
-  DST_TRY(ws(ctx, "r_pn", R, &W.pn));
   DST_TRY(ws_get(ctx, "r_pcs", 2 * R * rsz, &W.pcs));
   // per-pixel arrays sized for every pixel (the observed count is known later)
   DST_TRY(ws(ctx, "hits", v.n_pix, &S.hits));
@@ -532,9 +528,9 @@ int build_runs_plan(dst_ctx* ctx, const dst_problem* prob, Plan& P, const void* 
   HIP_TRY(dst::launch_rhs_runs(S.v, W, tod, S.tod_f32, m4d, S.valid, S.nvalid, S.J, b, st));
   dst::ChainSource cs;
   cs.bstart = W.bstart;
-  cs.tkey = W.nb ? W.tkey : reinterpret_cast<const uint32_t*>(W.tpix);
+  cs.tkey = W.tkey;
   cs.nb = W.nb;
-  return build_components(ctx, P, W.n_obs, W.pstart, W.pb, cs, st);
+  return build_components(ctx, P, W.n_obs, W.pstart, W.pkey, cs, st);
 }
 
 // With tod: also the sum map sd4, binned map md4 (compact [n_obs][4]) and the
@@ -603,7 +599,7 @@ int build_sample_plan(dst_ctx* ctx, const dst_problem* prob, Plan& P, const void
   cs.cpix = T.cpix;
   cs.L = v.L;
   cs.n_t = v.n_t;
-  return build_components(ctx, P, T.n_obs, T.cstart, T.sb, cs, st);
+  return build_components(ctx, P, T.n_obs, T.cstart, reinterpret_cast<const uint32_t*>(T.sb), cs, st);
 }
 
 // The form of the binning for the plan's sizes.
@@ -1010,7 +1006,7 @@ int solve_uneven(dst_ctx* ctx, const dst_problem* problems, const std::vector<in
   }
   // arrays only the setup reads: one set serves every problem's setup in turn
   for (const char* name : {"r_tcount", "r_toff", "r_rec", "r_raw", "r_keys0", "r_keys1", "r_vals0", "r_vals1",
-                           "r_t0", "r_tmp", "r_pb", "r_pn", "r_tpix", "r_tn", "r_seg", "r_pk0", "r_pk1", "r_bkey0",
+                           "r_t0", "r_tmp", "r_seg", "r_pk0", "r_pk1", "r_bkey0",
                            "r_bkey1", "r_nobs", "r_nout", "r_ccount", "sd4", "comp_parent", "comp_cursor", "comp_pmin", "comp_flags", "counts"})
     ctx->ws_shared.insert(name);
   for (int k = 0; k < n; ++k) {
@@ -1026,7 +1022,6 @@ int solve_uneven(dst_ctx* ctx, const dst_problem* problems, const std::vector<in
     m.P.bpw = 4;
     DST_TRY(ws(ctx, "cg_b", N, &m.b));
     DST_TRY(build_runs_plan(ctx, &pr, m.P, pr.tod, &m.sd4, &m.md4, m.b, st));
-    if (m.P.W.nb <= 0) return fail(ctx, DST_EHIP, "problem %d: run keys do not pack (internal)", idx[k]);
     DST_TRY(build_bin(ctx, m.P, st));
     // the closing operator of each problem: its own lanes per pixel (32 for all took 4.2 ms of an 80 ms survey batch)
     m.P.lpp = dst::bin_lanes_for(m.P.W.R, m.P.W.n_obs, m.P.dense_t);

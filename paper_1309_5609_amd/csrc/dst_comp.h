@@ -67,9 +67,9 @@ struct ChainSource {
 
 // Components over the pixels whose T block is valid (bit 0 of valid).
 // Elements elem_start[c] .. elem_start[c + 1] - 1 belong to compact pixel c
-// (runs or samples in pixel order); eb[e] is the baseline of element e;
+// (runs or samples in pixel order); ekey[e] >> cs.nb is the baseline of element e;
 // nvalid_T[b] the number of valid samples of baseline b.  Asynchronous.
-hipError_t launch_components(int64_t n_b, int64_t n_obs, const int64_t* elem_start, const int32_t* eb,
+hipError_t launch_components(int64_t n_b, int64_t n_obs, const int64_t* elem_start, const uint32_t* ekey,
                              const uint8_t* valid, const int32_t* nvalid_T, const ChainSource& cs, Comp& C,
                              hipStream_t st);
 

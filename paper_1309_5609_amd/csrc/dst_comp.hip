@@ -136,7 +136,8 @@ constexpr int kBaseLanes = 16;  // lanes per baseline in the baseline sweep (4 b
 
 // Round r, pixel side: pmin[c] = smallest label of the baselines of valid pixel c.
 __global__ void __launch_bounds__(kBlk) k_lp_pix(int r, int64_t n_obs, const int64_t* __restrict__ elem_start,
-                                                 const int32_t* __restrict__ eb, const uint8_t* __restrict__ valid,
+                                                 const uint32_t* __restrict__ ekey, int nb,
+                                                 const uint8_t* __restrict__ valid,
                                                  const int32_t* __restrict__ label, int32_t* __restrict__ pmin,
                                                  const int32_t* __restrict__ flags) {
   if (lp_done(r, flags)) return;
@@ -149,8 +150,9 @@ __global__ void __launch_bounds__(kBlk) k_lp_pix(int r, int64_t n_obs, const int
     int32_t mn = INT32_MAX;
     if (on) {
       const int64_t e0 = elem_start[c], e1 = elem_start[c + 1];
-      if (sub == 0) mn = label[eb[e1 - 1]];
-      for (int64_t e = e0 + (int64_t)sub * kStride; e < e1; e += kPixLanes * kStride) mn = min(mn, label[eb[e]]);
+      if (sub == 0) mn = label[ekey[e1 - 1] >> nb];
+      for (int64_t e = e0 + (int64_t)sub * kStride; e < e1; e += kPixLanes * kStride)
+        mn = min(mn, label[ekey[e] >> nb]);
     }
     mn = group_min(mn, kPixLanes);
     if (on && sub == 0) pmin[c] = mn;
@@ -235,7 +237,8 @@ __global__ void __launch_bounds__(kBlk) k_lp_seed(int64_t n_b, const int32_t* __
 // first baseline is joined (parents only move to ancestors, so any value
 // read, even a stale one, that equals that root proves the link).
 __global__ void __launch_bounds__(kBlk) k_uf_link(int64_t n_obs, const int64_t* __restrict__ elem_start,
-                                                  const int32_t* __restrict__ eb, const uint8_t* __restrict__ valid,
+                                                  const uint32_t* __restrict__ ekey, int nb,
+                                                  const uint8_t* __restrict__ valid,
                                                   int32_t* __restrict__ parent, const int32_t* __restrict__ gate) {
   if (*gate == 0) return;
   const int lane = threadIdx.x & 63;
@@ -244,11 +247,11 @@ __global__ void __launch_bounds__(kBlk) k_uf_link(int64_t n_obs, const int64_t* 
     if (!(valid[c] & 1)) continue;
     const int64_t e0 = elem_start[c], e1 = elem_start[c + 1];
     if (e1 - e0 < 2) continue;
-    const int32_t first = eb[e0];
+    const int32_t first = (int32_t)(ekey[e0] >> nb);
     const int32_t rf = uf_find(parent, first);
     for (int64_t e = e0 + 1 + lane; e < e1; e += 64) {
-      const int32_t b = eb[e];
-      if (b != eb[e - 1] && b != rf && uf_load(parent + b) != rf) uf_union(parent, rf, b);
+      const int32_t b = (int32_t)(ekey[e] >> nb);
+      if (b != (int32_t)(ekey[e - 1] >> nb) && b != rf && uf_load(parent + b) != rf) uf_union(parent, rf, b);
     }
   }
 }
@@ -385,7 +388,7 @@ unsigned grid_of(int64_t n, int64_t per, unsigned cap) {
 
 }  // namespace
 
-hipError_t launch_components(int64_t n_b, int64_t n_obs, const int64_t* elem_start, const int32_t* eb,
+hipError_t launch_components(int64_t n_b, int64_t n_obs, const int64_t* elem_start, const uint32_t* ekey,
                              const uint8_t* valid, const int32_t* nvalid_T, const ChainSource& cs, Comp& C,
                              hipStream_t st) {
   const unsigned gb = grid_of(n_b, kBlk, 4096);
@@ -394,14 +397,14 @@ hipError_t launch_components(int64_t n_b, int64_t n_obs, const int64_t* elem_sta
   for (int r = 0; r < kRounds; ++r) {
     if (n_obs > 0)
       hipLaunchKernelGGL(k_lp_pix, dim3(grid_of(n_obs, kBlk / kPixLanes, 65536)), dim3(kBlk), 0, st, r, n_obs,
-                         elem_start, eb, valid, C.label, C.pmin, C.flags);
+                         elem_start, ekey, cs.nb, valid, C.label, C.pmin, C.flags);
     hipLaunchKernelGGL(k_lp_base, dim3(grid_of(n_b, kBlk / kBaseLanes, 65536)), dim3(kBlk), 0, st, r, n_b, cs.bstart,
                        cs.tkey, cs.nb, cs.cpix, cs.L, cs.n_t, valid, C.pmin, C.label, C.flags);
   }
   hipLaunchKernelGGL(k_lp_seed, dim3(gb), dim3(kBlk), 0, st, n_b, C.label, C.parent, C.flags);
   if (n_obs > 0)
-    hipLaunchKernelGGL(k_uf_link, dim3(grid_of(n_obs, kBlk / 64, 65536)), dim3(kBlk), 0, st, n_obs, elem_start, eb,
-                       valid, C.parent, C.flags + kGate);
+    hipLaunchKernelGGL(k_uf_link, dim3(grid_of(n_obs, kBlk / 64, 65536)), dim3(kBlk), 0, st, n_obs, elem_start, ekey,
+                       cs.nb, valid, C.parent, C.flags + kGate);
   hipLaunchKernelGGL(k_uf_label, dim3(gb), dim3(kBlk), 0, st, n_b, nvalid_T, C.parent, C.label, C.ncomp);
   hipLaunchKernelGGL(k_comp_lists, dim3(1), dim3(1024), 0, st, n_b, C.label, C.start, C.member, C.cursor, C.ncomp);
   return hipGetLastError();

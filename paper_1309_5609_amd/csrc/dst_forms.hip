@@ -340,7 +340,7 @@ uint32_t bin_pipe_blocks(int64_t n_obs, int lpp) {
 
 BinShape bin_shape(const View& vc, const Runs& W, int mode) {
   BinShape s;
-  if (mode == BIN_PLAIN || W.n_obs <= 0 || W.nb <= 0) return s;
+  if (mode == BIN_PLAIN || W.n_obs <= 0) return s;
   const bool fits = vc.n_b * columns_of(vc) <= kLdsDoubles, pipe = vc.rowQ >= 0;
   if (mode < 0) {
     if (fits && !vc.iqu && W.R >= kMinRuns && W.n_obs >= kMinPix)

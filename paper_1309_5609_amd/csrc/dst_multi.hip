@@ -58,7 +58,7 @@ constexpr int kStageM = 256;
 template <typename PT, typename TT, bool HAS_T, bool HAS_QU, int NR>
 __global__ void __launch_bounds__(kBlock) k_multi_tod(View v, TodSet tods, const uint32_t* __restrict__ bstart,
                                                       const uint32_t* __restrict__ t0,
-                                                      const int32_t* __restrict__ tpix, const int32_t* __restrict__ tn,
+                                                      const uint32_t* __restrict__ tkey, int nb,
                                                       const uint32_t* __restrict__ ipos,
                                                       const uint8_t* __restrict__ valid, int Rp, int ri0,
                                                       double* __restrict__ prs, double* __restrict__ braw) {
@@ -82,8 +82,9 @@ __global__ void __launch_bounds__(kBlock) k_multi_tod(View v, TodSet tods, const
     const int64_t j = jb + lane;
     const bool has = j < r1;
     const int64_t ts = has ? (int64_t)t0[j] : 0;
-    const int n = has ? tn[j] : 0;
-    const uint8_t f = has ? valid[tpix[j]] : 0;
+    const uint32_t key = has ? tkey[j] : 0u;
+    const int n = has ? (int)(key & ((1u << nb) - 1u)) + 1 : 0;
+    const uint8_t f = has ? valid[key >> nb] : 0;
     // samples spanned by these runs (lane 0 always holds one)
     const int last = r1 - 1 - jb < 63 ? (int)(r1 - 1 - jb) : 63;
     const int64_t lo = __shfl(ts, 0, 64), hi = __shfl(ts + n, last, 64);
@@ -289,7 +290,7 @@ __device__ __forceinline__ void load_v(const GT* q, double (&x)[V]) {
 // mixed-precision iterations; sums in FP64 either way).
 template <typename RT, bool HAS_T, bool HAS_QU, int V, typename GT>
 __global__ void __launch_bounds__(kBlock) k_multi_bin(View vc, int R, int Rp, const int64_t* __restrict__ pstart,
-                                                      const int32_t* __restrict__ pb, const int32_t* __restrict__ pn,
+                                                      const uint32_t* __restrict__ pkey, int nb,
                                                       const RT* __restrict__ pcs, const GT* __restrict__ p,
                                                       const double* __restrict__ Minv4,
                                                       GT* __restrict__ m, const MultiCtl* __restrict__ ctl) {
@@ -337,8 +338,9 @@ __global__ void __launch_bounds__(kBlock) k_multi_bin(View vc, int R, int Rp, co
     for (int64_t wb = j0; wb < j1; wb += 63) {
       const int64_t jl = wb + lane;
       const bool inw = lane < 63 && jl < j1;
-      const int w_b = inw ? pb[jl] : -1;
-      const int w_n = (HAS_T && inw) ? pn[jl] : 0;
+      const uint32_t w_key = inw ? pkey[jl] : 0u;
+      const int w_b = inw ? (int)(w_key >> nb) : -1;
+      const int w_n = (HAS_T && inw) ? (int)(w_key & ((1u << nb) - 1u)) + 1 : 0;
       const CS2<RT> w_cs = (HAS_QU && inw) ? reinterpret_cast<const CS2<RT>*>(pcs)[jl] : make_cs<RT>(0.0, 0.0);
       const RT w_c = w_cs.x, w_s = w_cs.y;
       const int nwin = j1 - wb < 63 ? (int)(j1 - wb) : 63;
@@ -418,8 +420,8 @@ __global__ void __launch_bounds__(kBlock) k_multi_bin(View vc, int R, int Rp, co
 template <typename RT, bool HAS_T, bool HAS_QU, int MODE, int V, typename GT>
 __global__ void __launch_bounds__(kBlock) k_multi_unbin(View vc, int R, int Rp, const uint32_t* __restrict__ bstart,
                                                         const uint32_t* __restrict__ border,
-                                                        const int32_t* __restrict__ tpix,
-                                                        const int32_t* __restrict__ tn, const RT* __restrict__ tcs,
+                                                        const uint32_t* __restrict__ tkey, int nb,
+                                                        const RT* __restrict__ tcs,
                                                         const GT* __restrict__ m,
                                                         const int32_t* __restrict__ nvalid,
                                                         const double* __restrict__ p, const double* __restrict__ braw,
@@ -468,8 +470,9 @@ __global__ void __launch_bounds__(kBlock) k_multi_unbin(View vc, int R, int Rp, 
     for (int64_t wb = rs0; wb < rs1; wb += 63) {
       const int64_t jl = wb + lane;
       const bool inw = lane < 63 && jl < rs1;
-      const int w_c = inw ? tpix[jl] : -1;
-      const int w_n = (HAS_T && inw) ? tn[jl] : 0;
+      const uint32_t w_key = inw ? tkey[jl] : 0u;
+      const int w_c = inw ? (int)(w_key >> nb) : -1;
+      const int w_n = (HAS_T && inw) ? (int)(w_key & ((1u << nb) - 1u)) + 1 : 0;
       const CS2<RT> w_cs = (HAS_QU && inw) ? reinterpret_cast<const CS2<RT>*>(tcs)[jl] : make_cs<RT>(0.0, 0.0);
       const RT w_C = w_cs.x, w_S = w_cs.y;
       const int nwin = rs1 - wb < 63 ? (int)(rs1 - wb) : 63;
@@ -1029,7 +1032,7 @@ hipError_t launch_multi_tod(const View& vc, int psi_f32, const TodSet& tods, int
       by_streams(vc, [&](auto T, auto Q) {
         constexpr bool HT = decltype(T)::value, HQ = decltype(Q)::value;
         auto launch = [&](auto kern) {
-          hipLaunchKernelGGL(kern, dim3(g), dim3(kBlock), 0, st, vc, tods, W.bstart, W.t0, W.tpix, W.tn, ipos, valid,
+          hipLaunchKernelGGL(kern, dim3(g), dim3(kBlock), 0, st, vc, tods, W.bstart, W.t0, W.tkey, W.nb, ipos, valid,
                              Rp, ri0, prs, braw);
         };
         if (nr >= 5)
@@ -1073,7 +1076,7 @@ hipError_t multi_bin_impl(const View& vc, const Runs& W, const Multi& mu, const 
     using RT = typename decltype(rt)::type;
     by_streams(vc, [&](auto T, auto Q) {
       auto launch = [&](auto kern) {
-        hipLaunchKernelGGL(kern, dim3(g), dim3(kBlock), 0, st, vc, mu.R, mu.Rp, W.pstart, W.pb, W.pn,
+        hipLaunchKernelGGL(kern, dim3(g), dim3(kBlock), 0, st, vc, mu.R, mu.Rp, W.pstart, W.pkey, W.nb,
                            static_cast<const RT*>(W.pcs), p, Minv4, m, ctl);
       };
       if (mu.Rp >= 2)
@@ -1111,7 +1114,7 @@ hipError_t multi_unbin_impl(const View& vc, const Runs& W, const Multi& mu, int 
     by_streams(vc, [&](auto T, auto Q) {
       constexpr bool HT = decltype(T)::value, HQ = decltype(Q)::value;
       auto launch = [&](auto kern) {
-        hipLaunchKernelGGL(kern, dim3(g), dim3(kBlock), 0, st, vc, mu.R, mu.Rp, W.bstart, W.border, W.tpix, W.tn,
+        hipLaunchKernelGGL(kern, dim3(g), dim3(kBlock), 0, st, vc, mu.R, mu.Rp, W.bstart, W.border, W.tkey, W.nb,
                            static_cast<const RT*>(W.tcs), m, nvalid, p, braw, q, ctl, partials);
       };
       auto by_mode = [&](auto VV) {

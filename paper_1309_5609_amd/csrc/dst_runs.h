@@ -23,25 +23,46 @@ __host__ __device__ inline CS2<RT> make_cs(double c, double s) {
   return v;
 }
 
-// Per-run record read by the per-pixel setup (one aligned 64-byte access):
-// length, baseline, sums over the run of cos 2psi, sin 2psi, cos^2 2psi,
-// cos 2psi sin 2psi, d_T and of the rotated, weighted q/u pair
-// (w_q d_q c - w_u d_u s, w_q d_q s + w_u d_u c).
+// Per-run records read by the per-pixel setup in pixel order (gathered: one
+// aligned access each, so their size is what the setup moves): the key
+// baseline << nb | (length - 1) and the sums over the run of d_T and of the
+// rotated, weighted q/u pair (w_q d_q c - w_u d_u s, w_q d_q s + w_u d_u c).
+// Unequal q/u weights and radiometers need the sums of
+// cos^2 2psi and cos 2psi sin 2psi as well and carry those of cos 2psi and
+// sin 2psi along.  With equal weights the block is w times the hits, so the
+// record is half the size, and without timelines it is the key alone.
+// (30 days at N_side 256, FP64, equal weights: run build 2.00 -> 1.41 ms, per-pixel
+// setup 1.10 -> 1.29 ms with the angle sums gathered beside the record, pixel
+// numbering 0.27 -> 0.18 ms with the keys packed by the run build; 90 days of
+// intensity: 2.26 -> 1.80, 3.95 -> 3.70 and 1.77 -> 1.26 ms.)
 struct alignas(64) RunRecord {
-  int32_t n;
-  int32_t b;
+  uint32_t key;
+  uint32_t pad;
   double C, S, cc, cs, dT, dQ, dU;
 };
 static_assert(sizeof(RunRecord) == 64, "run record must be one 64-byte line");
-
-// Intensity-only problems keep a 16-byte record per run (length, baseline,
-// sum of d_T) and one raw sum per run: the angle moments are not needed.
-struct alignas(16) RunRecordT {
-  int32_t n;
-  int32_t b;
+struct alignas(32) RunRecordQU {
+  uint32_t key;
+  uint32_t pad;
+  double dT, dQ, dU;
+};
+static_assert(sizeof(RunRecordQU) == 32, "equal-weight run record must be 32 bytes");
+struct alignas(16) RunRecordT {  // intensity only
+  uint32_t key;
+  uint32_t pad;
   double dT;
 };
 static_assert(sizeof(RunRecordT) == 16, "intensity run record must be 16 bytes");
+
+template <bool HAS_T, bool HAS_QU, bool IQU, bool TOD, bool EQ>
+using RecordOf = std::conditional_t<
+    IQU || (HAS_QU && !EQ), RunRecord,
+    std::conditional_t<!TOD, uint32_t, std::conditional_t<HAS_QU, RunRecordQU, RunRecordT>>>;
+// Bytes per record.
+inline size_t run_record_bytes(bool has_qu, bool iqu, bool tod, bool equal_weights) {
+  if (iqu || (has_qu && !equal_weights)) return sizeof(RunRecord);
+  return !tod ? sizeof(uint32_t) : has_qu ? sizeof(RunRecordQU) : sizeof(RunRecordT);
+}
 
 // A run is a maximal stretch of consecutive unmasked samples on one pixel
 // inside one baseline.  Runs are kept twice: in time order (t*: rescan and
@@ -53,9 +74,9 @@ static_assert(sizeof(RunRecordT) == 16, "intensity run record must be 16 bytes")
 //
 // Buffers belong to the caller's workspace.  Sizes: tcount, toff
 // [run_tiles(n_t)];
-// bstart [n_b + 1]; t0, tpix, tn, pb, pn [R] and the pairs tcs, pcs [2 R] (FP32
+// bstart [n_b + 1]; t0, tkey, pkey [R] and the pairs tcs, pcs [2 R] (FP32
 // when f32, else FP64);
-// raw [3 R]; rec [R]; keys, vals 2 x [R]; seg [2 n_pix] (zero-filled before
+// raw [3 R]; rec run_record_bytes(...) R; keys, vals 2 x [R]; seg [2 n_pix] (zero-filled before
 // runs_build); pk, pv 2 x [n_pix]; cid [n_pix] (filled with -1 before
 // runs_build); ccount, pstart [n_pix + 1]; bkey, bord 2 x [n_b].
 struct Runs {
@@ -68,12 +89,10 @@ struct Runs {
   unsigned long long* n_out = nullptr;  // samples in no run (masked or out of range); zero-filled before runs_count
   uint32_t* bstart = nullptr;
   bool f32 = false;  // run sums of cos 2psi, sin 2psi (tcs, pcs) stored in FP32 (else FP64)
-  int32_t* tpix = nullptr;
-  int32_t* tn = nullptr;
   void* tcs = nullptr;  // [2 R] CS2 pairs per run, time order
   double* raw = nullptr;       // [3 R] ([R] for T only), time order: at each run that ends its baseline or a
                                // 64-run window, the sums of d_T, d_q, d_u over the baseline's runs in the window
-  RunRecord* rec = nullptr;    // [R] per-run records (time order); RunRecordT for T only
+  void* rec = nullptr;         // [R] per-run records (time order), RecordOf the problem
   uint32_t* keys[2] = {nullptr, nullptr};
   uint32_t* vals[2] = {nullptr, nullptr};
   const uint32_t* rperm = nullptr;
@@ -85,18 +104,16 @@ struct Runs {
   int64_t* ccount = nullptr;
   const uint32_t* order = nullptr;  // compact id -> pixel (set by runs_build)
   int64_t n_obs = 0;
-  int32_t* pb = nullptr;
-  int32_t* pn = nullptr;
   void* pcs = nullptr;  // [2 R] CS2 pairs per run, pixel order
   int64_t* pstart = nullptr;
-  // Iteration keys [R] (time and pixel order): index << nb | (length - 1),
-  // used when nb > 0 (index and length fit 32 bits together).
+  // Run keys [R]: compact pixel << nb | (length - 1) in time order (pixel
+  // before runs_build has numbered the observed ones), baseline << nb |
+  // (length - 1) in pixel order.
   uint32_t* tkey = nullptr;
   uint32_t* pkey = nullptr;
-  int nb = 0;
-  // Set by runs_count: bits of the run length in a packed key, and the mask
+  // Set by runs_count: bits of the run length in a key (> 0), and the mask
   // of the forced run splits (t & smask == 0 starts a run; all ones: none).
-  int len_bits = 0;
+  int nb = 0;
   uint32_t smask = 0xffffffffu;
   int split_bits = 0;  // > 0: split runs at 2^split_bits samples at most (set by the caller)
   // Rescan order of the baselines (set by runs_build): sorted by the smallest

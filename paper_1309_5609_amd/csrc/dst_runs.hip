@@ -209,29 +209,30 @@ __global__ void __launch_bounds__(kBlock) k_tile_starts(const int32_t* __restric
   }
 }
 
-// One thread per run: length, sums of cos 2psi and sin 2psi, and the setup
-// sums.  Time-order outputs feed the rescan and the right-hand side (pixel,
-// length, C, S, and per baseline and 64-run window the sums of d_T, d_q,
-// d_u); a 64-byte record per run
-// feeds the per-pixel setup, which reads it in pixel order with one aligned
-// access.  Samples are summed in time order.  A wavefront takes 64
-// consecutive runs; when the samples they span fit kStage, the wavefront
-// first copies them (angles and timelines) into LDS with coalesced loads and
-// each lane then reads its run from there.
+// One thread per run: its key (pixel and length), sums of cos 2psi and sin
+// 2psi, and the setup sums.  Time-order outputs feed the rescan and the
+// right-hand side (key, C, S, and per baseline and 64-run window the sums of
+// d_T, d_q, d_u); the record feeds the per-pixel setup, which reads it in pixel
+// order with one aligned access.  Samples are summed in time order.  A
+// wavefront takes 64 consecutive runs; when the samples they span fit kStage,
+// the wavefront first copies them (angles and timelines) into LDS with
+// coalesced loads and each lane then reads its run from there.
 constexpr int kStage = 256;
 // Runs per wavefront of the run build: windows [k kRunWindow, (k + 1) kRunWindow)
 // of the time-order runs, whose per-baseline sums of d the right-hand side reads.
 constexpr int kRunWindow = 64;
 
-template <typename PT, typename TT, typename RT, bool HAS_T, bool HAS_QU, bool IQU, bool TOD>
+template <typename PT, typename TT, typename RT, bool HAS_T, bool HAS_QU, bool IQU, bool TOD, bool EQ>
 __global__ void __launch_bounds__(kBlock) k_run_build(View v, const TT* __restrict__ tod,
                                                       const uint32_t* __restrict__ t0,
-                                                      const unsigned long long* __restrict__ n_out, int64_t R,
-                                                      int32_t* __restrict__ rpix, int32_t* __restrict__ rn,
-                                                      RT* __restrict__ rcs, double* __restrict__ raw,
-                                                      RunRecord* __restrict__ rec) {
+                                                      const unsigned long long* __restrict__ n_out, int64_t R, int nb,
+                                                      uint32_t* __restrict__ rkey, RT* __restrict__ rcs,
+                                                      double* __restrict__ raw, void* __restrict__ rec_) {
+  using Rec = RecordOf<HAS_T, HAS_QU, IQU, TOD, EQ>;
+  Rec* rec = static_cast<Rec*>(rec_);
+  constexpr bool MOM = std::is_same<Rec, RunRecord>::value;  // second moments of the angles kept
   constexpr bool SA = HAS_QU || IQU;                 // angles used
-  constexpr bool TONLY = HAS_T && !HAS_QU && !IQU;   // intensity only: 16-byte records
+  constexpr bool TONLY = HAS_T && !HAS_QU && !IQU;   // intensity only
   constexpr bool ST = TOD && (HAS_T || IQU);         // T (or radiometer) timeline used
   constexpr bool SQ = TOD && HAS_QU && !IQU;         // q/u timelines used
   constexpr int NROW = (ST ? 1 : 0) + (SQ ? 2 : 0);
@@ -290,8 +291,10 @@ __global__ void __launch_bounds__(kBlock) k_run_build(View v, const TT* __restri
         rot2(ps, c, s);
         C += c;
         S += s;
-        cc += c * c;
-        cs += c * s;
+        if (MOM) {
+          cc += c * c;
+          cs += c * s;
+        }
       }
       if (TOD && IQU) {
         // radiometer row (1, c, s): sums of d and of the weighted c d, s d
@@ -346,7 +349,7 @@ __global__ void __launch_bounds__(kBlock) k_run_build(View v, const TT* __restri
       // last lane stores it at its run, so that raw holds, at every run that
       // ends a baseline or a 64-run window, the sum over that baseline's runs
       // in the window (the other entries are never read)
-      const int bl = has ? (int)(ts / v.L) : -1 - lane;
+      const int bl = has ? (int)((uint32_t)ts / (uint32_t)v.L) : -1 - lane;
       double s0 = dT, s1 = dq, s2 = du;
 #pragma unroll
       for (int off = 1; off < 64; off <<= 1) {
@@ -372,28 +375,28 @@ __global__ void __launch_bounds__(kBlock) k_run_build(View v, const TT* __restri
       }
     }
     if (!has) continue;
-    rpix[r] = v.pix[ts];
-    rn[r] = n;
+    rkey[r] = ((uint32_t)v.pix[ts] << nb) | (uint32_t)(n - 1);
     if (SA) reinterpret_cast<CS2<RT>*>(rcs)[r] = make_cs<RT>(C, S);
-    if (TONLY) {
-      RunRecordT x;
-      x.n = n;
-      x.b = (int32_t)(ts / v.L);
+    const uint32_t bkey = (((uint32_t)ts / (uint32_t)v.L) << nb) | (uint32_t)(n - 1);
+    if constexpr (std::is_same<Rec, uint32_t>::value) {
+      rec[r] = bkey;
+    } else {
+      Rec x;
+      x.key = bkey;
+      x.pad = 0;
       x.dT = dT;
-      reinterpret_cast<RunRecordT*>(rec)[r] = x;
-      continue;
+      if constexpr (!std::is_same<Rec, RunRecordT>::value) {
+        x.dQ = dQ;
+        x.dU = dU;
+      }
+      if constexpr (MOM) {
+        x.C = C;
+        x.S = S;
+        x.cc = cc;
+        x.cs = cs;
+      }
+      rec[r] = x;
     }
-    RunRecord x;
-    x.n = n;
-    x.b = (int32_t)(ts / v.L);
-    x.C = C;
-    x.S = S;
-    x.cc = cc;
-    x.cs = cs;
-    x.dT = dT;
-    x.dQ = dQ;
-    x.dU = dU;
-    rec[r] = x;
   }
 }
 
@@ -469,16 +472,22 @@ __global__ void __launch_bounds__(kBlock) k_compact(const uint32_t* __restrict__
 // 32 lanes per compact pixel: its runs (pixel order, time order within
 // the pixel) -> the pixel-order run arrays; hits, weight blocks, inverse,
 // validity; with TOD the sum map and binned map.  The sum of sin^2 2psi over
-// a run is its length minus the sum of cos^2 2psi.
-template <typename RT, bool HAS_T, bool HAS_QU, bool IQU, bool TOD>
+// a run is its length minus the sum of cos^2 2psi.  EQ: equal q/u weights,
+// whose QU block is w h times the unit matrix (NaN when an angle is not
+// finite, which C - C tells).
+template <typename RT, bool HAS_T, bool HAS_QU, bool IQU, bool TOD, bool EQ>
 __global__ void __launch_bounds__(kBlock) k_pixels_from_runs(
     View v, int64_t n_obs, const uint32_t* __restrict__ order, const int64_t* __restrict__ seg,
-    const uint32_t* __restrict__ rperm, const RunRecord* __restrict__ rec, double rcond_cut,
-    int32_t* __restrict__ pb, int32_t* __restrict__ pn, int nb, uint32_t* __restrict__ pkey, RT* __restrict__ pcs,
-    const int64_t* __restrict__ pstart, int32_t* __restrict__ hits, double* __restrict__ Minv4,
-    uint8_t* __restrict__ valid, double* __restrict__ m4_zero, double* __restrict__ sd4, double* __restrict__ md4,
+    const uint32_t* __restrict__ rperm, const void* __restrict__ rec_, const RT* __restrict__ tcs, double rcond_cut,
+    int nb, uint32_t* __restrict__ pkey, RT* __restrict__ pcs, const int64_t* __restrict__ pstart,
+    int32_t* __restrict__ hits, double* __restrict__ Minv4, uint8_t* __restrict__ valid,
+    double* __restrict__ m4_zero, double* __restrict__ sd4, double* __restrict__ md4,
     unsigned long long* __restrict__ counts) {
-  constexpr bool TONLY = HAS_T && !HAS_QU && !IQU;  // 16-byte records
+  using Rec = RecordOf<HAS_T, HAS_QU, IQU, TOD, EQ>;
+  constexpr bool MOM = std::is_same<Rec, RunRecord>::value;
+  constexpr bool ANG = (HAS_QU || IQU) && !MOM;  // angle sums read from the time-order pairs
+  const Rec* rec = static_cast<const Rec*>(rec_);
+  const uint32_t nmask = (1u << nb) - 1u;
   __shared__ unsigned long long lds[4 * 16];
   unsigned long long cnt[4] = {0, 0, 0, 0};
   // LPP lanes per pixel (two pixels per wavefront), U runs per lane and step
@@ -504,42 +513,46 @@ __global__ void __launch_bounds__(kBlock) k_pixels_from_runs(
       uint32_t q[U];
 #pragma unroll
       for (int u = 0; u < U; ++u) q[u] = jb + LPP * u < j1 ? rperm[jb + LPP * u] : 0u;
-      RunRecord xs[U];
+      Rec xs[U];
+      CS2<RT> ang[U];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         if (jb + LPP * u >= j1) continue;
-        if (TONLY) {
-          const RunRecordT y = reinterpret_cast<const RunRecordT*>(rec)[q[u]];
-          xs[u].n = y.n;
-          xs[u].b = y.b;
-          xs[u].dT = y.dT;
-        } else {
-          xs[u] = rec[q[u]];
-        }
+        xs[u] = rec[q[u]];
+        if (ANG) ang[u] = reinterpret_cast<const CS2<RT>*>(tcs)[q[u]];
       }
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int64_t j = jb + LPP * u;
         if (j >= j1) break;
-        const RunRecord& x = xs[u];
+        const Rec& x = xs[u];
         const int64_t d = d0 + (j - j0);
-        pb[d] = x.b;
-        pn[d] = x.n;
-        if (nb > 0) pkey[d] = ((uint32_t)x.b << nb) | (uint32_t)(x.n - 1);
-        acc[0] += (double)x.n;
-        if (HAS_QU || IQU) {
+        uint32_t key;
+        if constexpr (std::is_same<Rec, uint32_t>::value)
+          key = x;
+        else
+          key = x.key;
+        pkey[d] = key;
+        acc[0] += (double)((key & nmask) + 1u);
+        if constexpr (ANG) {
+          reinterpret_cast<CS2<RT>*>(pcs)[d] = ang[u];
+          acc[1] += (double)((ang[u].x - ang[u].x) + (ang[u].y - ang[u].y));
+        }
+        if constexpr (MOM) {
           reinterpret_cast<CS2<RT>*>(pcs)[d] = make_cs<RT>(x.C, x.S);
           acc[1] += x.cc;
           acc[2] += x.cs;
+          if (IQU) {
+            acc[NA - 2] += x.C;
+            acc[NA - 1] += x.S;
+          }
         }
-        if (IQU) {
-          acc[NA - 2] += x.C;
-          acc[NA - 1] += x.S;
-        }
-        if (TOD) {
+        if constexpr (TOD) {
           acc[3] += x.dT;
-          acc[4] += x.dQ;
-          acc[5] += x.dU;
+          if constexpr (!std::is_same<Rec, RunRecordT>::value) {
+            acc[4] += x.dQ;
+            acc[5] += x.dU;
+          }
         }
       }
     }
@@ -607,21 +620,10 @@ __global__ void __launch_bounds__(kBlock) k_pixels_from_runs(
       if (HAS_QU && h > 0) {
         const double wq = v.w[1], wu = v.w[2];
         const double scc = acc[1], sss = acc[0] - acc[1];
-        const double a = wq * scc + wu * sss;
-        const double b = (wq - wu) * acc[2];
-        const double d = wq * sss + wu * scc;
-        // eigenvalues of the symmetric 2x2 block [[a, b], [b, d]]
-        const double half = 0.5 * (a - d);
-        const double rad = sqrt(half * half + b * b);
-        const double lmax = 0.5 * (a + d) + rad;
-        const double det = a * d - b * b;
-        const double lmin = lmax > 0.0 ? det / lmax : 0.0;
-        if (lmax > 0.0 && lmin > 0.0 && lmin >= rcond_cut * lmax) {
-          f |= 2;
-          inv[1] = d / det;
-          inv[2] = -b / det;
-          inv[3] = a / det;
-        }
+        const double a = EQ ? wq * acc[0] + acc[1] : wq * scc + wu * sss;
+        const double b = EQ ? 0.0 : (wq - wu) * acc[2];
+        const double d = EQ ? a : wq * sss + wu * scc;
+        if (dev::qu_block_inverse(a, b, d, rcond_cut, inv + 1)) f |= 2;
       }
       hits[c] = (int32_t)h;
       double2* mi = reinterpret_cast<double2*>(Minv4 + 4 * c);
@@ -655,40 +657,35 @@ __global__ void __launch_bounds__(kBlock) k_pixels_from_runs(
   }
 }
 
-// One wavefront per baseline: its time-order runs take compact pixel ids
-// (pixel -> cid) and, with nb > 0, the packed iteration keys
-// c << nb | (length - 1); key[b] = the smallest compact id the baseline
-// visits (n_obs when none), which orders baselines for the rescan;
-// val[b] = b.
+// One wavefront per baseline: its time-order run keys take compact pixel ids,
+// pixel << nb | (length - 1) -> c << nb | (length - 1); key[b] = the smallest
+// compact id the baseline visits (n_obs when none), which orders baselines for
+// the rescan; val[b] = b.
 __global__ void __launch_bounds__(kBlock) k_compact_baselines(int64_t n_b, int64_t n_obs, int nb,
                                                               const uint32_t* __restrict__ bstart,
                                                               const int32_t* __restrict__ cid,
-                                                              int32_t* __restrict__ tpix,
-                                                              const int32_t* __restrict__ tn,
                                                               uint32_t* __restrict__ tkey, uint32_t* __restrict__ key,
                                                               uint32_t* __restrict__ val) {
   constexpr int U = 4;  // runs per lane whose loads are issued together
   const int lane = lane_id();
+  const uint32_t nmask = (1u << nb) - 1u;
   const int64_t nw = (int64_t)gridDim.x * kWaves;
   for (int64_t b = (int64_t)blockIdx.x * kWaves + (threadIdx.x >> 6); b < n_b; b += nw) {
     uint32_t m = (uint32_t)n_obs;
     const int64_t r0 = bstart[b], r1 = bstart[b + 1];
     for (int64_t rb = r0 + lane; rb < r1; rb += 64 * U) {
-      int32_t p[U], len[U];
+      uint32_t k[U];
+      int32_t c[U];
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int64_t r = rb + 64 * u;
-        p[u] = r < r1 ? tpix[r] : 0;
-        len[u] = (nb > 0 && r < r1) ? tn[r] : 1;
-      }
+      for (int u = 0; u < U; ++u) k[u] = rb + 64 * u < r1 ? tkey[rb + 64 * u] : 0u;
+#pragma unroll
+      for (int u = 0; u < U; ++u) c[u] = cid[k[u] >> nb];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int64_t r = rb + 64 * u;
         if (r >= r1) break;
-        const int32_t c = cid[p[u]];
-        tpix[r] = c;
-        if (nb > 0) tkey[r] = ((uint32_t)c << nb) | (uint32_t)(len[u] - 1);
-        m = min(m, (uint32_t)c);
+        tkey[r] = ((uint32_t)c[u] << nb) | (k[u] & nmask);
+        m = min(m, (uint32_t)c[u]);
       }
     }
     for (int off = 32; off > 0; off >>= 1) m = min(m, (uint32_t)__shfl_xor((int)m, off, 64));
@@ -706,11 +703,10 @@ __global__ void __launch_bounds__(kBlock) k_compact_baselines(int64_t n_b, int64
 // read again here.  The rescan's layout: 16 lanes per baseline, four
 // baselines per wavefront in the rescan order, the loads of four runs per
 // lane issued together.
-template <typename RT, typename TT, bool HAS_T, bool HAS_QU, bool IQU, bool TOD, bool PK>
+template <typename RT, typename TT, bool HAS_T, bool HAS_QU, bool IQU, bool TOD>
 __global__ void __launch_bounds__(kBlock) k_rhs_runs(View v, const uint32_t* __restrict__ bstart,
                                                      const uint32_t* __restrict__ border,
-                                                     const uint32_t* __restrict__ rkey,
-                                                     const int32_t* __restrict__ rn, int nb,
+                                                     const uint32_t* __restrict__ rkey, int nb,
                                                      const RT* __restrict__ rcs,
                                                      const double* __restrict__ raw, const double* __restrict__ md4,
                                                      const TT* __restrict__ tod, const uint32_t* __restrict__ t0,
@@ -738,9 +734,8 @@ __global__ void __launch_bounds__(kBlock) k_rhs_runs(View v, const uint32_t* __r
         const int64_t r = rb + SEG * u;
         const bool in = r < r1;
         const uint32_t key = in ? rkey[r] : 0u;
-        // packed keys (PK): compact pixel << nb | (length - 1); else pixel, lengths in rn
-        c[u] = in ? (int)(PK ? key >> nb : key) : -1;
-        nn[u] = in ? (PK ? (int)(key & ((1u << nb) - 1u)) + 1 : rn[r]) : 0;
+        c[u] = in ? (int)(key >> nb) : -1;
+        nn[u] = in ? (int)(key & ((1u << nb) - 1u)) + 1 : 0;
       }
       uint8_t f[U];
       double2 m01[U];
@@ -840,21 +835,19 @@ __global__ void __launch_bounds__(kBlock) k_rhs_runs(View v, const uint32_t* __r
 
 // ---------------------------------------------------------------- iteration kernels
 
-// Run stream of U runs j, j + stride, ... (key, length, and the interleaved
-// pair of sums of cos 2psi and sin 2psi, one load).  Every load is issued, with index 0 for runs at or past j1, so
-// the loads of all U runs are in flight together with no branches between
-// them; the caller zeroes those runs' terms.  PK: packed keys (index << nb |
-// length - 1), else index keys with the lengths in len_arr.
-template <typename RT, bool LEN, bool ANG, bool PK, int U>
-__device__ __forceinline__ void load_runs(const uint32_t* __restrict__ key_arr, const int32_t* __restrict__ len_arr,
-                                          const RT* __restrict__ cs_arr, int64_t j,
-                                          int64_t stride, int64_t j1, uint32_t (&key)[U], int32_t (&len)[U],
-                                          RT (&C)[U], RT (&S)[U]) {
+// Run stream of U runs j, j + stride, ... (the key, index << nb | length - 1,
+// and the interleaved pair of sums of cos 2psi and sin 2psi, one load).  Every
+// load is issued, with index 0 for runs at or past j1, so the loads of all U
+// runs are in flight together with no branches between them; the caller zeroes
+// those runs' terms.
+template <typename RT, bool ANG, int U>
+__device__ __forceinline__ void load_runs(const uint32_t* __restrict__ key_arr, const RT* __restrict__ cs_arr,
+                                          int64_t j, int64_t stride, int64_t j1, uint32_t (&key)[U], RT (&C)[U],
+                                          RT (&S)[U]) {
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     const int64_t jj = j + stride * u < j1 ? j + stride * u : 0;
     key[u] = key_arr[jj];
-    len[u] = (LEN && !PK) ? len_arr[jj] : 0;
     const CS2<RT> cs = ANG ? reinterpret_cast<const CS2<RT>*>(cs_arr)[jj] : make_cs<RT>(0.0, 0.0);
     C[u] = cs.x;
     S[u] = cs.y;
@@ -862,11 +855,11 @@ __device__ __forceinline__ void load_runs(const uint32_t* __restrict__ key_arr, 
 }
 
 // Index, length and angle sums of a loaded run; zero terms past j1.
-template <typename RT, bool PK>
-__device__ __forceinline__ void decode_run(uint32_t key, int32_t len, RT c, RT s, bool in, int nb, int32_t& idx,
-                                           double& n, double& C, double& S) {
-  idx = (int32_t)(PK ? key >> nb : key);
-  n = in ? (double)(PK ? (int32_t)(key & ((1u << nb) - 1u)) + 1 : len) : 0.0;
+template <typename RT>
+__device__ __forceinline__ void decode_run(uint32_t key, RT c, RT s, bool in, int nb, int32_t& idx, double& n,
+                                           double& C, double& S) {
+  idx = (int32_t)(key >> nb);
+  n = in ? (double)((int32_t)(key & ((1u << nb) - 1u)) + 1) : 0.0;
   C = in ? (double)c : 0.0;
   S = in ? (double)s : 0.0;
 }
@@ -875,10 +868,10 @@ __device__ __forceinline__ void decode_run(uint32_t key, int32_t len, RT c, RT s
 // work on one pixel (64 / LPP pixels per wavefront, each with its own chain of
 // dependent loads in flight); pw4[b] = (w_T p_T, w_q p_q, w_u p_u, 0).
 // The body takes the workgroup's place (vblock of vgrid) in its problem's grid.
-template <typename RT, bool HAS_T, bool HAS_QU, bool IQU, int LPP, bool PK>
+template <typename RT, bool HAS_T, bool HAS_QU, bool IQU, int LPP>
 __device__ __forceinline__ void bin_runs_body(int64_t n_obs, const int64_t* __restrict__ pstart,
-                                              const uint32_t* __restrict__ pb, const int32_t* __restrict__ pn,
-                                              int nb, const RT* __restrict__ pcs, const double* __restrict__ pw4,
+                                              const uint32_t* __restrict__ pkey, int nb,
+                                              const RT* __restrict__ pcs, const double* __restrict__ pw4,
                                               const double* __restrict__ Minv4, const uint8_t* __restrict__ valid,
                                               double* __restrict__ m4, int64_t vblock, int64_t vgrid) {
   constexpr int PPW = 64 / LPP;
@@ -899,16 +892,14 @@ __device__ __forceinline__ void bin_runs_body(int64_t n_obs, const int64_t* __re
     double acc[3] = {0.0, 0.0, 0.0};
     for (int64_t jb = j0 + sub; jb < j1; jb += LPP * U) {
       uint32_t key[U];
-      int32_t len[U];
       RT cr[U], sr[U];
-      // packed keys (PK): baseline << nb | (length - 1); else baseline, lengths in pn
-      load_runs<RT, HAS_T, HAS_QU || IQU, PK, U>(pb, pn, pcs, jb, LPP, j1, key, len, cr, sr);
+      load_runs<RT, HAS_QU || IQU, U>(pkey, pcs, jb, LPP, j1, key, cr, sr);
       double2 x0[U];
       double u0[U], nn[U], cc[U], ss[U];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         int32_t bb;
-        decode_run<RT, PK>(key[u], len[u], cr[u], sr[u], jb + LPP * u < j1, nb, bb, nn[u], cc[u], ss[u]);
+        decode_run<RT>(key[u], cr[u], sr[u], jb + LPP * u < j1, nb, bb, nn[u], cc[u], ss[u]);
         // runs past j1 read baseline pw4 of run 0 (a valid index) and add nothing
         if (TONLY) {
           x0[u] = make_double2(pw4[bb], 0.0);
@@ -958,18 +949,17 @@ __device__ __forceinline__ void bin_runs_body(int64_t n_obs, const int64_t* __re
   }
 }
 
-template <typename RT, bool HAS_T, bool HAS_QU, bool IQU, int LPP, bool PK>
+template <typename RT, bool HAS_T, bool HAS_QU, bool IQU, int LPP>
 __global__ void __launch_bounds__(kBlock) k_bin_runs(int64_t n_obs, const int64_t* __restrict__ pstart,
-                                                     const uint32_t* __restrict__ pb, const int32_t* __restrict__ pn,
-                                                     int nb,
+                                                     const uint32_t* __restrict__ pkey, int nb,
                                                      const RT* __restrict__ pcs,
                                                      const double* __restrict__ pw4,
                                                      const double* __restrict__ Minv4,
                                                      const uint8_t* __restrict__ valid, double* __restrict__ m4,
                                                      const CgCtl* __restrict__ gate) {
   if (gate && gate->done) return;
-  bin_runs_body<RT, HAS_T, HAS_QU, IQU, LPP, PK>(n_obs, pstart, pb, pn, nb, pcs, pw4, Minv4, valid, m4, blockIdx.x,
-                                                  gridDim.x);
+  bin_runs_body<RT, HAS_T, HAS_QU, IQU, LPP>(n_obs, pstart, pkey, nb, pcs, pw4, Minv4, valid, m4, blockIdx.x,
+                                              gridDim.x);
 }
 
 // The same binning with a three-stage software pipeline over the
@@ -980,8 +970,7 @@ __global__ void __launch_bounds__(kBlock) k_bin_runs(int64_t n_obs, const int64_
 // both precisions, kept as a launch shape for the autotuner.
 template <typename RT, bool HAS_T, bool HAS_QU, bool IQU, int LPP>
 __global__ void __launch_bounds__(kBlock) k_bin_runs_pipe(int64_t n_obs, const int64_t* __restrict__ pstart,
-                                                          const uint32_t* __restrict__ pb,
-                                                          const int32_t* __restrict__ pn, int nb,
+                                                          const uint32_t* __restrict__ pkey, int nb,
                                                           const RT* __restrict__ pcs,
                                                           const double* __restrict__ pw4,
                                                           const double* __restrict__ Minv4,
@@ -1002,15 +991,13 @@ __global__ void __launch_bounds__(kBlock) k_bin_runs_pipe(int64_t n_obs, const i
     j1x = h ? e : j0x;
   };
   uint32_t nkey[U];
-  int32_t nlen[U];
   RT nC[U], nS[U];
   auto fetch = [&](int64_t j0x, int64_t j1x) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int64_t j = j0x + sub + LPP * u;
       const bool in = j < j1x;
-      nkey[u] = in ? pb[j] : 0u;
-      nlen[u] = (HAS_T && !nb && in) ? pn[j] : 0;
+      nkey[u] = in ? pkey[j] : 0u;
       const CS2<RT> cs = ((HAS_QU || IQU) && in) ? reinterpret_cast<const CS2<RT>*>(pcs)[j] : make_cs<RT>(0.0, 0.0);
       nC[u] = cs.x;
       nS[u] = cs.y;
@@ -1030,9 +1017,8 @@ __global__ void __launch_bounds__(kBlock) k_bin_runs_pipe(int64_t n_obs, const i
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const bool in = j0 + sub + LPP * u < j1;
-      // packed keys (nb > 0): baseline << nb | (length - 1); else baseline, lengths in pn
-      bb[u] = in ? (int32_t)(nb ? nkey[u] >> nb : nkey[u]) : -1;
-      nn[u] = (HAS_T && in) ? (nb ? (int32_t)(nkey[u] & ((1u << nb) - 1u)) + 1 : nlen[u]) : 0;
+      bb[u] = in ? (int32_t)(nkey[u] >> nb) : -1;
+      nn[u] = (HAS_T && in) ? (int32_t)(nkey[u] & ((1u << nb) - 1u)) + 1 : 0;
       cc[u] = (double)nC[u];
       ss[u] = (double)nS[u];
     }
@@ -1071,15 +1057,13 @@ __global__ void __launch_bounds__(kBlock) k_bin_runs_pipe(int64_t n_obs, const i
     int64_t jb = j0 + sub + LPP * U;
     if (jb < j1) {
       uint32_t rkey[U];
-      int32_t rlen[U];
       RT rC[U], rS[U];
       auto rfetch = [&](int64_t jx) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
           const int64_t j = jx + LPP * u;
           const bool in = j < j1;
-          rkey[u] = in ? pb[j] : 0u;
-          rlen[u] = (HAS_T && !nb && in) ? pn[j] : 0;
+          rkey[u] = in ? pkey[j] : 0u;
           const CS2<RT> cs =
               ((HAS_QU || IQU) && in) ? reinterpret_cast<const CS2<RT>*>(pcs)[j] : make_cs<RT>(0.0, 0.0);
           rC[u] = cs.x;
@@ -1091,8 +1075,8 @@ __global__ void __launch_bounds__(kBlock) k_bin_runs_pipe(int64_t n_obs, const i
 #pragma unroll
         for (int u = 0; u < U; ++u) {
           const bool in = jb + LPP * u < j1;
-          bb[u] = in ? (int32_t)(nb ? rkey[u] >> nb : rkey[u]) : -1;
-          nn[u] = (HAS_T && in) ? (nb ? (int32_t)(rkey[u] & ((1u << nb) - 1u)) + 1 : rlen[u]) : 0;
+          bb[u] = in ? (int32_t)(rkey[u] >> nb) : -1;
+          nn[u] = (HAS_T && in) ? (int32_t)(rkey[u] & ((1u << nb) - 1u)) + 1 : 0;
           cc[u] = (double)rC[u];
           ss[u] = (double)rS[u];
         }
@@ -1159,11 +1143,11 @@ __global__ void __launch_bounds__(kBlock) k_bin_runs_pipe(int64_t n_obs, const i
 // The body takes the workgroup's place (vblock of vgrid, vgrid a multiple of
 // 8 and the problem's first workgroup on a multiple of 8, so vblock % 8 is
 // the hardware's XCD of the workgroup) in its problem's grid.
-template <typename RT, bool HAS_T, bool HAS_QU, bool IQU, bool CG, int BPW, bool PK>
+template <typename RT, bool HAS_T, bool HAS_QU, bool IQU, bool CG, int BPW>
 __device__ __forceinline__ void unbin_runs_body(const View& v, const uint32_t* __restrict__ bstart,
                                                 const uint32_t* __restrict__ border,
-                                                const uint32_t* __restrict__ rpix, const int32_t* __restrict__ rn,
-                                                int nb, const RT* __restrict__ rcs, const double* __restrict__ m4,
+                                                const uint32_t* __restrict__ rkey, int nb, const RT* __restrict__ rcs,
+                                                const double* __restrict__ m4,
                                                 const int32_t* __restrict__ nvalid, const double* __restrict__ p,
                                                 double* __restrict__ q, double* __restrict__ partials, int64_t vblock,
                                                 int64_t vgrid) {
@@ -1192,15 +1176,13 @@ __device__ __forceinline__ void unbin_runs_body(const View& v, const uint32_t* _
     // Software pipeline: the run stream of the next step is loaded while the
     // map values of this step are gathered.
     uint32_t key[U];
-    int32_t len[U];
     RT C[U], S[U];
     auto fetch = [&](int64_t rb) {
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int64_t r = rb + SEG * u;
         const bool in = r < r1;
-        key[u] = in ? rpix[r] : 0u;
-        len[u] = (HAS_T && !PK && in) ? rn[r] : 0;
+        key[u] = in ? rkey[r] : 0u;
         const CS2<RT> cs =
             ((HAS_QU || IQU) && in) ? reinterpret_cast<const CS2<RT>*>(rcs)[r] : make_cs<RT>(0.0, 0.0);
         C[u] = cs.x;
@@ -1213,10 +1195,9 @@ __device__ __forceinline__ void unbin_runs_body(const View& v, const uint32_t* _
       double Cd[U], Sd[U];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        // packed keys (PK): compact pixel << nb | (length - 1); else pixel, lengths in rn
         const bool in = rb + SEG * u < r1;
-        cc_[u] = in ? (int32_t)(PK ? key[u] >> nb : key[u]) : -1;
-        nn[u] = (HAS_T && in) ? (PK ? (int32_t)(key[u] & ((1u << nb) - 1u)) + 1 : len[u]) : 0;
+        cc_[u] = in ? (int32_t)(key[u] >> nb) : -1;
+        nn[u] = (HAS_T && in) ? (int32_t)(key[u] & ((1u << nb) - 1u)) + 1 : 0;
         Cd[u] = (double)C[u];
         Sd[u] = (double)S[u];
       }
@@ -1301,18 +1282,18 @@ __device__ __forceinline__ void unbin_runs_body(const View& v, const uint32_t* _
   }
 }
 
-template <typename RT, bool HAS_T, bool HAS_QU, bool IQU, bool CG, int BPW, bool PK>
+template <typename RT, bool HAS_T, bool HAS_QU, bool IQU, bool CG, int BPW>
 __global__ void __launch_bounds__(kBlock) k_unbin_runs(View v, const uint32_t* __restrict__ bstart,
                                                        const uint32_t* __restrict__ border,
-                                                       const uint32_t* __restrict__ rpix,
-                                                       const int32_t* __restrict__ rn, int nb, const RT* __restrict__ rcs,
+                                                       const uint32_t* __restrict__ rkey, int nb,
+                                                       const RT* __restrict__ rcs,
                                                        const double* __restrict__ m4,
                                                        const int32_t* __restrict__ nvalid,
                                                        const double* __restrict__ p, double* __restrict__ q,
                                                        CgCtl* __restrict__ ctl, double* __restrict__ partials) {
   if (CG && ctl->done) return;
-  unbin_runs_body<RT, HAS_T, HAS_QU, IQU, CG, BPW, PK>(v, bstart, border, rpix, rn, nb, rcs, m4, nvalid, p, q,
-                                                       partials, blockIdx.x, gridDim.x);
+  unbin_runs_body<RT, HAS_T, HAS_QU, IQU, CG, BPW>(v, bstart, border, rkey, nb, rcs, m4, nvalid, p, q, partials,
+                                                   blockIdx.x, gridDim.x);
 }
 
 // Stable sort of the runs by pixel in onesweep passes of ten bits, so the
@@ -1390,14 +1371,15 @@ int64_t run_tiles(int64_t n_t) { return (n_t + kTile - 1) / kTile; }
 hipError_t runs_count(const View& v, Runs& W, int* err, hipStream_t st) {
   const int64_t n_t = v.n_t, n_tiles = run_tiles(n_t);
   // run-length bits of the packed keys: all of L when it fits beside the
-  // pixel (bounded by n_pix) and baseline indices, else runs are split
+  // pixel (bounded by n_pix) and baseline indices, else runs are split (indices
+  // are below 2^31, so at least one bit is left)
   int room = 32 - (int)std::max(key_bits(std::max<int64_t>(v.n_pix, 1)), key_bits(std::max<int64_t>(v.n_b, 1)));
   if (W.split_bits > 0) room = std::min(room, W.split_bits);
-  if ((int)key_bits(v.L) <= room || room < 1) {
-    W.len_bits = (int)key_bits(v.L);
+  if ((int)key_bits(v.L) <= room) {
+    W.nb = (int)key_bits(v.L);
     W.smask = 0xffffffffu;
   } else {
-    W.len_bits = room;
+    W.nb = room;
     W.smask = (1u << room) - 1u;
   }
   const unsigned g = grid_for(n_tiles, kWaves, 8192);
@@ -1460,19 +1442,20 @@ hipError_t runs_build(const View& v, int psi_f32, const void* tod, int tod_f32, 
   // 2. run records and setup moments (time order)
   const bool pf = psi_f32 && (v.rowQ >= 0 || v.iqu);
   const unsigned grb = grid_for(R, kBlock, 16384);  // 64 runs per wavefront, 256 per workgroup
+  const bool eq = v.w[1] == v.w[2];
   by_float(pf, [&](auto pt) {
     using PT = typename decltype(pt)::type;
     by_float(tod_f32, [&](auto tt) {
       using TT = typename decltype(tt)::type;
-      by_float(W.f32, [&](auto rt) {
-        using RT = typename decltype(rt)::type;
-        by_streams(v, [&](auto T, auto Q, auto I) {
-          by_bool(tod != nullptr, [&](auto D) {
-            hipLaunchKernelGGL((k_run_build<PT, TT, RT, decltype(T)::value, decltype(Q)::value, decltype(I)::value,
-                                            decltype(D)::value>),
+      // the sums' type is the angles'
+      by_streams(v, [&](auto T, auto Q, auto I) {
+        by_bool(tod != nullptr, [&](auto D) {
+          by_bool(eq, [&](auto E) {
+            constexpr bool HT = decltype(T)::value, HQ = decltype(Q)::value, HI = decltype(I)::value;
+            hipLaunchKernelGGL((k_run_build<PT, TT, PT, HT, HQ, HI, decltype(D)::value,
+                                            HQ && !HI && decltype(E)::value>),
                                dim3(grb), dim3(kBlock), 0, st, v, static_cast<const TT*>(tod), W.t0, W.n_out, W.R,
-                               W.tpix, W.tn,
-                               static_cast<RT*>(W.tcs), W.raw, W.rec);
+                               W.nb, W.tkey, static_cast<PT*>(W.tcs), W.raw, W.rec);
           });
         });
       });
@@ -1516,11 +1499,6 @@ hipError_t runs_build(const View& v, int psi_f32, const void* tod, int tod_f32, 
     DST_CHECK(rocprim::exclusive_scan(W.tmp, tmp, W.ccount, W.pstart, (int64_t)0, (size_t)W.n_obs + 1,
                                       rocprim::plus<int64_t>(), st));
   }
-  // one 32-bit key per run for the iterations (index and length) when both fit
-  const unsigned nb = (unsigned)W.len_bits;
-  W.nb = 0;
-  if (W.tkey && W.pkey && key_bits(std::max<int64_t>(W.n_obs, 1)) + nb <= 32 && key_bits(v.n_b) + nb <= 32)
-    W.nb = (int)nb;
   // 5. per-pixel setup from the runs; pixel-order run arrays and keys
   if (W.n_obs > 0) {
     // two pixels per wavefront; at most 16384 workgroups, each taking pixels
@@ -1531,11 +1509,14 @@ hipError_t runs_build(const View& v, int psi_f32, const void* tod, int tod_f32, 
       using RT = typename decltype(rt)::type;
       by_streams(v, [&](auto T, auto Q, auto I) {
         by_bool(tod != nullptr, [&](auto D) {
-          hipLaunchKernelGGL((k_pixels_from_runs<RT, decltype(T)::value, decltype(Q)::value, decltype(I)::value,
-                                                 decltype(D)::value>),
-                             dim3(gw), dim3(kBlock), 0, st, v, W.n_obs, W.order, W.seg, W.rperm, W.rec, rcond_cut,
-                             W.pb, W.pn, W.nb, W.pkey, static_cast<RT*>(W.pcs), W.pstart, hits, Minv4,
-                             valid, m4_zero, sd4, md4, counts);
+          by_bool(eq, [&](auto E) {
+            constexpr bool HT = decltype(T)::value, HQ = decltype(Q)::value, HI = decltype(I)::value;
+            hipLaunchKernelGGL((k_pixels_from_runs<RT, HT, HQ, HI, decltype(D)::value,
+                                                   HQ && !HI && decltype(E)::value>),
+                               dim3(gw), dim3(kBlock), 0, st, v, W.n_obs, W.order, W.seg, W.rperm, W.rec,
+                               static_cast<const RT*>(W.tcs), rcond_cut, W.nb, W.pkey, static_cast<RT*>(W.pcs),
+                               W.pstart, hits, Minv4, valid, m4_zero, sd4, md4, counts);
+          });
         });
       });
     });
@@ -1545,7 +1526,7 @@ hipError_t runs_build(const View& v, int psi_f32, const void* tod, int tod_f32, 
   // rescan order of the baselines: by the smallest compact id each visits (stable)
   if (v.n_b > 0) {
     hipLaunchKernelGGL(k_compact_baselines, dim3(grid_for(v.n_b, kWaves, 16384)), dim3(kBlock), 0, st, v.n_b,
-                       W.n_obs, W.nb, W.bstart, W.cid, W.tpix, W.tn, W.tkey, W.bkey[0], W.bord[0]);
+                       W.n_obs, W.nb, W.bstart, W.cid, W.tkey, W.bkey[0], W.bord[0]);
     DST_CHECK(hipGetLastError());
     rocprim::double_buffer<uint32_t> keys(W.bkey[0], W.bkey[1]);
     rocprim::double_buffer<uint32_t> vals(W.bord[0], W.bord[1]);
@@ -1566,14 +1547,11 @@ hipError_t launch_rhs_runs(const View& vc, const Runs& W, const void* tod, int t
       using TT = typename decltype(tt)::type;
       by_streams(vc, [&](auto T, auto Q, auto I) {
         by_bool(tod != nullptr, [&](auto D) {
-          by_bool(W.nb != 0, [&](auto K) {
-            hipLaunchKernelGGL((k_rhs_runs<RT, TT, decltype(T)::value, decltype(Q)::value, decltype(I)::value,
-                                            decltype(D)::value, decltype(K)::value>),
-                               dim3(g), dim3(kBlock), 0, st, vc, W.bstart, W.border,
-                               W.nb ? W.tkey : reinterpret_cast<const uint32_t*>(W.tpix), W.tn, W.nb,
-                               static_cast<const RT*>(W.tcs), W.raw, md4, static_cast<const TT*>(tod), W.t0,
-                               valid, nvalid, J, b);
-          });
+          hipLaunchKernelGGL((k_rhs_runs<RT, TT, decltype(T)::value, decltype(Q)::value, decltype(I)::value,
+                                          decltype(D)::value>),
+                             dim3(g), dim3(kBlock), 0, st, vc, W.bstart, W.border, W.tkey, W.nb,
+                             static_cast<const RT*>(W.tcs), W.raw, md4, static_cast<const TT*>(tod), W.t0, valid,
+                             nvalid, J, b);
         });
       });
     });
@@ -1606,8 +1584,7 @@ hipError_t launch_bin_runs(const View& vc, const Runs& W, const double* pw4, con
     by_streams(vc, [&](auto T, auto Q, auto I) {
       constexpr bool HT = decltype(T)::value, HQ = decltype(Q)::value, HI = decltype(I)::value;
       auto launch = [&](auto kern) {
-        hipLaunchKernelGGL(kern, dim3(g), dim3(kBlock), 0, st, W.n_obs, W.pstart,
-                           W.nb ? W.pkey : reinterpret_cast<const uint32_t*>(W.pb), W.pn, W.nb,
+        hipLaunchKernelGGL(kern, dim3(g), dim3(kBlock), 0, st, W.n_obs, W.pstart, W.pkey, W.nb,
                            static_cast<const RT*>(W.pcs), pw4, Minv4, valid, m4, gate);
       };
       // the pipelined variant keeps the four-double layout: not for intensity-only problems
@@ -1616,19 +1593,16 @@ hipError_t launch_bin_runs(const View& vc, const Runs& W, const double* pw4, con
         return;
       }
       if (pipe) lpp = 64;
-      by_bool(W.nb != 0, [&](auto K) {
-        constexpr bool PK = decltype(K)::value;
-        if (lpp == 4)
-          launch(k_bin_runs<RT, HT, HQ, HI, 4, PK>);
-        else if (lpp == 8)
-          launch(k_bin_runs<RT, HT, HQ, HI, 8, PK>);
-        else if (lpp == 16)
-          launch(k_bin_runs<RT, HT, HQ, HI, 16, PK>);
-        else if (lpp == 32)
-          launch(k_bin_runs<RT, HT, HQ, HI, 32, PK>);
-        else
-          launch(k_bin_runs<RT, HT, HQ, HI, 64, PK>);
-      });
+      if (lpp == 4)
+        launch(k_bin_runs<RT, HT, HQ, HI, 4>);
+      else if (lpp == 8)
+        launch(k_bin_runs<RT, HT, HQ, HI, 8>);
+      else if (lpp == 16)
+        launch(k_bin_runs<RT, HT, HQ, HI, 16>);
+      else if (lpp == 32)
+        launch(k_bin_runs<RT, HT, HQ, HI, 32>);
+      else
+        launch(k_bin_runs<RT, HT, HQ, HI, 64>);
     });
   });
   return hipGetLastError();
@@ -1651,22 +1625,17 @@ hipError_t launch_unbin_runs(const View& vc, const Runs& W, const double* m4, co
         constexpr bool HT = decltype(T)::value, HQ = decltype(Q)::value, HI = decltype(I)::value;
         constexpr bool C = decltype(CG)::value;
         auto launch = [&](auto kern) {
-          hipLaunchKernelGGL(kern, dim3(g), dim3(kBlock), 0, st, vc, W.bstart, W.border,
-                             W.nb ? W.tkey : reinterpret_cast<const uint32_t*>(W.tpix), W.tn, W.nb,
-                             static_cast<const RT*>(W.tcs), m4, nvalid, p, q, ctl,
-                             partials);
+          hipLaunchKernelGGL(kern, dim3(g), dim3(kBlock), 0, st, vc, W.bstart, W.border, W.tkey, W.nb,
+                             static_cast<const RT*>(W.tcs), m4, nvalid, p, q, ctl, partials);
         };
-        by_bool(W.nb != 0, [&](auto K) {
-          constexpr bool PK = decltype(K)::value;
-          if (bpw == 8)
-            launch(k_unbin_runs<RT, HT, HQ, HI, C, 8, PK>);
-          else if (bpw == 4)
-            launch(k_unbin_runs<RT, HT, HQ, HI, C, 4, PK>);
-          else if (bpw == 2)
-            launch(k_unbin_runs<RT, HT, HQ, HI, C, 2, PK>);
-          else
-            launch(k_unbin_runs<RT, HT, HQ, HI, C, 1, PK>);
-        });
+        if (bpw == 8)
+          launch(k_unbin_runs<RT, HT, HQ, HI, C, 8>);
+        else if (bpw == 4)
+          launch(k_unbin_runs<RT, HT, HQ, HI, C, 4>);
+        else if (bpw == 2)
+          launch(k_unbin_runs<RT, HT, HQ, HI, C, 2>);
+        else
+          launch(k_unbin_runs<RT, HT, HQ, HI, C, 1>);
       });
     });
   });
@@ -1686,8 +1655,8 @@ __global__ void __launch_bounds__(kBlock) k_group_bin(GroupLaunch G) {
   const GroupProblem& P = G.prob[S.first + j];
   if (P.ctl->done) return;
   const int64_t vb = b - S.bin_start[j], vg = S.bin_start[j + 1] - S.bin_start[j];
-  bin_runs_body<RT, HT, HQ, HI, LPP, true>(P.v.n_pix, P.pstart, P.pkey, nullptr, P.nb, static_cast<const RT*>(P.pcs),
-                                           P.pw4, P.Minv4, P.valid, P.m4, vb, vg);
+  bin_runs_body<RT, HT, HQ, HI, LPP>(P.v.n_pix, P.pstart, P.pkey, P.nb, static_cast<const RT*>(P.pcs), P.pw4, P.Minv4,
+                                     P.valid, P.m4, vb, vg);
 }
 
 template <typename RT, int KIND, int BPW>
@@ -1699,9 +1668,8 @@ __global__ void __launch_bounds__(kBlock) k_group_unbin(GroupLaunch G) {
   const GroupProblem& P = G.prob[S.first + j];
   if (P.ctl->done) return;
   const int64_t vb = b - S.unbin_start[j], vg = S.unbin_start[j + 1] - S.unbin_start[j];
-  unbin_runs_body<RT, HT, HQ, HI, true, BPW, true>(P.v, P.bstart, P.border, P.tkey, nullptr, P.nb,
-                                                   static_cast<const RT*>(P.tcs), P.m4, P.nvalid, P.p, P.q,
-                                                   P.part_unbin, vb, vg);
+  unbin_runs_body<RT, HT, HQ, HI, true, BPW>(P.v, P.bstart, P.border, P.tkey, P.nb, static_cast<const RT*>(P.tcs), P.m4,
+                                             P.nvalid, P.p, P.q, P.part_unbin, vb, vg);
 }
 
 // One workgroup per problem.
