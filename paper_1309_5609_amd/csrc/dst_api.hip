@@ -66,8 +66,8 @@ struct dst_ctx {
   // shared-pointing batch, problem group), updated in place by each capture
   hipGraphExec_t graphs[3] = {nullptr, nullptr, nullptr};
   hipStream_t cap = nullptr;  // private stream on which iteration graphs are captured
-  int unbin_bpw = 4;          // launch shape of the run rescan (baselines per wavefront)
-  int bin_lpp = 0;            // launch shape of the run binning (lanes per pixel; 0: default 32)
+  int unbin_bpw = 0;          // launch shape of the run rescan (baselines per wavefront; 0 by size)
+  int bin_lpp = 0;            // launch shape of the run binning (lanes per pixel; 0 by size)
   int bin_form = -1;          // form of the run binning (dst_forms.h; -1 by size)
   int run_split_bits = 0;     // > 0: longest run 2^bits samples (runs split beyond; results unchanged)
   // launch shapes chosen by the autotuner, per problem shape: lanes per pixel of the binning (0: its other form),
@@ -614,12 +614,12 @@ int build_bin(dst_ctx* ctx, Plan& P, hipStream_t st) {
 int build_plan(dst_ctx* ctx, const dst_problem* prob, Plan& P, const void* tod, double** sd4, double** md4,
                double* b, hipStream_t st) {
   P.lpp = ctx->bin_lpp;
-  P.bpw = ctx->unbin_bpw;
+  P.bpw = ctx->unbin_bpw ? ctx->unbin_bpw : dst::unbin_bpw_for(P.full.n_b, P.full.iqu);
   if (!P.runs) return build_sample_plan(ctx, prob, P, tod, sd4, md4, b, st);
   DST_TRY(build_runs_plan(ctx, prob, P, tod, sd4, md4, b, st));
   if (P.lpp == 0) {
     const View& v = P.S.v;
-    P.lpp = dst::bin_lanes_for(P.W.R, P.W.n_obs, v.rowT >= 0 && v.rowQ < 0 && !v.iqu);
+    P.lpp = dst::bin_lanes_for(P.W.R, P.W.n_obs, v.rowT >= 0 && v.rowQ < 0 && !v.iqu, v.iqu);
   }
   return DST_OK;
 }
@@ -649,7 +649,7 @@ int plan_unbin(dst_ctx* ctx, Plan& P, const double* p, double* q, CgCtl* ctl, do
 // out = K v = F^T Z F v through the solver's kernels.
 int plan_operator(dst_ctx* ctx, Plan& P, const double* vin, double* out, hipStream_t st) {
   Setup& S = P.S;
-  HIP_TRY(dst::launch_p_update4(S.v, const_cast<double*>(vin), nullptr, P.pw4, nullptr, 0, P.dense_t, st));
+  HIP_TRY(dst::launch_pw4(S.v, vin, P.pw4, nullptr, P.dense_t, st));
   DST_TRY(plan_bin(ctx, P, nullptr, st));
   DST_TRY(plan_unbin(ctx, P, vin, out, nullptr, nullptr, st));
   return DST_OK;
@@ -1024,7 +1024,7 @@ int solve_uneven(dst_ctx* ctx, const dst_problem* problems, const std::vector<in
     DST_TRY(build_runs_plan(ctx, &pr, m.P, pr.tod, &m.sd4, &m.md4, m.b, st));
     DST_TRY(build_bin(ctx, m.P, st));
     // the closing operator of each problem: its own lanes per pixel (32 for all took 4.2 ms of an 80 ms survey batch)
-    m.P.lpp = dst::bin_lanes_for(m.P.W.R, m.P.W.n_obs, m.P.dense_t);
+    m.P.lpp = dst::bin_lanes_for(m.P.W.R, m.P.W.n_obs, m.P.dense_t, v.iqu);
     DST_TRY(ws(ctx, "cg_a", N, &m.a));
     DST_TRY(ws(ctx, "cg_r", N, &m.r));
     DST_TRY(ws(ctx, "cg_z", N, &m.z));
@@ -1042,7 +1042,7 @@ int solve_uneven(dst_ctx* ctx, const dst_problem* problems, const std::vector<in
     HIP_TRY(dst::launch_comp_project(cv, m.b, 1, 1, st));
     HIP_TRY(dst::launch_cg_start(v, m.b, nullptr, nullptr, m.a, m.r, m.z, m.p, m.P.S.J, m.ctl, m.part, opts.tol,
                                  opts.max_iter, st));
-    HIP_TRY(dst::launch_p_update4(v, m.p, nullptr, m.P.pw4, nullptr, 0, m.P.dense_t, st));
+    HIP_TRY(dst::launch_pw4(v, m.p, m.P.pw4, nullptr, m.P.dense_t, st));
     HIP_TRY(hipMemcpyAsync(m.counts, m.P.S.counts, sizeof m.counts, hipMemcpyDeviceToHost, st));
     if (m.P.C.ncomp) HIP_TRY(hipMemcpyAsync(&m.ncomp, m.P.C.ncomp, sizeof m.ncomp, hipMemcpyDeviceToHost, st));
     DST_TRY(finish(ctx, &m.P.S, st));
@@ -1123,7 +1123,7 @@ int solve_uneven(dst_ctx* ctx, const dst_problem* problems, const std::vector<in
       obs += gp[sl.first + j].v.n_pix;
       lds = lds && M[order[sl.first + j]].P.bin.form == dst::BIN_LDS;
     }
-    sl.lpp = dst::bin_lanes_for(runs, obs, K == dst::GK_T);
+    sl.lpp = dst::bin_lanes_for(runs, obs, K == dst::GK_T, K == dst::GK_IQU);
     sl.bpw = group_bpw(ctx, K);
     // one form for the slice: LDS where every problem has it, else by the runs per pixel (or as the context says)
     const bool angles = K == dst::GK_QU || K == dst::GK_TQU;
@@ -1354,7 +1354,7 @@ int gmres_loop(dst_ctx* ctx, Plan& P, const View& v, const double* b, double* a,
       }
       // a += J V y, then the restart residual r = b - P K a and v_0 = r / ||r||
       HIP_TRY(dst::launch_gm_update(gs, S.J, V, a, N, st));
-      HIP_TRY(dst::launch_p_update4(S.v, a, nullptr, P.pw4, gate, 0, P.dense_t, st));
+      HIP_TRY(dst::launch_pw4(S.v, a, P.pw4, gate, P.dense_t, st));
       DST_TRY(plan_bin(ctx, P, gate, st));
       DST_TRY(plan_unbin(ctx, P, a, q, gate, partials, st));
       HIP_TRY(dst::launch_comp_project(cv, q, 1, 1, st));
@@ -1695,7 +1695,7 @@ int dst_solve(dst_ctx* ctx, const dst_problem* prob, const dst_solve_opts* opts_
   HIP_TRY(hipEventRecord(ev[0], st));
 
   const int64_t N = (int64_t)v.n_streams * v.n_b;
-  double *b, *a, *r, *z, *p, *q, *ka, *partials, *sd4 = nullptr, *md4 = nullptr, *rnorm;
+  double *b, *a, *r, *z, *p, *q, *ka, *partials, *part2, *sd4 = nullptr, *md4 = nullptr, *rnorm;
   CgCtl* ctl;
   DST_TRY(ws(ctx, "cg_b", N, &b));
   // pointing setup, binned map and right-hand side b = F^T W (d - A m_d)
@@ -1713,6 +1713,7 @@ int dst_solve(dst_ctx* ctx, const dst_problem* prob, const dst_solve_opts* opts_
   DST_TRY(ws(ctx, "cg_q", N, &q));
   DST_TRY(ws(ctx, "cg_ka", N, &ka));
   DST_TRY(ws(ctx, "cg_part", 3 * (size_t)std::max<int64_t>(v.n_b, 4096), &partials));
+  DST_TRY(ws(ctx, "cg_part2", 2 * (size_t)dst::cg_update_blocks(v), &part2));
   DST_TRY(ws(ctx, "cg_rnorm", 1, &rnorm));
   DST_TRY(ws(ctx, "cg_ctl", 1, &ctl));
   HIP_TRY(dst::launch_fill_u32(reinterpret_cast<uint32_t*>(ctl), sizeof(CgCtl) / 4, 0u, st));
@@ -1728,11 +1729,16 @@ int dst_solve(dst_ctx* ctx, const dst_problem* prob, const dst_solve_opts* opts_
     ka_ptr = ka;
   }
   HIP_TRY(dst::launch_cg_start(v, b, ka_ptr, opts.a0, a, r, z, p, S.J, ctl, partials, opts.tol, opts.max_iter, st));
-  HIP_TRY(dst::launch_p_update4(v, p, nullptr, P.pw4, nullptr, 0, P.dense_t, st));
+  HIP_TRY(dst::launch_pw4(v, p, P.pw4, nullptr, P.dense_t, st));
   if (opts.flags & DST_SOLVE_AUTOTUNE) DST_TRY(autotune(ctx, P, p, ka, st));
 
   // PCG iterations: pixel-major bin + inverse (m = M^-1 A^T W F p) -> rescan and
-  // baseline sums (q = K p, alpha) -> a, r, z update (beta) -> p and its copy
+  // baseline sums (q = K p) -> a, r, z update with the step length -> p and its
+  // copy with beta.  The step length has a kernel of its own when the rescan's
+  // partials are many or several components are projected (known on the host
+  // once the setup has run: until then one is assumed).
+  const int64_t n_step = P.runs ? dst::unbin_runs_parts(vc, P.bpw) : vc.n_b;
+  bool own_step = n_step <= dst::kStepParts;
   auto one_iteration = [&](hipStream_t s, bool timed) -> int {
     hipEvent_t e[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};
     if (timed) {
@@ -1746,11 +1752,10 @@ int dst_solve(dst_ctx* ctx, const dst_problem* prob, const dst_solve_opts* opts_
     if (timed) HIP_TRY(hipEventRecord(e[1], s));
     if (timed) HIP_TRY(hipEventRecord(e[2], s));
     DST_TRY(plan_unbin(ctx, P, p, q, ctl, partials, s));
-    HIP_TRY(dst::launch_cg_alpha(P.runs ? dst::unbin_runs_parts(vc, P.bpw) : vc.n_b, ctl, partials, cv, q, p, s));
+    if (!own_step) HIP_TRY(dst::launch_cg_alpha(n_step, ctl, partials, cv, q, p, s));
     if (timed) HIP_TRY(hipEventRecord(e[3], s));
-    HIP_TRY(dst::launch_cg_update(v, a, r, z, p, q, S.J, ctl, partials, s));
-    HIP_TRY(dst::launch_cg_beta(dst::cg_update_blocks(v), ctl, partials, s));
-    HIP_TRY(dst::launch_p_update4(v, p, z, P.pw4, ctl, 1, P.dense_t, s));
+    HIP_TRY(dst::launch_cg_update(v, a, r, z, p, q, S.J, ctl, own_step ? partials : nullptr, n_step, part2, s));
+    HIP_TRY(dst::launch_cg_direction(v, p, z, P.pw4, ctl, part2, dst::cg_update_blocks(v), P.dense_t, s));
     if (timed) HIP_TRY(hipEventRecord(e[4], s));
     return DST_OK;
   };
@@ -1760,9 +1765,11 @@ int dst_solve(dst_ctx* ctx, const dst_problem* prob, const dst_solve_opts* opts_
   struct {
     hipGraphExec_t exec = nullptr;  // kept by the context
   } gg;
-  if (!use_gmres && !(opts.flags & (DST_SOLVE_NO_GRAPH | DST_SOLVE_PROFILE)))
-    DST_TRY(capture_graph_kept(ctx, 0, check_every,
-                               [&](hipStream_t s) { return one_iteration(s, false); }, &gg.exec));
+  const bool use_graph = !use_gmres && !(opts.flags & (DST_SOLVE_NO_GRAPH | DST_SOLVE_PROFILE));
+  auto capture = [&]() {
+    return capture_graph_kept(ctx, 0, check_every, [&](hipStream_t s) { return one_iteration(s, false); }, &gg.exec);
+  };
+  if (use_graph) DST_TRY(capture());
   HIP_TRY(hipEventRecord(ev[1], st));
   HIP_TRY(hipMemcpyAsync(ctx->ctl_host, ctl, sizeof(CgCtl), hipMemcpyDeviceToHost, st));
   HIP_TRY(hipMemcpyAsync(ctx->rb_host->counts, S.counts, 4 * sizeof(unsigned long long), hipMemcpyDeviceToHost,
@@ -1772,6 +1779,10 @@ int dst_solve(dst_ctx* ctx, const dst_problem* prob, const dst_solve_opts* opts_
   DST_TRY(finish(ctx, &S, st));
   const int ncomp = ctx->rb_host->ncomp[0];
   if (info) info->n_components = ncomp;
+  if (ncomp > 1 && own_step) {
+    own_step = false;
+    if (use_graph) DST_TRY(capture());
+  }
   {
     const unsigned long long* c = ctx->rb_host->counts;
     if (info) {

@@ -15,6 +15,56 @@
 
 namespace dst {
 
+// Workgroups of a grid that finish a reduction for themselves: every one of
+// them reads all partials of the kernel before it, in the same order, so all
+// hold the same bits and no single-workgroup kernel stands between.  What they
+// write for the next kernels (workgroup 0) is not what the others of the same
+// launch read: rz and iter are kept in rz_old and iter_old by the update for
+// the direction, and a `done` seen early stops a workgroup that would have
+// stopped on the same sums.
+//
+// Sums of N rows of n_part partials, valid in every thread, in one order
+// whatever the workgroup's size: partial j belongs to slot j mod 1024, the 64
+// slots of a slice are added by a butterfly and the slices in turn, so a
+// solve's bits do not depend on which kernel finishes the sums.
+// lds: 16 N doubles.
+template <int N>
+__device__ __forceinline__ void sum_rows(const double* __restrict__ partials, int64_t n_part, double (&tot)[N],
+                                         double* lds) {
+  constexpr int kSlots = 1024;
+  const int n_slice = (int)((n_part < kSlots ? n_part + 63 : kSlots) / 64);
+  for (int s = threadIdx.x >> 6; s < n_slice; s += blockDim.x >> 6) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) tot[i] = 0.0;
+    for (int64_t j = s * 64 + dev::lane_id(); j < n_part; j += kSlots) {
+#pragma unroll
+      for (int i = 0; i < N; ++i) tot[i] += partials[i * n_part + j];
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+#pragma unroll
+      for (int i = 0; i < N; ++i) tot[i] += __shfl_xor(tot[i], off, 64);
+    }
+    if (dev::lane_id() == 0) {
+#pragma unroll
+      for (int i = 0; i < N; ++i) lds[i * 16 + s] = tot[i];
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < N; ++i) tot[i] = 0.0;
+  for (int s = 0; s < n_slice; ++s) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) tot[i] = s == 0 ? lds[i * 16] : tot[i] + lds[i * 16 + s];
+  }
+  __syncthreads();
+}
+
+// Outcome of p.(P K p): DONE_RUNNING with a step, or why there is none.
+__device__ __forceinline__ int step_outcome(double pkp) {
+  return !isfinite(pkp) ? DONE_NAN : (pkp <= 0.0 ? DONE_BREAKDOWN : DONE_RUNNING);
+}
+
 // Step length from the rescan's partials (n_part of each kind: p.q, T sum of
 // q, T sum of p): the null-space projection of q = K p (one component: the
 // mean mu over T-valid baselines, applied by the residual update; several:
@@ -23,77 +73,81 @@ namespace dst {
 __device__ inline void cg_alpha_body(int64_t n_part, CgCtl* ctl, const double* partials, const CompView& cv,
                                      double* q, const double* p, double* lds, double* clds) {
   if (ctl->done) return;
-  double tot[3] = {0.0, 0.0, 0.0};
-  for (int64_t j = threadIdx.x; j < n_part; j += blockDim.x) {
-    tot[0] += partials[j];
-    tot[1] += partials[n_part + j];
-    tot[2] += partials[2 * n_part + j];
-  }
-  dev::block_sum<3>(tot, lds);
+  double tot[3];
+  sum_rows<3>(partials, n_part, tot, lds);
   const int ncomp = cv.ncomp ? *cv.ncomp : 0;
   double corr = 0.0;
   if (ncomp > 1) corr = comp_project_block(cv, ncomp, q, p, 1, 1, clds);
   if (threadIdx.x == 0) {
     const double mu = ncomp > 1 ? 0.0 : (ctl->n_e > 0.0 ? tot[1] / ctl->n_e : 0.0);
     const double pkp = ncomp > 1 ? tot[0] - corr : tot[0] - mu * tot[2];
+    const int done = step_outcome(pkp);
     ctl->mu = mu;
-    if (!isfinite(pkp)) {
-      ctl->done = DONE_NAN;
-    } else if (pkp <= 0.0) {
-      ctl->done = DONE_BREAKDOWN;
-    } else {
+    if (done)
+      ctl->done = done;
+    else
       ctl->alpha = ctl->rz / pkp;
-    }
-  }
-}
-
-// Stopping test on ||r|| and beta = r'.z' / r.z from the update's n_part
-// partials of each kind.  One workgroup.  lds: 32 doubles.
-__device__ inline void cg_beta_body(int n_part, CgCtl* ctl, const double* partials, double* lds) {
-  if (ctl->done) return;
-  double tot[2] = {0.0, 0.0};
-  for (int j = threadIdx.x; j < n_part; j += blockDim.x) {
-    tot[0] += partials[j];
-    tot[1] += partials[n_part + j];
-  }
-  dev::block_sum<2>(tot, lds);
-  if (threadIdx.x == 0) {
-    const double rz_new = tot[0];
-    const double rn = sqrt(tot[1]);
-    ctl->iter += 1;
-    ctl->r_norm = rn;
-    if (!isfinite(rz_new) || !isfinite(rn)) {
-      ctl->done = DONE_NAN;
-    } else if (rn <= ctl->tol * ctl->b_norm) {
-      ctl->done = DONE_CONVERGED;
-    } else if (ctl->iter >= ctl->max_iter) {
-      ctl->done = DONE_MAXITER;
-    } else {
-      ctl->beta = rz_new / ctl->rz;
-      ctl->rz = rz_new;
-    }
   }
 }
 
 // a += alpha p;  r -= alpha P q;  z = J r;  the workgroup's partials of r.z
-// and r.r at partials[vblock] and partials[vgrid + vblock].  lds: 32 doubles.
-__device__ inline void cg_update_body(const View& v, double* a, double* r, double* z, const double* p,
-                                      const double* q, const double* J, const CgCtl* ctl, double* partials,
+// and r.r at partials[vblock] and partials[vgrid + vblock].  STEP: alpha and
+// mu from the rescan's n_step partials of each kind (one component); else as
+// cg_alpha_body left them.  The first element's values are loaded before the
+// partials are summed.  lds: 48 doubles.
+template <bool STEP>
+__device__ inline void cg_update_body(const View& v, double* __restrict__ a, double* __restrict__ r,
+                                      double* __restrict__ z, const double* __restrict__ p,
+                                      const double* __restrict__ q, const double* __restrict__ J, CgCtl* ctl,
+                                      const double* __restrict__ step, int64_t n_step, double* __restrict__ partials,
                                       int64_t vblock, int64_t vgrid, double* lds) {
   if (ctl->done) return;
   const int64_t N = (int64_t)v.n_streams * v.n_b;
-  const double alpha = ctl->alpha, mu = ctl->mu;
+  int64_t i = vblock * blockDim.x + threadIdx.x;
+  double ji = 0.0, qi = 0.0, pi = 0.0, ai = 0.0, ri = 0.0;
+  auto load = [&]() {
+    if (i < N) {
+      ji = J[i];
+      qi = q[i];
+      pi = p[i];
+      ai = a[i];
+      ri = r[i];
+    }
+  };
+  load();
+  double alpha, mu;
+  if (STEP) {
+    double tot[3];
+    sum_rows<3>(step, n_step, tot, lds);
+    const double n_e = ctl->n_e;
+    mu = n_e > 0.0 ? tot[1] / n_e : 0.0;
+    const double pkp = tot[0] - mu * tot[2];
+    const int done = step_outcome(pkp);
+    if (done) {
+      if (vblock == 0 && threadIdx.x == 0) ctl->done = done;
+      return;
+    }
+    alpha = ctl->rz / pkp;
+  } else {
+    alpha = ctl->alpha;
+    mu = ctl->mu;
+  }
+  if (vblock == 0 && threadIdx.x == 0) {
+    ctl->rz_old = ctl->rz;
+    ctl->iter_old = ctl->iter;
+  }
   double acc[2] = {0.0, 0.0};
-  for (int64_t i = vblock * blockDim.x + threadIdx.x; i < N; i += vgrid * blockDim.x) {
-    const double ji = J[i];
-    const double qi = q[i] - ((v.rowT >= 0 && i < v.n_b && ji > 0.0) ? mu : 0.0);
-    a[i] += alpha * p[i];
-    const double ri = r[i] - alpha * qi;
-    r[i] = ri;
-    const double zi = ji * ri;
+  while (i < N) {
+    const double qv = qi - ((v.rowT >= 0 && i < v.n_b && ji > 0.0) ? mu : 0.0);
+    a[i] = ai + alpha * pi;
+    const double rv = ri - alpha * qv;
+    r[i] = rv;
+    const double zi = ji * rv;
     z[i] = zi;
-    acc[0] += ri * zi;
-    acc[1] += ri * ri;
+    acc[0] += rv * zi;
+    acc[1] += rv * rv;
+    i += vgrid * blockDim.x;
+    load();
   }
   dev::block_sum<2>(acc, lds);
   if (threadIdx.x == 0) {
@@ -102,36 +156,76 @@ __device__ inline void cg_update_body(const View& v, double* a, double* r, doubl
   }
 }
 
-// p = z + beta p (z == NULL: p unchanged) and its weighted interleaved copy
-// pw4[b] = (w_T p_T, w_q p_q, w_u p_u, 0) read by the pixel-order binning
-// (dense_t: intensity-only, pw4[b] = w_T p_T, one double per baseline).
-__device__ inline void p_update4_body(const View& v, double* p, const double* z, double* pw4, const CgCtl* ctl,
-                                      int use_beta, int dense_t, int64_t vblock, int64_t vgrid) {
-  if (ctl && ctl->done) return;
-  const double beta = use_beta ? ctl->beta : 0.0;
-  const int64_t n_b = v.n_b;
-  if (dense_t) {
-    for (int64_t b = vblock * blockDim.x + threadIdx.x; b < n_b; b += vgrid * blockDim.x) {
-      double pi = z ? z[b] + beta * p[b] : p[b];
-      if (z) p[b] = pi;
-      pw4[b] = v.w[0] * pi;
-    }
-    return;
-  }
-  for (int64_t b = vblock * blockDim.x + threadIdx.x; b < n_b; b += vgrid * blockDim.x) {
-    double w4[4] = {0.0, 0.0, 0.0, 0.0};
-    const int rows[3] = {v.rowT, v.rowQ, v.rowU};
+// Weighted interleaved copy of p, pw4[b] = (w_T p_T, w_q p_q, w_u p_u, 0), read
+// by the pixel-order binning (dense_t: intensity-only, pw4[b] = w_T p_T, one
+// double per baseline); with Z first p = z + beta p.  pre: the values of the
+// thread's first baseline, loaded already.
+struct DirectionPre {
+  double z[3], p[3];
+};
+template <bool Z>
+__device__ __forceinline__ void load_direction(const View& v, int64_t b, const double* __restrict__ p,
+                                               const double* __restrict__ z, DirectionPre& x) {
+  const int rows[3] = {v.rowT, v.rowQ, v.rowU};
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      if (rows[k] < 0) continue;
-      const int64_t i = rows[k] * n_b + b;
-      double pi = z ? z[i] + beta * p[i] : p[i];
-      if (z) p[i] = pi;
-      w4[k] = v.w[k] * pi;
-    }
+  for (int k = 0; k < 3; ++k) {
+    const bool in = b < v.n_b && rows[k] >= 0;
+    x.p[k] = in ? p[rows[k] * v.n_b + b] : 0.0;
+    x.z[k] = (Z && in) ? z[rows[k] * v.n_b + b] : 0.0;
+  }
+}
+template <bool Z>
+__device__ __forceinline__ void store_direction(const View& v, int64_t b, double beta, const DirectionPre& x,
+                                                double* __restrict__ p, double* __restrict__ pw4, int dense_t) {
+  const int rows[3] = {v.rowT, v.rowQ, v.rowU};
+  double w4[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    if (rows[k] < 0) continue;
+    const double pi = Z ? x.z[k] + beta * x.p[k] : x.p[k];
+    if (Z) p[rows[k] * v.n_b + b] = pi;
+    w4[k] = v.w[k] * pi;
+  }
+  if (dense_t) {
+    pw4[b] = w4[0];
+  } else {
     double2* o = reinterpret_cast<double2*>(pw4 + 4 * b);
     o[0] = make_double2(w4[0], w4[1]);
     o[1] = make_double2(w4[2], 0.0);
+  }
+}
+
+// Stopping test on ||r|| and beta = r'.z' / r.z from the update's n_part
+// partials of each kind, then p = z + beta p and its copy.  lds: 32 doubles.
+__device__ inline void cg_direction_body(const View& v, double* __restrict__ p, const double* __restrict__ z,
+                                         double* __restrict__ pw4, CgCtl* ctl, const double* __restrict__ partials,
+                                         int64_t n_part, int dense_t, int64_t vblock, int64_t vgrid, double* lds) {
+  if (ctl->done) return;
+  int64_t b = vblock * blockDim.x + threadIdx.x;
+  DirectionPre x;
+  load_direction<true>(v, b, p, z, x);
+  double tot[2];
+  sum_rows<2>(partials, n_part, tot, lds);
+  const double rz_new = tot[0], rn = sqrt(tot[1]);
+  const int iter = ctl->iter_old + 1;
+  const int done = (!isfinite(rz_new) || !isfinite(rn))  ? DONE_NAN
+                   : rn <= ctl->tol * ctl->b_norm        ? DONE_CONVERGED
+                   : iter >= ctl->max_iter               ? DONE_MAXITER
+                                                         : DONE_RUNNING;
+  const double beta = rz_new / ctl->rz_old;
+  if (vblock == 0 && threadIdx.x == 0) {
+    ctl->iter = iter;
+    ctl->r_norm = rn;
+    if (done)
+      ctl->done = done;
+    else
+      ctl->rz = rz_new;
+  }
+  if (done) return;
+  while (b < v.n_b) {
+    store_direction<true>(v, b, beta, x, p, pw4, dense_t);
+    b += vgrid * blockDim.x;
+    load_direction<true>(v, b, p, z, x);
   }
 }
 

@@ -28,7 +28,7 @@ struct View {
 struct CgCtl {
   double rz;       // r.z of the current residual
   double alpha;    // step of the current iteration
-  double beta;     // p update coefficient
+  double rz_old;   // r.z before the current update (kept by the update for the direction)
   double mu;       // mean of the T part of K p over T-valid baselines (null-space projection)
   double b_norm;   // ||P b||
   double r_norm;   // ||r|| of the recurrence
@@ -39,7 +39,7 @@ struct CgCtl {
   int32_t iter;
   int32_t done;    // 0 running, 1 converged, 2 breakdown, 3 non-finite, 4 max_iter
   int32_t max_iter;
-  int32_t pad;
+  int32_t iter_old;  // iterations before the current update
   uint32_t counter[4];  // arrival counters of the last-block reductions
 };
 
@@ -71,11 +71,20 @@ hipError_t launch_reduce(const View& v, const void* x, int x_f32, const uint8_t*
 hipError_t launch_cg_start(const View& v, double* b, const double* ka, const double* a0, double* a, double* r,
                            double* z, double* p, const double* J, CgCtl* ctl, double* partials, double tol,
                            int max_iter, hipStream_t st);
-// per-block partials of r.z and r.r at partials[0 .. 2 * cg_update_blocks(v))
+// per-block partials of r.z and r.r at partials[0 .. 2 * cg_update_blocks(v));
+// the step comes from the rescan's n_step partials of each kind at step
+// (step == NULL: from launch_cg_alpha)
+// Up to this many partials of each kind every workgroup of the residual update
+// sums them for itself instead of waiting for one workgroup's kernel: 24
+// partials (six hours, 360 baselines) 1462 -> 1356 us a solve, 180 (a radiometer
+// day, 166 iterations) 5034 -> 4581 us, 2700 (30 days) 14.82 -> 14.67 ms, 4050
+// (90 days of intensity) 34.79 ms either way; the reads grow with the partials
+// times the workgroups beyond.
+constexpr int64_t kStepParts = 4096;
 hipError_t launch_cg_update(const View& v, double* a, double* r, double* z, const double* p, const double* q,
-                            const double* J, CgCtl* ctl, double* partials, hipStream_t st);
+                            const double* J, CgCtl* ctl, const double* step, int64_t n_step, double* partials,
+                            hipStream_t st);
 int cg_update_blocks(const View& v);
-hipError_t launch_p_update(const View& v, double* p, const double* z, const CgCtl* ctl, hipStream_t st);
 // a_T -= mean of a_T over baselines with valid T samples (J_T > 0).
 hipError_t launch_canonicalise(const View& v, double* a, const double* J, double* partials, CgCtl* ctl,
                                hipStream_t st);

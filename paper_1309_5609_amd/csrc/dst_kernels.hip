@@ -511,7 +511,8 @@ __global__ void __launch_bounds__(kBlock) k_cg_init(View v, double* __restrict__
     ctl->max_iter = max_iter;
     ctl->iter = 0;
     ctl->alpha = 0.0;
-    ctl->beta = 0.0;
+    ctl->rz_old = tot[0];
+    ctl->iter_old = 0;
     ctl->mu = 0.0;
     if (!isfinite(tot[0]) || !isfinite(tot[1]) || !isfinite(tot[2])) {
       ctl->done = DONE_NAN;
@@ -527,21 +528,16 @@ __global__ void __launch_bounds__(kBlock) k_cg_init(View v, double* __restrict__
 }
 
 // a += alpha p;  r -= alpha P q;  z = J r;  per-block partials of r.z and r.r
-// (finished by a single-workgroup kernel).
+// (finished by the direction).  Nothing here is far from a launch's own cost:
+// see kStepParts for when the step length is taken from the rescan's partials.
+template <bool STEP>
 __global__ void __launch_bounds__(kBlock) k_cg_update(View v, double* __restrict__ a, double* __restrict__ r,
                                                       double* __restrict__ z, const double* __restrict__ p,
                                                       const double* __restrict__ q, const double* __restrict__ J,
-                                                      CgCtl* __restrict__ ctl, double* __restrict__ partials) {
-  __shared__ double lds[2 * 16];
-  cg_update_body(v, a, r, z, p, q, J, ctl, partials, blockIdx.x, gridDim.x, lds);
-}
-
-__global__ void __launch_bounds__(kBlock) k_p_update(int64_t N, double* __restrict__ p, const double* __restrict__ z,
-                                                     const CgCtl* __restrict__ ctl) {
-  if (ctl->done) return;
-  const double beta = ctl->beta;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < N; i += (int64_t)gridDim.x * blockDim.x)
-    p[i] = z[i] + beta * p[i];
+                                                      CgCtl* __restrict__ ctl, const double* __restrict__ step,
+                                                      int64_t n_step, double* __restrict__ partials) {
+  __shared__ double lds[3 * 16];
+  cg_update_body<STEP>(v, a, r, z, p, q, J, ctl, step, n_step, partials, blockIdx.x, gridDim.x, lds);
 }
 
 // Canonical T baselines: zero mean over baselines with valid T samples; the
@@ -756,14 +752,10 @@ hipError_t launch_cg_start(const View& v, double* b, const double* ka, const dou
 int cg_update_blocks(const View& v) { return (int)vec_grid(v); }
 
 hipError_t launch_cg_update(const View& v, double* a, double* r, double* z, const double* p, const double* q,
-                            const double* J, CgCtl* ctl, double* partials, hipStream_t st) {
-  hipLaunchKernelGGL(k_cg_update, dim3(vec_grid(v)), dim3(kBlock), 0, st, v, a, r, z, p, q, J, ctl, partials);
-  return hipGetLastError();
-}
-
-hipError_t launch_p_update(const View& v, double* p, const double* z, const CgCtl* ctl, hipStream_t st) {
-  const int64_t N = (int64_t)v.n_streams * v.n_b;
-  hipLaunchKernelGGL(k_p_update, dim3(vec_grid(v)), dim3(kBlock), 0, st, N, p, z, ctl);
+                            const double* J, CgCtl* ctl, const double* step, int64_t n_step, double* partials,
+                            hipStream_t st) {
+  const auto kern = step ? k_cg_update<true> : k_cg_update<false>;
+  hipLaunchKernelGGL(kern, dim3(vec_grid(v)), dim3(kBlock), 0, st, v, a, r, z, p, q, J, ctl, step, n_step, partials);
   return hipGetLastError();
 }
 

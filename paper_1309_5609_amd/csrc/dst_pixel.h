@@ -62,17 +62,18 @@ hipError_t launch_bin_pixel(const View& vc, int psi_f32, const Transpose& T, con
                             const uint8_t* valid, double* m4, const CgCtl* gate, hipStream_t st);
 hipError_t launch_unbin_cg(const View& vc, int psi_f32, const double* m4, const int32_t* nvalid, const double* p,
                            double* q, CgCtl* ctl, double* partials, hipStream_t st);
-// Single-workgroup finishes of the CG step (alpha) and of the residual update (beta).
-// alpha reads n_part partials of each kind (n_b from k_unbin_cg); when the
+// Single-workgroup finish of the CG step (alpha), where the update does not take
+// it from the partials itself: reads n_part partials of each kind (n_b from k_unbin_cg); when the
 // baseline-pixel graph has several components it projects q = K p in place
 // (p: the search direction).
 hipError_t launch_cg_alpha(int64_t n_part, CgCtl* ctl, const double* partials, const CompView& cv, double* q,
                            const double* p, hipStream_t st);
-hipError_t launch_cg_beta(int n_part, CgCtl* ctl, const double* partials, hipStream_t st);
-// p = z + beta p (z == NULL: p unchanged) and pw4 = interleaved w .* p
-// (dense_t: intensity-only run form, pw4[b] = w_T p_T)
-hipError_t launch_p_update4(const View& v, double* p, const double* z, double* pw4, const CgCtl* ctl, int use_beta,
-                            int dense_t, hipStream_t st);
+// pw4 = interleaved w .* p (dense_t: intensity-only run form, pw4[b] = w_T p_T)
+hipError_t launch_pw4(const View& v, const double* p, double* pw4, const CgCtl* gate, int dense_t, hipStream_t st);
+// Stopping test and beta from the update's n_part partials of each kind,
+// p = z + beta p and its copy pw4.
+hipError_t launch_cg_direction(const View& v, double* p, const double* z, double* pw4, CgCtl* ctl,
+                               const double* partials, int n_part, int dense_t, hipStream_t st);
 // Full-sky outputs: hits[p] and out3[p] = a4[cid[p]] - b4[cid[p]] (0 where unobserved;
 // any of hits / b4 / out3 may be NULL; b_dense: b4 holds one double per pixel, the I value).
 hipError_t launch_scatter(int64_t n_pix, const int32_t* cid, const int32_t* chits, int32_t* hits, const double* a4,

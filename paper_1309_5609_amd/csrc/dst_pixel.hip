@@ -501,16 +501,22 @@ __global__ void __launch_bounds__(1024) k_cg_alpha(int64_t n_part, CgCtl* __rest
   cg_alpha_body(n_part, ctl, partials, cv, q, p, lds, clds);
 }
 
-__global__ void __launch_bounds__(1024) k_cg_beta(int n_part, CgCtl* __restrict__ ctl,
-                                                  const double* __restrict__ partials) {
-  __shared__ double lds[2 * 16];
-  cg_beta_body(n_part, ctl, partials, lds);
+__global__ void __launch_bounds__(kBlock) k_pw4(View v, const double* __restrict__ p, double* __restrict__ pw4,
+                                                const CgCtl* __restrict__ gate, int dense_t) {
+  if (gate && gate->done) return;
+  for (int64_t b = (int64_t)blockIdx.x * kBlock + threadIdx.x; b < v.n_b; b += (int64_t)gridDim.x * kBlock) {
+    DirectionPre x;
+    load_direction<false>(v, b, p, nullptr, x);
+    store_direction<false>(v, b, 0.0, x, nullptr, pw4, dense_t);
+  }
 }
 
-__global__ void __launch_bounds__(kBlock) k_p_update4(View v, double* __restrict__ p, const double* __restrict__ z,
-                                                      double* __restrict__ pw4, const CgCtl* __restrict__ ctl,
-                                                      int use_beta, int dense_t) {
-  p_update4_body(v, p, z, pw4, ctl, use_beta, dense_t, blockIdx.x, gridDim.x);
+__global__ void __launch_bounds__(kBlock) k_cg_direction(View v, double* __restrict__ p, const double* __restrict__ z,
+                                                         double* __restrict__ pw4, CgCtl* __restrict__ ctl,
+                                                         const double* __restrict__ partials, int n_part,
+                                                         int dense_t) {
+  __shared__ double lds[2 * 16];
+  cg_direction_body(v, p, z, pw4, ctl, partials, n_part, dense_t, blockIdx.x, gridDim.x, lds);
 }
 
 unsigned grid_for(int64_t n, int64_t per_block, unsigned cap) {
@@ -751,15 +757,15 @@ hipError_t launch_cg_alpha(int64_t n_part, CgCtl* ctl, const double* partials, c
   return hipGetLastError();
 }
 
-hipError_t launch_cg_beta(int n_part, CgCtl* ctl, const double* partials, hipStream_t st) {
-  hipLaunchKernelGGL(k_cg_beta, dim3(1), dim3(1024), 0, st, n_part, ctl, partials);
+hipError_t launch_pw4(const View& v, const double* p, double* pw4, const CgCtl* gate, int dense_t, hipStream_t st) {
+  hipLaunchKernelGGL(k_pw4, dim3(grid_for(v.n_b, kBlock, 1024)), dim3(kBlock), 0, st, v, p, pw4, gate, dense_t);
   return hipGetLastError();
 }
 
-hipError_t launch_p_update4(const View& v, double* p, const double* z, double* pw4, const CgCtl* ctl, int use_beta,
-                            int dense_t, hipStream_t st) {
-  const unsigned g = grid_for(v.n_b, kBlock, 1024);
-  hipLaunchKernelGGL(k_p_update4, dim3(g), dim3(kBlock), 0, st, v, p, z, pw4, ctl, use_beta, dense_t);
+hipError_t launch_cg_direction(const View& v, double* p, const double* z, double* pw4, CgCtl* ctl,
+                               const double* partials, int n_part, int dense_t, hipStream_t st) {
+  hipLaunchKernelGGL(k_cg_direction, dim3(grid_for(v.n_b, kBlock, 1024)), dim3(kBlock), 0, st, v, p, z, pw4, ctl,
+                     partials, n_part, dense_t);
   return hipGetLastError();
 }
 

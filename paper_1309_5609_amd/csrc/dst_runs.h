@@ -141,8 +141,8 @@ hipError_t runs_build(const View& v, int psi_f32, const void* tod, int tod_f32, 
 hipError_t launch_rhs_runs(const View& vc, const Runs& W, const void* tod, int tod_f32, const double* md4,
                            const uint8_t* valid, int32_t* nvalid, double* J, double* b, hipStream_t st);
 // Lanes per pixel of the binning for `runs` runs over n_obs pixels
-// (t_only: an intensity-only problem).
-int bin_lanes_for(int64_t runs, int64_t n_obs, bool t_only);
+// (t_only: an intensity-only problem, iqu: a radiometer).
+int bin_lanes_for(int64_t runs, int64_t n_obs, bool t_only, bool iqu);
 // m = M^-1 A^T W F p (pw4 = interleaved w .* p).
 // lpp: lanes per pixel (64, 32, 16, 8 or 4; -64: 64 with the pixel pipeline; 0: 32).
 hipError_t launch_bin_runs(const View& vc, const Runs& W, const double* pw4, const double* Minv4,
@@ -152,6 +152,8 @@ hipError_t launch_bin_runs(const View& vc, const Runs& W, const double* pw4, con
 // bpw: baselines per wavefront (1, 2, 4 or 8; else 4), taken in the order
 // W.border.
 int64_t unbin_runs_parts(const View& vc, int bpw);
+// Baselines per wavefront of the rescan for n_b baselines.
+int unbin_bpw_for(int64_t n_b, bool iqu);
 hipError_t launch_unbin_runs(const View& vc, const Runs& W, const double* m4, const int32_t* nvalid, const double* p,
                              double* q, CgCtl* ctl, double* partials, int bpw, hipStream_t st);
 

@@ -1559,16 +1559,33 @@ hipError_t launch_rhs_runs(const View& vc, const Runs& W, const void* tod, int t
   return hipGetLastError();
 }
 
-int bin_lanes_for(int64_t runs, int64_t n_obs, bool t_only) {
+constexpr int64_t kFillLanes = (int64_t)1 << 18;  // 1024 lanes on each of 256 CUs
+
+int bin_lanes_for(int64_t runs, int64_t n_obs, bool t_only, bool iqu) {
   // sparse pixels (few runs each) take fewer lanes, so that most lanes are
   // not idle: lanes per pixel times runs per lane and step (8 for LPP <= 16)
   // near the mean runs per pixel; dense ones 32 lanes.  Intensity-only runs
   // (one 4-byte key each) do best with 8 pixels per wavefront even when
   // dense (measured: 365 days at N_side 512, 285 runs per pixel).
+  // Where the pixels are too few to give every CU 1024 lanes, lanes are added:
+  // the time is the chain of loads per lane then (iterations of 8369 and 19892
+  // pixels: 25.2 -> 22.9 and 38.9 -> 32.2 us; 78440 pixels stay: 37.2 us, 40.0
+  // with twice the lanes).  Not for radiometers, though their iteration would
+  // take 20.1 us for 22.2: over their 100 to 200 iterations another order of
+  // the sums moves the maps by some 1e-9, as much as their error.
   const double mean = n_obs > 0 ? (double)runs / (double)n_obs : 0.0;
-  if (mean <= 32.0) return 4;
-  if (mean <= 64.0 || t_only) return 8;
-  return 32;
+  int lanes = mean <= 32.0 ? 4 : (mean <= 64.0 || t_only) ? 8 : 32;
+  while (!iqu && lanes < 32 && n_obs * lanes < kFillLanes) lanes *= 2;
+  return lanes;
+}
+
+int unbin_bpw_for(int64_t n_b, bool iqu) {
+  // Four baselines of one stretch of sky per wavefront share its gathers' lines;
+  // with few baselines the chip is not full and the chain of loads per lane
+  // counts instead (iterations of 360 baselines: 25.0 us with four, 23.0 with
+  // two, 21.9 with one; 1440: 37.2, 33.6, 33.7; 2880: 26.8, 25.9, 26.8; but 6720: a
+  // solve in 8.74 ms with four, 8.99 with two).  Radiometers: as above.
+  return iqu ? 4 : n_b <= 1024 ? 1 : n_b <= 4096 ? 2 : 4;
 }
 
 hipError_t launch_bin_runs(const View& vc, const Runs& W, const double* pw4, const double* Minv4,
@@ -1682,27 +1699,21 @@ __global__ void __launch_bounds__(1024) k_group_alpha(GroupLaunch G) {
 }
 
 __global__ void __launch_bounds__(kBlock) k_group_update(GroupLaunch G) {
+  __shared__ double lds[3 * 16];
+  const uint32_t b = blockIdx.x;
+  const int i = group_of(G.vec_start, G.n, b);
+  const GroupProblem& P = G.prob[i];
+  const int64_t vb = b - G.vec_start[i], vg = G.vec_start[i + 1] - G.vec_start[i];
+  cg_update_body<false>(P.v, P.a, P.r, P.z, P.p, P.q, P.J, P.ctl, nullptr, 0, P.part_update, vb, vg, lds);
+}
+
+__global__ void __launch_bounds__(kBlock) k_group_direction(GroupLaunch G) {
   __shared__ double lds[2 * 16];
   const uint32_t b = blockIdx.x;
   const int i = group_of(G.vec_start, G.n, b);
   const GroupProblem& P = G.prob[i];
   const int64_t vb = b - G.vec_start[i], vg = G.vec_start[i + 1] - G.vec_start[i];
-  cg_update_body(P.v, P.a, P.r, P.z, P.p, P.q, P.J, P.ctl, P.part_update, vb, vg, lds);
-}
-
-__global__ void __launch_bounds__(1024) k_group_beta(GroupLaunch G) {
-  __shared__ double lds[2 * 16];
-  const int i = blockIdx.x;
-  const GroupProblem& P = G.prob[i];
-  cg_beta_body((int)P.vec_n, P.ctl, P.part_update, lds);
-}
-
-__global__ void __launch_bounds__(kBlock) k_group_p(GroupLaunch G) {
-  const uint32_t b = blockIdx.x;
-  const int i = group_of(G.vec_start, G.n, b);
-  const GroupProblem& P = G.prob[i];
-  const int64_t vb = b - G.vec_start[i], vg = G.vec_start[i + 1] - G.vec_start[i];
-  p_update4_body(P.v, P.p, P.z, P.pw4, P.ctl, 1, P.dense_t, vb, vg);
+  cg_direction_body(P.v, P.p, P.z, P.pw4, P.ctl, P.part_update, P.vec_n, P.dense_t, vb, vg, lds);
 }
 
 }  // namespace
@@ -1755,8 +1766,7 @@ hipError_t launch_group_phase(const GroupLaunch& G, int phase, hipStream_t st) {
       if (phase == 1) hipLaunchKernelGGL(k_group_alpha, dim3(G.n), dim3(1024), 0, st, G);
     } else {
       hipLaunchKernelGGL(k_group_update, dim3(G.vec_total), dim3(kBlock), 0, st, G);
-      hipLaunchKernelGGL(k_group_beta, dim3(G.n), dim3(1024), 0, st, G);
-      hipLaunchKernelGGL(k_group_p, dim3(G.vec_total), dim3(kBlock), 0, st, G);
+      hipLaunchKernelGGL(k_group_direction, dim3(G.vec_total), dim3(kBlock), 0, st, G);
     }
   });
   return hipGetLastError();
