@@ -119,10 +119,11 @@ int dst_version(void);
  * 32 = default, 16, or -64 for 64 with a software pipeline over pixels),
  * DST_BIN_FORM (form of the binning: 0 plain, 1 baseline values in LDS where
  * they fit, 2 pipelined gathers; by default by the problem's sizes) and
- * DST_UNBIN_BPW (baselines per wavefront in the rescan: 1, 2, 4 or 8; by
- * default by their number).  DST_RUN_SPLIT_BITS = k splits runs of consecutive samples on one
- * pixel at 2^k samples at most (runs are split anyway where a pixel id and a
- * run length would not fit one 32-bit key).  They change speed only, not
+ * DST_UNBIN_BPW (baselines per wavefront in the rescan: 1, 2, 4 or 8, or 16
+ * per workgroup with the map staged through LDS; by default by their number
+ * and the runs per pixel).  DST_RUN_SPLIT_BITS = k splits runs of consecutive
+ * samples on one pixel at 2^k samples at most (runs are split anyway where a
+ * pixel id and a run length would not fit one 32-bit key).  They change speed only, not
  * results beyond summation order. */
 int dst_create(dst_ctx** ctx, int device);
 

@@ -22,7 +22,7 @@ OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libdst.so")
 SOURCES = ["dst_kernels.hip", "dst_pixel.hip", "dst_runs.hip", "dst_multi.hip", "dst_pointing.hip", "dst_noise.hip",
            "dst_gmres.hip", "dst_comp.hip",
-           "dst_bucket.hip", "dst_forms.hip", "dst_api.hip"]
+           "dst_bucket.hip", "dst_forms.hip", "dst_stage.hip", "dst_api.hip"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950",

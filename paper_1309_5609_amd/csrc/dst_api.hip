@@ -27,6 +27,7 @@
 #include "dst_multi.h"
 #include "dst_pixel.h"
 #include "dst_runs.h"
+#include "dst_stage.h"
 
 using dst::CgCtl;
 using dst::View;
@@ -71,7 +72,7 @@ struct dst_ctx {
   int bin_form = -1;          // form of the run binning (dst_forms.h; -1 by size)
   int run_split_bits = 0;     // > 0: longest run 2^bits samples (runs split beyond; results unchanged)
   // launch shapes chosen by the autotuner, per problem shape: lanes per pixel of the binning (0: its other form),
-  // baselines per wavefront of the rescan
+  // baselines per wavefront of the rescan (0: staged)
   std::map<std::tuple<int64_t, int64_t, int, int>, std::pair<int, int>> tuned;
 };
 
@@ -409,6 +410,8 @@ int operator_map(dst_ctx* ctx, const dst_problem* prob, Setup& S, const void* to
 // ids, per-pixel blocks from it (no atomics), and the per-baseline counts and
 // Jacobi diagonal.  Every solver kernel works in compact pixel space (S.v has
 // pix = the compact ids, n_pix = observed pixels); outputs are scattered back.
+constexpr int kStageBpw = 16;  // DST_UNBIN_BPW that asks for the staged rescan
+
 struct Plan {
   Setup S;
   View full;
@@ -421,6 +424,7 @@ struct Plan {
   dst::BinRuns bruns;
   int lpp = 0;            // launch shapes of the run binning (0: default) and rescan
   int bpw = 4;
+  dst::Stage stage;       // the rescan staged through LDS
   dst::Comp C;            // components of the baseline-pixel graph (streams with a T-like row)
   int dense_t = 0;        // run form, intensity only: p and m kept as one double per baseline / pixel
   const int32_t* cid() const { return runs ? W.cid : T.cid; }
@@ -611,6 +615,25 @@ int build_bin(dst_ctx* ctx, Plan& P, hipStream_t st) {
   return DST_OK;
 }
 
+// The staged form of the rescan where it pays, in buffers of the setup that are
+// done with: the sort's keys [R] take the staged keys, the runs' records
+// (rec_bytes each) the lists (left out where these do not hold them).
+int build_stage(dst_ctx* ctx, Plan& P, size_t rec_bytes, hipStream_t st) {
+  const View& vc = P.S.v;
+  const dst::Runs& W = P.W;
+  dst::Stage& S = P.stage;
+  if (ctx->unbin_bpw ? ctx->unbin_bpw != kStageBpw || !dst::stage_can(vc, W) : !dst::stage_pays(vc, W)) return DST_OK;
+  S.blocks = dst::stage_blocks(vc);
+  const size_t words = (size_t)S.blocks * (size_t)dst::stage_cap(vc);
+  if ((words + S.blocks) * sizeof(uint32_t) > (size_t)W.R * rec_bytes) return DST_OK;
+  S.on = true;
+  S.key = W.keys[0];
+  S.list = static_cast<uint32_t*>(W.rec);
+  S.count = S.list + words;
+  HIP_TRY(dst::stage_build(vc, W, S, st));
+  return DST_OK;
+}
+
 int build_plan(dst_ctx* ctx, const dst_problem* prob, Plan& P, const void* tod, double** sd4, double** md4,
                double* b, hipStream_t st) {
   P.lpp = ctx->bin_lpp;
@@ -639,7 +662,9 @@ int plan_bin(dst_ctx* ctx, Plan& P, const CgCtl* gate, hipStream_t st) {
 
 int plan_unbin(dst_ctx* ctx, Plan& P, const double* p, double* q, CgCtl* ctl, double* partials, hipStream_t st) {
   Setup& S = P.S;
-  if (P.runs)
+  if (P.stage.on)
+    HIP_TRY(dst::launch_unbin_staged(S.v, P.W, P.stage, P.m4, S.nvalid, p, q, ctl, partials, st));
+  else if (P.runs)
     HIP_TRY(dst::launch_unbin_runs(S.v, P.W, P.m4, S.nvalid, p, q, ctl, partials, P.bpw, st));
   else
     HIP_TRY(dst::launch_unbin_cg(S.v, S.psi_f32, P.m4, S.nvalid, p, q, ctl, partials, st));
@@ -1433,13 +1458,23 @@ int autotune(dst_ctx* ctx, Plan& P, const double* p, double* scratch, hipStream_
         best_bpw = bpw;
       }
     }
+    if (P.stage.on) {
+      const float t = time_of([&] {
+        return dst::launch_unbin_staged(S.v, P.W, P.stage, P.m4, S.nvalid, p, scratch, nullptr, nullptr, st);
+      });
+      if (t < 0.f) return fail(ctx, DST_EHIP, "autotuner: a rescan launch failed");
+      if (t < tu) best_bpw = 0;
+    }
     it = ctx->tuned.emplace(key, std::make_pair(best_lpp, best_bpw)).first;
   }
   if (it->second.first != 0) {
     P.lpp = it->second.first;
     P.bin.form = dst::BIN_PLAIN;
   }
-  P.bpw = it->second.second;
+  if (it->second.second != 0) {
+    P.bpw = it->second.second;
+    P.stage.on = false;
+  }
   return DST_OK;
 }
 
@@ -1460,6 +1495,7 @@ int dst_create(dst_ctx** out, int device) {
   if (const char* e = std::getenv("DST_UNBIN_BPW")) ctx->unbin_bpw = std::atoi(e);
   if (const char* e = std::getenv("DST_BIN_LPP")) ctx->bin_lpp = std::atoi(e);
   if (const char* e = std::getenv("DST_BIN_FORM")) ctx->bin_form = std::atoi(e);
+  if (ctx->bin_form > dst::BIN_PIPE) ctx->bin_form = -1;
   if (const char* e = std::getenv("DST_RUN_SPLIT_BITS")) ctx->run_split_bits = std::atoi(e);
   DeviceGuard g(device);
   if (hipHostMalloc(reinterpret_cast<void**>(&ctx->ctl_host), sizeof(CgCtl), hipHostMallocDefault) != hipSuccess ||
@@ -1703,7 +1739,10 @@ int dst_solve(dst_ctx* ctx, const dst_problem* prob, const dst_solve_opts* opts_
   P.full = v;
   P.runs = !(opts.flags & DST_SOLVE_PER_SAMPLE);
   DST_TRY(build_plan(ctx, prob, P, prob->tod, &sd4, &md4, b, st));
-  if (P.runs) DST_TRY(build_bin(ctx, P, st));
+  if (P.runs) {
+    DST_TRY(build_bin(ctx, P, st));
+    DST_TRY(build_stage(ctx, P, dst::run_record_bytes(v.rowQ >= 0, v.iqu, prob->tod != nullptr, v.w[1] == v.w[2]), st));
+  }
   Setup& S = P.S;
   const View& vc = S.v;
   DST_TRY(ws(ctx, "cg_a", N, &a));
@@ -1737,7 +1776,9 @@ int dst_solve(dst_ctx* ctx, const dst_problem* prob, const dst_solve_opts* opts_
   // copy with beta.  The step length has a kernel of its own when the rescan's
   // partials are many or several components are projected (known on the host
   // once the setup has run: until then one is assumed).
-  const int64_t n_step = P.runs ? dst::unbin_runs_parts(vc, P.bpw) : vc.n_b;
+  const int64_t n_step = P.stage.on ? dst::staged_parts(vc)
+                         : P.runs      ? dst::unbin_runs_parts(vc, P.bpw)
+                                       : vc.n_b;
   bool own_step = n_step <= dst::kStepParts;
   auto one_iteration = [&](hipStream_t s, bool timed) -> int {
     hipEvent_t e[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};
