@@ -469,13 +469,13 @@ __global__ void __launch_bounds__(kBlock) k_compact(const uint32_t* __restrict__
   }
 }
 
-// 32 lanes per compact pixel: its runs (pixel order, time order within
+// LPP lanes per compact pixel: its runs (pixel order, time order within
 // the pixel) -> the pixel-order run arrays; hits, weight blocks, inverse,
 // validity; with TOD the sum map and binned map.  The sum of sin^2 2psi over
 // a run is its length minus the sum of cos^2 2psi.  EQ: equal q/u weights,
 // whose QU block is w h times the unit matrix (NaN when an angle is not
 // finite, which C - C tells).
-template <typename RT, bool HAS_T, bool HAS_QU, bool IQU, bool TOD, bool EQ>
+template <typename RT, bool HAS_T, bool HAS_QU, bool IQU, bool TOD, bool EQ, int LPP>
 __global__ void __launch_bounds__(kBlock) k_pixels_from_runs(
     View v, int64_t n_obs, const uint32_t* __restrict__ order, const int64_t* __restrict__ seg,
     const uint32_t* __restrict__ rperm, const void* __restrict__ rec_, const RT* __restrict__ tcs, double rcond_cut,
@@ -490,8 +490,8 @@ __global__ void __launch_bounds__(kBlock) k_pixels_from_runs(
   const uint32_t nmask = (1u << nb) - 1u;
   __shared__ unsigned long long lds[4 * 16];
   unsigned long long cnt[4] = {0, 0, 0, 0};
-  // LPP lanes per pixel (two pixels per wavefront), U runs per lane and step
-  constexpr int LPP = 32, PPW = 64 / LPP, U = 4;
+  // U runs per lane and step
+  constexpr int PPW = 64 / LPP, U = 4;
   const int lane = lane_id();
   const int grp = lane / LPP, sub = lane % LPP;
   const int64_t nw = (int64_t)gridDim.x * kWaves * PPW;
@@ -1501,19 +1501,28 @@ hipError_t runs_build(const View& v, int psi_f32, const void* tod, int tod_f32, 
   }
   // 5. per-pixel setup from the runs; pixel-order run arrays and keys
   if (W.n_obs > 0) {
-    // two pixels per wavefront; at most 16384 workgroups, each taking pixels
-    // 131072 apart (4096: setup +0.04 ms, 1024: +0.24 ms; one step per
+    // at most 16384 workgroups, each taking pixels
+    // 131072 apart with 32 lanes each (4096: setup +0.04 ms, 1024: +0.24 ms; one step per
     // workgroup, about 39000 of them: +1.0 ms)
-    const unsigned gw = grid_for(W.n_obs, 2 * kWaves, 16384);
+    // Eight lanes per pixel, four runs each at a time, up to 64 runs per pixel:
+    // solves of 2 days q/u (17 runs per pixel) 3.24 -> 2.90 ms, a batch (42)
+    // 24.57 -> 24.22 ms, 7 days masked (13) 8.74 -> 8.73 ms; denser ones keep 32
+    // (30 days, 125 runs: 13.94 ms, 13.99 with eight).  Radiometers keep 32 as
+    // well: see bin_lanes_for.
+    const int lanes = !v.iqu && W.R <= 64 * W.n_obs ? 8 : 32;
+    const unsigned gw = grid_for(W.n_obs, 64 / lanes * kWaves, 16384);
     by_float(W.f32, [&](auto rt) {
       using RT = typename decltype(rt)::type;
       by_streams(v, [&](auto T, auto Q, auto I) {
         by_bool(tod != nullptr, [&](auto D) {
           by_bool(eq, [&](auto E) {
             constexpr bool HT = decltype(T)::value, HQ = decltype(Q)::value, HI = decltype(I)::value;
-            hipLaunchKernelGGL((k_pixels_from_runs<RT, HT, HQ, HI, decltype(D)::value,
-                                                   HQ && !HI && decltype(E)::value>),
-                               dim3(gw), dim3(kBlock), 0, st, v, W.n_obs, W.order, W.seg, W.rperm, W.rec,
+            constexpr bool HD = decltype(D)::value, HE = HQ && !HI && decltype(E)::value;
+            auto kern = k_pixels_from_runs<RT, HT, HQ, HI, HD, HE, 32>;
+            if constexpr (!HI) {
+              if (lanes == 8) kern = k_pixels_from_runs<RT, HT, HQ, HI, HD, HE, 8>;
+            }
+            hipLaunchKernelGGL(kern, dim3(gw), dim3(kBlock), 0, st, v, W.n_obs, W.order, W.seg, W.rperm, W.rec,
                                static_cast<const RT*>(W.tcs), rcond_cut, W.nb, W.pkey, static_cast<RT*>(W.pcs),
                                W.pstart, hits, Minv4, valid, m4_zero, sd4, md4, counts);
           });
