@@ -1333,10 +1333,11 @@ int gmres_loop(dst_ctx* ctx, Plan& P, const View& v, const double* b, double* a,
   const int m = opts.restart > 0 ? opts.restart : 50;
   const CgCtl h0 = *ctx->ctl_host;
   const double bnorm = h0.b_norm, n_e = h0.n_e;
-  double *V, *z, *part, *gsw;
+  double *V, *z, *part, *part2, *gsw;
   DST_TRY(ws(ctx, "gm_V", (size_t)(m + 2) * N, &V));  // slot 0: T mask e; slots 1..m+1: basis
   DST_TRY(ws(ctx, "gm_z", N, &z));
   DST_TRY(ws(ctx, "gm_part", (size_t)(m + 2) * dst::gmres_dot_blocks(N), &part));
+  DST_TRY(ws(ctx, "gm_part2", (size_t)(m + 2) * dst::gmres_dot_blocks(N), &part2));
   DST_TRY(ws(ctx, "gm_state", (sizeof(dst::GmState) + sizeof(double) - 1) / sizeof(double), &gsw));
   dst::GmState* gs = reinterpret_cast<dst::GmState*>(gsw);
   dst::GmStatus* hs = ctx->gm_host;
@@ -1368,9 +1369,7 @@ int gmres_loop(dst_ctx* ctx, Plan& P, const View& v, const double* b, double* a,
         DST_TRY(plan_bin(ctx, P, gate, st));
         DST_TRY(plan_unbin(ctx, P, z, q, gate, partials, st));
         HIP_TRY(dst::launch_comp_project(cv, q, 1, 1, st));
-        HIP_TRY(dst::launch_gm_dots(gs, V, j + 2, q, N, part, gs->h1, st));  // e.w, v_0.w .. v_j.w
-        HIP_TRY(dst::launch_gm_orth(gs, 1, V, j, q, N, part, nullptr, st));
-        HIP_TRY(dst::launch_gm_orth(gs, 2, V, j, q, N, part, ds + (j & 1), st));
+        HIP_TRY(dst::launch_gm_orth(gs, V, j, q, N, part, part2, ds + (j & 1), st));
         HIP_TRY(hipEventRecord(ctx->gm_ev[j & 1], st));
         if (j > 0) {
           HIP_TRY(hipEventSynchronize(ctx->gm_ev[(j - 1) & 1]));

@@ -142,12 +142,14 @@ hipError_t launch_gm_init(GmState* s, double bnorm, double n_e, double tol, int 
 // v_j = inv_h src; z = J v_j; pw4 = the per-baseline weighted z (binning layout).
 hipError_t launch_gm_next(const View& v, GmState* s, const double* src, double* vj, const double* J, double* z,
                           double* pw4, int dense_t, hipStream_t st);
-// out[i] = V_i . w for i < k (V_i = V + i N); partial: k * gmres_dot_blocks(N) doubles.
+// out[i] = V_i . w for i < k (V_i = V + i N; out may be NULL: the partials only); partial: k * gmres_dot_blocks(N)
+// doubles.
 hipError_t launch_gm_dots(GmState* s, const double* V, int k, const double* w, int64_t N, double* partial,
                           double* out, hipStream_t st);
-// mode 1: w -= (h1_0 / n_e) e + sum_{i <= j} h1_{i+1} v_i, then partial dots v_i . w (i <= j) into h2;
-// mode 2: w -= sum_{i <= j} h2_i v_i, then ||w||^2, the Givens step j and the status.
-hipError_t launch_gm_orth(GmState* s, int mode, const double* V, int j, double* w, int64_t N, double* partial,
+// Step j from w = P K J v_j: h1 = (e.w, v_0.w .. v_j.w); w -= (h1_0 / n_e) e + sum_{i <= j} h1_{i+1} v_i and
+// h2 = (v_i.w); w -= sum_{i <= j} h2_i v_i and ||w||; the Givens step j and the status.
+// part, part2: (j + 2) * gmres_dot_blocks(N) doubles each.
+hipError_t launch_gm_orth(GmState* s, const double* V, int j, double* w, int64_t N, double* part, double* part2,
                           GmStatus* status, hipStream_t st);
 // y = R^-1 g over the cycle's k columns, then a += J sum_i y_i v_i; resumes a paused solve.
 hipError_t launch_gm_update(GmState* s, const double* J, const double* V, double* a, int64_t N, hipStream_t st);
