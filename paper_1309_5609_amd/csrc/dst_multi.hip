@@ -266,6 +266,21 @@ __device__ __forceinline__ bool lane_active(int r, int R, const MultiCtl* ctl) {
   return r < R && (ctl == nullptr || ctl->done[r] == DONE_RUNNING);
 }
 
+// One run of a window per lane, run 0 for lanes past the end j1 (no branch
+// around the loads, which stay in flight until used).
+template <typename RT>
+struct RunWindow {
+  uint32_t key;
+  CS2<RT> cs;
+  template <bool ANG>
+  __device__ __forceinline__ void load(const uint32_t* __restrict__ keys, const RT* __restrict__ angles, int64_t j,
+                                       int64_t j1) {
+    const int64_t jj = j < j1 ? j : 0;
+    key = keys[jj];
+    if (ANG) cs = reinterpret_cast<const CS2<RT>*>(angles)[jj];
+  }
+};
+
 // V consecutive realizations' values of one row (V = 1 or 2; 16-byte aligned
 // when V = 2 because Rp is even then).
 template <int V, typename GT>
@@ -467,14 +482,14 @@ __global__ void __launch_bounds__(kBlock) k_multi_unbin(View vc, int R, int Rp, 
     // the slots by shuffles; the run loop only gathers m, kStepsUnbin steps at
     // a time with no branch between the gathers (lane 63 holds no run, so a
     // step past the window reads it and gathers row 0 with zero weight)
-    for (int64_t wb = rs0; wb < rs1; wb += 63) {
+    RunWindow<RT> win, next;
+    win.template load<HAS_QU>(tkey, tcs, rs0 + lane, rs1);
+    for (int64_t wb = rs0; wb < rs1; wb += 63, win = next) {
       const int64_t jl = wb + lane;
       const bool inw = lane < 63 && jl < rs1;
-      const uint32_t w_key = inw ? tkey[jl] : 0u;
-      const int w_c = inw ? (int)(w_key >> nb) : -1;
-      const int w_n = (HAS_T && inw) ? (int)(w_key & ((1u << nb) - 1u)) + 1 : 0;
-      const CS2<RT> w_cs = (HAS_QU && inw) ? reinterpret_cast<const CS2<RT>*>(tcs)[jl] : make_cs<RT>(0.0, 0.0);
-      const RT w_C = w_cs.x, w_S = w_cs.y;
+      const int w_c = inw ? (int)(win.key >> nb) : -1;
+      const int w_n = (HAS_T && inw) ? (int)(win.key & ((1u << nb) - 1u)) + 1 : 0;
+      const RT w_C = (HAS_QU && inw) ? win.cs.x : (RT)0, w_S = (HAS_QU && inw) ? win.cs.y : (RT)0;
       const int nwin = rs1 - wb < 63 ? (int)(rs1 - wb) : 63;
       for (int k0 = 0; k0 < nwin; k0 += kStepsUnbin * slots) {  // uniform: every lane takes part in the shuffles
         int nn[kStepsUnbin];
@@ -490,7 +505,6 @@ __global__ void __launch_bounds__(kBlock) k_multi_unbin(View vc, int R, int Rp, 
           mr[u] = reinterpret_cast<const GT*>(reinterpret_cast<const char*>(mT) +
                                               (uint64_t)(uint32_t)max(cc, 0) * rowB);
         }
-        if (!any) continue;
         double t[kStepsUnbin][V], mQ[kStepsUnbin][V], mU[kStepsUnbin][V];
 #pragma unroll
         for (int u = 0; u < kStepsUnbin; ++u) {
@@ -500,6 +514,9 @@ __global__ void __launch_bounds__(kBlock) k_multi_unbin(View vc, int R, int Rp, 
             load_v<V>(mr[u] + dU, mU[u]);
           }
         }
+        // the next window, behind the first gathers of this one (16 realizations of 10 days: 0.240 -> 0.226 ms a
+        // launch; the same across the binning's pixels, 42 runs each, cost more registers than it hid: 0.374 -> 0.429)
+        if (k0 == 0) next.template load<HAS_QU>(tkey, tcs, jl + 63, rs1);
 #pragma unroll
         for (int u = 0; u < kStepsUnbin; ++u) {
           const double N = (double)nn[u], C = (double)cu[u], S = (double)su[u];
