@@ -615,9 +615,11 @@ int build_bin(dst_ctx* ctx, Plan& P, hipStream_t st) {
   return DST_OK;
 }
 
-// The staged form of the rescan where it pays, in buffers of the setup that are
-// done with: the sort's keys [R] take the staged keys, the runs' records
-// (rec_bytes each) the lists (left out where these do not hold them).
+// The staged form of the rescan where it pays.  rec_bytes > 0: in buffers of the
+// setup that are done with, the sort's keys [R] for the staged keys and the
+// runs' records (rec_bytes each) for the lists, left out where these do not
+// hold them; 0 (another problem's setup uses those next): in buffers of its
+// own, left out where there is no memory for them.
 int build_stage(dst_ctx* ctx, Plan& P, size_t rec_bytes, hipStream_t st) {
   const View& vc = P.S.v;
   const dst::Runs& W = P.W;
@@ -625,10 +627,15 @@ int build_stage(dst_ctx* ctx, Plan& P, size_t rec_bytes, hipStream_t st) {
   if (ctx->unbin_bpw ? ctx->unbin_bpw != kStageBpw || !dst::stage_can(vc, W) : !dst::stage_pays(vc, W)) return DST_OK;
   S.blocks = dst::stage_blocks(vc);
   const size_t words = (size_t)S.blocks * (size_t)dst::stage_cap(vc);
-  if ((words + S.blocks) * sizeof(uint32_t) > (size_t)W.R * rec_bytes) return DST_OK;
+  if (rec_bytes > 0) {
+    if ((words + S.blocks) * sizeof(uint32_t) > (size_t)W.R * rec_bytes) return DST_OK;
+    S.key = W.keys[0];
+    S.list = static_cast<uint32_t*>(W.rec);
+  } else if (ws(ctx, "st_key", W.R, &S.key) != DST_OK || ws(ctx, "st_list", words + S.blocks, &S.list) != DST_OK) {
+    (void)hipGetLastError();
+    return DST_OK;
+  }
   S.on = true;
-  S.key = W.keys[0];
-  S.list = static_cast<uint32_t*>(W.rec);
   S.count = S.list + words;
   HIP_TRY(dst::stage_build(vc, W, S, st));
   return DST_OK;
@@ -1048,6 +1055,7 @@ int solve_uneven(dst_ctx* ctx, const dst_problem* problems, const std::vector<in
     DST_TRY(ws(ctx, "cg_b", N, &m.b));
     DST_TRY(build_runs_plan(ctx, &pr, m.P, pr.tod, &m.sd4, &m.md4, m.b, st));
     DST_TRY(build_bin(ctx, m.P, st));
+    DST_TRY(build_stage(ctx, m.P, 0, st));
     // the closing operator of each problem: its own lanes per pixel (32 for all took 4.2 ms of an 80 ms survey batch)
     m.P.lpp = dst::bin_lanes_for(m.P.W.R, m.P.W.n_obs, m.P.dense_t, v.iqu);
     DST_TRY(ws(ctx, "cg_a", N, &m.a));
@@ -1128,6 +1136,7 @@ int solve_uneven(dst_ctx* ctx, const dst_problem* problems, const std::vector<in
     g.part_update = m.part2;
     g.cv = m.P.cv();
     g.bin = m.P.bruns;
+    g.stage = m.P.stage;
     if (g.kind != dst::GK_T) {
       if (f32 >= 0 && f32 != (int)W.f32) return fail(ctx, DST_EINVAL, "internal: mixed angle precision in a group");
       f32 = (int)W.f32;
@@ -1143,7 +1152,9 @@ int solve_uneven(dst_ctx* ctx, const dst_problem* problems, const std::vector<in
     // lanes per pixel of the kind's binning from its runs per observed pixel
     int64_t runs = 0, obs = 0;
     bool lds = true;
+    sl.staged = true;
     for (int j = 0; j < sl.count; ++j) {
+      sl.staged = sl.staged && gp[sl.first + j].stage.on;
       runs += n_runs[sl.first + j];
       obs += gp[sl.first + j].v.n_pix;
       lds = lds && M[order[sl.first + j]].P.bin.form == dst::BIN_LDS;
@@ -1164,7 +1175,8 @@ int solve_uneven(dst_ctx* ctx, const dst_problem* problems, const std::vector<in
     uint32_t* bs = ranges.data() + roff[K];
     uint32_t* us = bs + sl.count + 1;
     for (int j = 0; j < sl.count; ++j) {
-      const dst::GroupProblem& g = gp[sl.first + j];
+      dst::GroupProblem& g = gp[sl.first + j];
+      if (sl.staged) g.unbin_n = (uint32_t)dst::staged_parts(g.v);
       const uint32_t blocks = sl.form == dst::BIN_LDS    ? M[order[sl.first + j]].P.bin.blocks
                               : sl.form == dst::BIN_PIPE ? dst::bin_pipe_blocks(g.v.n_pix, sl.lpp)
                                                          : dst::group_bin_blocks(g.v.n_pix, sl.lpp);

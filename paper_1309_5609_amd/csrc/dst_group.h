@@ -31,6 +31,18 @@ struct BinRuns {
   const void* cs = nullptr;
 };
 
+// The rescan staged through LDS (dst_stage.hip): the baselines in blocks of the rescan order, each with the list of the
+// distinct pixels its runs are on.
+struct Stage {
+  bool on = false;
+  int64_t blocks = 0;
+  uint32_t* key = nullptr;    // [R] position in the block's list << nb | (length - 1)
+  uint32_t* list = nullptr;   // [blocks][stage_cap]
+  uint32_t* count = nullptr;  // [blocks] entries of the list (kStageOver: too many, keys as they were)
+};
+
+constexpr uint32_t kStageOver = 0xffffffffu;
+
 // One problem of a group, in device memory.  All arrays are the problem's
 // own (compact pixel space, packed run keys).
 struct GroupProblem {
@@ -58,6 +70,7 @@ struct GroupProblem {
   double* part_update;  // [2][vec_n]
   CompView cv;
   BinRuns bin;  // the runs for the binning forms of dst_forms.hip
+  Stage stage;  // the staged rescan, where the slice has it
 };
 
 // Problem of workgroup b: the i with start[i] <= b < start[i + 1].
@@ -85,6 +98,7 @@ struct GroupSlice {
   uint32_t bin_total = 0, unbin_total = 0;
   int lpp = 32;  // lanes per pixel of the binning (4, 8, 16 or 32)
   int bpw = 4;   // baselines per wavefront of the rescan (1, 2, 4 or 8)
+  bool staged = false;  // the rescan is the staged one
   int form = 0;  // form of the binning (dst_forms.h; 0: the plain one)
 };
 struct GroupLaunch {

@@ -23,6 +23,7 @@
 #include <type_traits>
 
 #include "dst_forms.h"
+#include "dst_stage.h"
 #include "dst_internal.h"
 #include "dst_runs.h"
 #include "dst_cg.h"
@@ -1747,6 +1748,10 @@ hipError_t launch_group_phase(const GroupLaunch& G, int phase, hipStream_t st) {
       constexpr int K = decltype(kind)::value;
       const GroupSlice& S = G.kind[K];
       if (S.count == 0) return;
+      if (phase == 1 && S.staged) {
+        (void)launch_group_unbin_staged(G, K, st);  // its launch error is reported below
+        return;
+      }
       if (phase == 1) {
         switch (S.bpw) {
           case 1: hipLaunchKernelGGL((k_group_unbin<RT, K, 1>), dim3(S.unbin_total), dim3(kBlock), 0, st, G); break;

@@ -5,22 +5,11 @@
 
 #include <cstdint>
 
+#include "dst_group.h"
 #include "dst_internal.h"
 #include "dst_runs.h"
 
 namespace dst {
-
-// The baselines in blocks of the rescan order, each with the list of the
-// distinct pixels its runs are on.
-struct Stage {
-  bool on = false;
-  int64_t blocks = 0;
-  uint32_t* key = nullptr;    // [R] position in the block's list << nb | (length - 1)
-  uint32_t* list = nullptr;   // [blocks][stage_cap]
-  uint32_t* count = nullptr;  // [blocks] entries of the list (kStageOver: too many, keys as they were)
-};
-
-constexpr uint32_t kStageOver = 0xffffffffu;
 
 // Whether the problem can be staged (all but radiometers), and whether that is worth its setup.
 inline bool stage_can(const View& vc, const Runs& W) { return !vc.iqu && W.n_obs > 0; }
@@ -33,5 +22,8 @@ hipError_t stage_build(const View& vc, const Runs& W, const Stage& S, hipStream_
 int64_t staged_parts(const View& vc);
 hipError_t launch_unbin_staged(const View& vc, const Runs& W, const Stage& S, const double* m4, const int32_t* nvalid,
                                const double* p, double* q, CgCtl* ctl, double* partials, hipStream_t st);
+
+// The rescan of a group's kind whose problems are all staged.
+hipError_t launch_group_unbin_staged(const GroupLaunch& G, int kind, hipStream_t st);
 
 }  // namespace dst

@@ -14,6 +14,9 @@
 // 90 days of intensity at N_side 512: 0.49 -> 0.30 ms a launch, 0.98 ms for the
 // lists, solve 34.9 -> 32.1 ms; 30 days T/q/u FP64 at N_side 256 (39 M runs of
 // 20 bytes): 0.205 -> 0.183 ms, lists 0.17 ms, solve 14.63 -> 14.07 ms.
+// In a group, a survey of 365 days of intensity beside eight channels: rescans
+// 3.45 -> 2.78 ms an iteration, lists 4 ms, 252.6 -> 246.4 ms; 60 days beside
+// four: 72.6 -> 71.1 ms.
 // The same for the intensity binning (64 pixels per workgroup, whose runs read
 // a baseline four times): 0.49 -> 0.41 ms a launch, and 1.6 ms for its lists
 // took that away again.
@@ -209,27 +212,30 @@ __device__ __forceinline__ void rescan_row(const uint32_t* __restrict__ key, con
   }
 }
 
+// vblock of vgrid: the workgroup's place in its problem's launch (vgrid and the
+// problem's first workgroup multiples of 8).
 template <typename RT, bool HAS_T, bool HAS_QU>
-__global__ void __launch_bounds__(kThreads, 4) k_unbin_staged(
-    View v, int64_t n_blocks, const uint32_t* __restrict__ bstart, const uint32_t* __restrict__ border,
-    const uint32_t* __restrict__ key, const uint32_t* __restrict__ list, const uint32_t* __restrict__ count, int nb,
-    const RT* __restrict__ rcs, const double* __restrict__ m4, const int32_t* __restrict__ nvalid,
-    const double* __restrict__ p, double* __restrict__ q, CgCtl* __restrict__ ctl, double* __restrict__ partials) {
-  __shared__ double lds[kLds];
-  __shared__ double red[kWaves][3];
+__device__ __forceinline__ void unbin_staged_body(double* lds, double (*red)[3], const View& v, const Stage& S,
+                                                  const uint32_t* __restrict__ bstart,
+                                                  const uint32_t* __restrict__ border, int nb,
+                                                  const RT* __restrict__ rcs, const double* __restrict__ m4,
+                                                  const int32_t* __restrict__ nvalid, const double* __restrict__ p,
+                                                  double* __restrict__ q, bool cg, double* __restrict__ partials,
+                                                  int64_t vblock, int64_t vgrid) {
   constexpr bool TONLY = HAS_T && !HAS_QU;
   constexpr int CAP = cap_of(HAS_T, HAS_QU);
-  if (ctl && ctl->done) return;
+  const int64_t n_blocks = S.blocks;
+  const uint32_t* __restrict__ key = S.key;
   const int lane = lane_id(), wave = threadIdx.x >> 6;
   const int64_t n_b = v.n_b;
   // consecutive blocks on one XCD
-  const int64_t g = (int64_t)(blockIdx.x & 7) * ((n_blocks + 7) / 8) + (blockIdx.x >> 3);
+  const int64_t g = (vblock & 7) * ((n_blocks + 7) / 8) + (vblock >> 3);
   double t[3] = {0.0, 0.0, 0.0};  // p.q, T sums of q and p
   if (g < n_blocks) {
-    const uint32_t D = count[g];
+    const uint32_t D = S.count[g];
     const bool staged = D != kStageOver;
     if (staged) {
-      const uint32_t* l = list + g * CAP;
+      const uint32_t* l = S.list + g * CAP;
       for (uint32_t i = threadIdx.x; i < D; i += kThreads) {
         if (TONLY) {
           lds[i] = m4[l[i]];
@@ -279,7 +285,7 @@ __global__ void __launch_bounds__(kThreads, 4) k_unbin_staged(
       }
     }
   }
-  if (!ctl) return;
+  if (!cg) return;
   if (lane == 0) {
 #pragma unroll
     for (int j = 0; j < 3; ++j) red[wave][j] = t[j];
@@ -290,9 +296,36 @@ __global__ void __launch_bounds__(kThreads, 4) k_unbin_staged(
     for (int j = 0; j < 3; ++j) {
       double x = 0.0;
       for (int w = 0; w < kWaves; ++w) x += red[w][j];
-      partials[j * (int64_t)gridDim.x + blockIdx.x] = x;
+      partials[j * vgrid + vblock] = x;
     }
   }
+}
+
+template <typename RT, bool HAS_T, bool HAS_QU>
+__global__ void __launch_bounds__(kThreads, 4) k_unbin_staged(
+    View v, Stage S, const uint32_t* __restrict__ bstart, const uint32_t* __restrict__ border, int nb,
+    const RT* __restrict__ rcs, const double* __restrict__ m4, const int32_t* __restrict__ nvalid,
+    const double* __restrict__ p, double* __restrict__ q, CgCtl* __restrict__ ctl, double* __restrict__ partials) {
+  __shared__ double lds[kLds];
+  __shared__ double red[kWaves][3];
+  if (ctl && ctl->done) return;
+  unbin_staged_body<RT, HAS_T, HAS_QU>(lds, red, v, S, bstart, border, nb, rcs, m4, nvalid, p, q, ctl != nullptr,
+                                       partials, blockIdx.x, gridDim.x);
+}
+
+template <typename RT, int KIND>
+__global__ void __launch_bounds__(kThreads, 4) k_group_unbin_staged(GroupLaunch G) {
+  constexpr bool HT = KIND != GK_QU, HQ = KIND != GK_T;
+  __shared__ double lds[kLds];
+  __shared__ double red[kWaves][3];
+  const GroupSlice& L = G.kind[KIND];
+  const uint32_t b = blockIdx.x;
+  const int j = group_of(L.unbin_start, L.count, b);
+  const GroupProblem& P = G.prob[L.first + j];
+  if (P.ctl->done) return;
+  unbin_staged_body<RT, HT, HQ>(lds, red, P.v, P.stage, P.bstart, P.border, P.nb, static_cast<const RT*>(P.tcs), P.m4,
+                                P.nvalid, P.p, P.q, true, P.part_unbin, b - L.unbin_start[j],
+                                L.unbin_start[j + 1] - L.unbin_start[j]);
 }
 
 }  // namespace
@@ -327,9 +360,8 @@ hipError_t launch_unbin_staged(const View& vc, const Runs& W, const Stage& S, co
   auto launch = [&](auto rt, auto T, auto Q) {
     using RT = decltype(rt);
     hipLaunchKernelGGL((k_unbin_staged<RT, decltype(T)::value, decltype(Q)::value>),
-                       dim3((unsigned)staged_parts(vc)), dim3(kThreads), 0, st, vc, S.blocks, W.bstart,
-                       W.border, S.key, S.list, S.count, W.nb, static_cast<const RT*>(W.tcs), m4, nvalid, p, q, ctl,
-                       partials);
+                       dim3((unsigned)staged_parts(vc)), dim3(kThreads), 0, st, vc, S, W.bstart, W.border, W.nb,
+                       static_cast<const RT*>(W.tcs), m4, nvalid, p, q, ctl, partials);
   };
   auto by_streams = [&](auto rt) {
     if (vc.rowT >= 0 && vc.rowQ >= 0)
@@ -343,6 +375,24 @@ hipError_t launch_unbin_staged(const View& vc, const Runs& W, const Stage& S, co
     by_streams(0.0f);
   else
     by_streams(0.0);
+  return hipGetLastError();
+}
+
+hipError_t launch_group_unbin_staged(const GroupLaunch& G, int kind, hipStream_t st) {
+  const dim3 g(G.kind[kind].unbin_total);
+  auto by_kind = [&](auto rt) {
+    using RT = decltype(rt);
+    if (kind == GK_T)
+      hipLaunchKernelGGL((k_group_unbin_staged<RT, GK_T>), g, dim3(kThreads), 0, st, G);
+    else if (kind == GK_QU)
+      hipLaunchKernelGGL((k_group_unbin_staged<RT, GK_QU>), g, dim3(kThreads), 0, st, G);
+    else
+      hipLaunchKernelGGL((k_group_unbin_staged<RT, GK_TQU>), g, dim3(kThreads), 0, st, G);
+  };
+  if (G.f32)
+    by_kind(0.0f);
+  else
+    by_kind(0.0);
   return hipGetLastError();
 }
 

@@ -64,3 +64,23 @@ def test_staged_against_plain(monkeypatch, streams, dtype, n, L, nside):
     for k in ("baselines", "destriped_map", "binned_map"):
         # three operator applications of sums of up to n terms: n eps = 3e-11
         assert rel(res[0][k].cpu().numpy(), res[1][k].cpu().numpy()) < 1e-10, k
+
+
+def test_staged_group(monkeypatch):
+    """Channels advanced together, their rescans staged; several stream sets, one of them (a radiometer) never staged."""
+    from paper_1309_5609_amd import dst
+    ps = [toy(n_samples=9100, L=250, nside=16), toy(n_samples=30001, L=11, nside=16), toy(n_samples=700, L=7),
+          toy(streams="T"), toy(streams="T", n_samples=120000, L=1500, nside=128), toy(streams="QU"),
+          toy(streams="IQU", n_samples=20000, L=400)]
+    c = context(monkeypatch, True)
+    dps = [dst.to_device(p) for p in ps]
+    _, res = dst.dst_solve_batched(c, dps, tol=1e-13, max_iter=3000)
+    _, eager = dst.dst_solve_batched(c, dps, tol=1e-13, max_iter=3000, flags=dst.DST_SOLVE_NO_GRAPH)
+    for p, out, one in zip(ps, res, eager):
+        ref = O.solve(*args(p), tol=1e-13, max_iter=3000)
+        assert abs(out["iterations"] - ref.iterations) <= 1 + ref.iterations // 50
+        assert rel(out["baselines"].cpu().numpy(), ref.baselines) < 1e-9
+        ok = {"QU": ref.valid_QU}.get(p.streams, ref.valid_T)
+        assert rel(out["destriped_map"].cpu().numpy()[ok], ref.destriped_map[ok]) < 1e-9
+        assert np.array_equal(out["baselines"].cpu().numpy(), one["baselines"].cpu().numpy())
+    c.close()
