@@ -286,10 +286,11 @@ def noise_form(ctx, n: int, segment: int = 1 << 24, reps: int = 3) -> dict:
     torch.cuda.synchronize()
     dt = (time.perf_counter() - t) / reps
     m = segment.bit_length() - 1
-    passes = -(-m // 8)
-    # per complex value (two samples): white write 16 B; each FFT pass reads and
-    # writes 16 B, forward and inverse; the unpack reads 16 B and writes 2 x 8 B
-    per_sample = (16 + 2 * passes * 32 + 16 + 16) / 2
+    columns = 0 if m <= 12 else 1 if m <= 22 else 2
+    passes = columns + 1
+    # per complex value (two samples): the first pass draws its values and writes 16 B, the last writes 2 x 8 B, the
+    # passes between them read and write 16 B each (the middle one both transforms of 4,096 values and the gain)
+    per_sample = (16 if columns == 0 else 16 + 32 * (2 * columns - 1) + 32) / 2
     gbs = 3 * n * per_sample / dt / 1e9
     del out
     torch.cuda.empty_cache()
@@ -297,8 +298,8 @@ def noise_form(ctx, n: int, segment: int = 1 << 24, reps: int = 3) -> dict:
             "fft_passes_per_transform": passes, "model_bytes_per_sample": per_sample, "achieved_GBs": gbs,
             "frac": gbs / HBM_PEAK_GBS,
             "method": "Philox4x64-10 + Box-Muller white noise, filtered per segment pair by one complex FFT: "
-                      f"{passes} Stockham passes of radix <= 256 each way, computed in LDS; gain applied as the "
-                      "inverse transform reads the spectrum"}
+                      f"{columns} in-place passes over columns each way around one over blocks of 4,096 values with the "
+                      "gain, in LDS; the first draws the white noise, the last adds into the timeline"}
 
 
 def batched_form(ctx, p, dp, n_real: int, tol: float, steps: int, warmup: int, plain_value: float) -> dict:
@@ -524,8 +525,8 @@ def main() -> int:
     k_ms = {k: float(np.mean([r[f"t_{k}_ms"] for r in runs])) for k in ("bin", "apply", "unbin", "update")}
     dom = max(("bin", "unbin"), key=lambda k: k_ms[k])
     rt = "float" if args.workload == 2 else "double"
-    dom_kernel = {"bin": f"k_bin_runs<{rt}, true, true, false, 32, true>",
-                  "unbin": f"k_unbin_runs<{rt}, true, true, false, true, 4, true>"}[dom]
+    dom_kernel = {"bin": f"k_bin_runs<{rt}, true, true, false, 32>",
+                  "unbin": f"k_unbin_staged<{rt}, true, true>"}[dom]
     traffic = measured_traffic(dom_kernel)
     launch_s = k_ms[dom] * 1e-3
     achieved = mb[dom] / launch_s / 1e9
