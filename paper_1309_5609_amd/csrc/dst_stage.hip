@@ -10,7 +10,7 @@
 // into LDS, and the runs, whose keys hold positions in the list, are gathered
 // from there (64 random 8-byte reads: 8 to 12 cycles).  Half a CU's LDS per
 // workgroup, so that one copies while another streams; a block whose list does
-// not fit (2 % of them in both cases below) reads its values from memory.
+// not fit (fewer than one in twenty below) reads its values from memory.
 // 90 days of intensity at N_side 512: 0.49 -> 0.30 ms a launch, 0.98 ms for the
 // lists, solve 34.9 -> 32.1 ms; 30 days T/q/u FP64 at N_side 256 (39 M runs of
 // 20 bytes): 0.205 -> 0.183 ms, lists 0.17 ms, solve 14.63 -> 14.07 ms.
