@@ -59,7 +59,8 @@ int multi_padded(int R);
 hipError_t launch_run_positions(const Runs& W, uint32_t* ipos, hipStream_t st);
 
 // Timelines of up to kTodBatch realizations handled by one setup pass; their
-// per-run data sums share one record of kRunRec doubles (one 128-byte line).
+// per-run data sums share one record of kRunRec doubles (one 128-byte line),
+// fewer in a pass of one or two.
 constexpr int kTodBatch = 5;
 constexpr int kRunRec = 16;
 static_assert(3 * kTodBatch <= kRunRec, "a pass's run sums must fit one record");
@@ -69,7 +70,7 @@ struct TodSet {
 
 // Realizations ri0 .. ri0 + nr - 1 (nr <= kTodBatch, same tod dtype): per-run
 // sums of the weighted data at each run's pixel-order position, one record of
-// kRunRec doubles per run (one 128-byte line: realization i at [3 i .. 3 i + 2]
+// up to kRunRec doubles per run (realization i at [3 i .. 3 i + 2]
 // = w_T d_T, rotated Q, rotated U), and per-baseline sums w_k d_k over valid
 // samples into braw ([n_b][n_streams][Rp]).  prs holds kRunRec R doubles.
 hipError_t launch_multi_tod(const View& vc, int psi_f32, const TodSet& tods, int nr, int tod_f32, const Runs& W,

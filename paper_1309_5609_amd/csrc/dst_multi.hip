@@ -46,7 +46,7 @@ __global__ void __launch_bounds__(kBlock) k_run_positions(int64_t n_obs, const u
 // One wavefront per baseline; one lane per run; NR realizations per pass
 // (their timelines share the angle loads and the trigonometry).  Per run and
 // realization: w_T sum d_T and the rotated, weighted q/u sums, stored in the
-// run's record (one 128-byte line holding every realization of the pass) at
+// run's record (one 128-byte line or less holding every realization of the pass) at
 // its pixel-order position, so each scattered store writes a whole line; per
 // baseline: w_k sum d_k over valid samples (the data part of b = F^T Z d).
 // When the samples of 64 consecutive runs fit kStageM (half that with FP64
@@ -54,6 +54,12 @@ __global__ void __launch_bounds__(kBlock) k_run_positions(int64_t n_obs, const u
 // copies them (angles and timelines) into LDS with coalesced loads and the
 // lanes read their runs from there.
 constexpr int kStageM = 256;
+// Doubles per run's record in a pass of NR realizations: a pass of one or two
+// (the remainder of a batch) packs four or two records to the line, and so
+// writes and reads a quarter or half of the lines (the last one of 16
+// realizations of 10 days: 1.05 -> 0.64 ms here and 0.39 -> 0.14 ms in the
+// per-pixel sums).
+constexpr int rec_doubles(int nr) { return nr == 1 ? 4 : nr == 2 ? 8 : kRunRec; }
 
 template <typename PT, typename TT, bool HAS_T, bool HAS_QU, int NR>
 __global__ void __launch_bounds__(kBlock) k_multi_tod(View v, TodSet tods, const uint32_t* __restrict__ bstart,
@@ -158,18 +164,19 @@ __global__ void __launch_bounds__(kBlock) k_multi_tod(View v, TodSet tods, const
     if (!has) continue;
     const bool vT = HAS_T && (f & 1), vQ = HAS_QU && (f & 2);
     const int64_t pos = ipos[j];
-    double rec[kRunRec];
+    constexpr int REC = rec_doubles(NR);
+    double rec[REC];
 #pragma unroll
-    for (int e = 0; e < kRunRec; ++e) rec[e] = 0.0;
+    for (int e = 0; e < REC; ++e) rec[e] = 0.0;
 #pragma unroll
     for (int i = 0; i < NR; ++i) {
       rec[3 * i] = vT ? v.w[0] * dT[i] : 0.0;
       rec[3 * i + 1] = vQ ? dQ[i] : 0.0;
       rec[3 * i + 2] = vQ ? dU[i] : 0.0;
     }
-    double2* o = reinterpret_cast<double2*>(prs + (int64_t)kRunRec * pos);
+    double2* o = reinterpret_cast<double2*>(prs + (int64_t)REC * pos);
 #pragma unroll
-    for (int e = 0; e < kRunRec / 2; ++e) o[e] = make_double2(rec[2 * e], rec[2 * e + 1]);
+    for (int e = 0; e < REC / 2; ++e) o[e] = make_double2(rec[2 * e], rec[2 * e + 1]);
 #pragma unroll
     for (int i = 0; i < NR; ++i) {
       if (vT) acc[3 * i] += dT[i];
@@ -216,7 +223,7 @@ __global__ void __launch_bounds__(kBlock) k_multi_pixsum(int64_t n_obs, View vc,
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
         const int64_t j = jb + 64 * u;
-        const double2* xr = reinterpret_cast<const double2*>(prs + (int64_t)kRunRec * j);
+        const double2* xr = reinterpret_cast<const double2*>(prs + (int64_t)rec_doubles(NR) * j);
 #pragma unroll
         for (int e = 0; e < ND; ++e) x[u][e] = j < j1 ? xr[e] : make_double2(0.0, 0.0);
       }
