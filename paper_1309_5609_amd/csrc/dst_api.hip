@@ -14,7 +14,6 @@
 #include <string>
 #include <map>
 #include <tuple>
-#include <unordered_map>
 #include <unordered_set>
 #include <vector>
 
@@ -28,20 +27,26 @@
 #include "dst_pixel.h"
 #include "dst_runs.h"
 #include "dst_stage.h"
+#include "dst_workspace.h"
 
 using dst::CgCtl;
 using dst::View;
 
 constexpr int kMaxGroup = 64;  // problems advanced together by one group of launches
 
+namespace {
+bool device_alloc(void** ptr, size_t bytes) {
+  if (hipMalloc(ptr, bytes) == hipSuccess) return true;
+  (void)hipGetLastError();
+  return false;
+}
+void device_free(void* ptr) { (void)hipFree(ptr); }
+}  // namespace
+
 struct dst_ctx {
   int device = 0;
   std::string err;
-  struct Buf {
-    void* ptr = nullptr;
-    size_t bytes = 0;
-  };
-  std::unordered_map<std::string, Buf> ws;
+  dst::Workspace ws{device_alloc, device_free};
   std::string ws_prefix;      // prepended to slot names (one namespace per problem of a group)
   std::unordered_set<std::string> ws_shared;  // slots that stay unprefixed (setup-only arrays)
   CgCtl* ctl_host = nullptr;  // pinned mirror of the device CG scalars
@@ -114,34 +119,27 @@ int fail(dst_ctx* ctx, int code, const char* fmt, ...) {
     if (rc_ != DST_OK) return rc_; \
   } while (0)
 
-// Device workspace slot `name` (inside the context's current slot prefix),
-// grown to at least `bytes`.
+// Name of workspace slot `name` inside the context's current slot prefix.
+std::string ws_name(const dst_ctx* ctx, const char* name) {
+  return (ctx->ws_prefix.empty() || ctx->ws_shared.count(name)) ? std::string(name) : ctx->ws_prefix + name;
+}
+
+// Device workspace slot `name`, grown to at least `bytes`.
 int ws_get(dst_ctx* ctx, const char* name, size_t bytes, void** out) {
-  if (bytes == 0) bytes = 256;
-  auto& b = ctx->ws[(ctx->ws_prefix.empty() || ctx->ws_shared.count(name)) ? std::string(name)
-                                                                           : ctx->ws_prefix + name];
-  if (b.bytes < bytes) {
-    if (b.ptr) (void)hipFree(b.ptr);
-    b.ptr = nullptr;
-    b.bytes = 0;
-    size_t want = (bytes + 255) & ~(size_t)255;
-    if (hipMalloc(&b.ptr, want) != hipSuccess) {
-      (void)hipGetLastError();
-      b.ptr = nullptr;
-      return fail(ctx, DST_ENOMEM, "cannot allocate %zu bytes of workspace '%s'", want, name);
-    }
-    b.bytes = want;
-  }
-  *out = b.ptr;
+  const size_t want = bytes == 0 ? 256 : (bytes + 255) & ~(size_t)255;
+  *out = ctx->ws.get(ws_name(ctx, name), want);
+  if (!*out) return fail(ctx, DST_ENOMEM, "cannot allocate %zu bytes of workspace '%s'", want, name);
   return DST_OK;
 }
 
-// Frees slot `name` of the current prefix (no-op when absent).
-void ws_release(dst_ctx* ctx, const char* name) {
-  auto it = ctx->ws.find(ctx->ws_prefix + name);
-  if (it == ctx->ws.end()) return;
-  if (it->second.ptr) (void)hipFree(it->second.ptr);
-  ctx->ws.erase(it);
+// Start of a call's work on `st`.
+void ws_begin(dst_ctx* ctx, hipStream_t st) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &cap) != hipSuccess) {
+    (void)hipGetLastError();
+    cap = hipStreamCaptureStatusNone;
+  }
+  ctx->ws.begin(cap != hipStreamCaptureStatusNone);
 }
 
 template <typename T>
@@ -308,8 +306,6 @@ int bucket_pass(dst_ctx* ctx, const dst_problem* prob, const View& v, const void
   const dst::BucketBytes need = dst::bucket_bytes(v, tod || base);
   DST_TRY(ws_get(ctx, "bk_acc_hits", need.acc_hits, reinterpret_cast<void**>(&W.acc_hits)));
   DST_TRY(ws_get(ctx, "bk_acc", need.acc, reinterpret_cast<void**>(&W.acc)));
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(st, &cap) != hipSuccess) (void)hipGetLastError();
   struct Part {
     const char* name;
     size_t per;
@@ -318,8 +314,8 @@ int bucket_pass(dst_ctx* ctx, const dst_problem* prob, const View& v, const void
   W.n_chunks = need.best_chunks;
   for (Part& p : parts) {
     if (p.per == 0) continue;
-    if (cap != hipStreamCaptureStatusNone) {
-      const int64_t held = (int64_t)(ctx->ws[ctx->ws_prefix + p.name].bytes / p.per);
+    if (ctx->ws.captured()) {
+      const int64_t held = (int64_t)(ctx->ws.held(p.name) / p.per);
       W.n_chunks = std::max<int64_t>(1, std::min(W.n_chunks, held));
     }
     // at least kBucketReserve bytes, so that a later call on a longer timeline can run in pieces without growing
@@ -1542,8 +1538,7 @@ int dst_destroy(dst_ctx* ctx) {
   if (!ctx) return DST_OK;
   DeviceGuard g(ctx->device);
   (void)hipDeviceSynchronize();
-  for (auto& kv : ctx->ws)
-    if (kv.second.ptr) (void)hipFree(kv.second.ptr);
+  ctx->ws.clear();
   if (ctx->ctl_host) (void)hipHostFree(ctx->ctl_host);
   if (ctx->err_host) (void)hipHostFree(ctx->err_host);
   if (ctx->err_dev) (void)hipFree(ctx->err_dev);
@@ -1576,6 +1571,7 @@ int dst_pixel_setup(dst_ctx* ctx, const dst_problem* prob, int32_t* hits_out, do
   ctx->err.clear();
   DeviceGuard g(ctx->device);
   hipStream_t st = static_cast<hipStream_t>(stream);
+  ws_begin(ctx, st);
   dst::BucketOut o;
   o.hits = hits_out;
   o.blocks = blocks_out;
@@ -1598,6 +1594,7 @@ int dst_bin(dst_ctx* ctx, const dst_problem* prob, const double* baselines, uint
   ctx->err.clear();
   DeviceGuard g(ctx->device);
   hipStream_t st = static_cast<hipStream_t>(stream);
+  ws_begin(ctx, st);
   dst::BucketOut o;
   o.hits = hits_out;
   ((flags & DST_BIN_MAP) ? o.map3 : o.sum3) = map_out;
@@ -1623,6 +1620,7 @@ int dst_bin_noalloc(dst_ctx* ctx, const dst_problem* prob, const double* baselin
   ctx->err.clear();
   DeviceGuard g(ctx->device);
   hipStream_t st = static_cast<hipStream_t>(stream);
+  ws_begin(ctx, st);
   Setup S;
   S.v = v;
   double* s4 = nullptr;
@@ -1639,6 +1637,7 @@ int dst_unbin(dst_ctx* ctx, const dst_problem* prob, const double* map, double* 
   ctx->err.clear();
   DeviceGuard g(ctx->device);
   hipStream_t st = static_cast<hipStream_t>(stream);
+  ws_begin(ctx, st);
   HIP_TRY(dst::launch_scan(v, prob->psi_dtype == DST_F32, map, tod_out, ctx->err_dev, st));
   return issued(ctx);
 }
@@ -1652,6 +1651,7 @@ int dst_baseline_reduce(dst_ctx* ctx, const dst_problem* prob, const void* x, do
   ctx->err.clear();
   DeviceGuard g(ctx->device);
   hipStream_t st = static_cast<hipStream_t>(stream);
+  ws_begin(ctx, st);
   Setup S;
   S.v = v;
   dst::BucketOut o;
@@ -1673,6 +1673,7 @@ int dst_residual(dst_ctx* ctx, const dst_problem* prob, const double* a, double*
   ctx->err.clear();
   DeviceGuard g(ctx->device);
   hipStream_t st = static_cast<hipStream_t>(stream);
+  ws_begin(ctx, st);
   Setup S;
   S.v = v;
   double* m4 = nullptr;
@@ -1696,6 +1697,7 @@ int dst_apply_operator(dst_ctx* ctx, const dst_problem* prob, const double* vin,
   ctx->err.clear();
   DeviceGuard g(ctx->device);
   hipStream_t st = static_cast<hipStream_t>(stream);
+  ws_begin(ctx, st);
   Plan P;
   P.full = v;
   DST_TRY(build_plan(ctx, prob, P, nullptr, nullptr, nullptr, nullptr, st));
@@ -1727,6 +1729,7 @@ int dst_solve(dst_ctx* ctx, const dst_problem* prob, const dst_solve_opts* opts_
   ctx->err.clear();
   DeviceGuard g(ctx->device);
   hipStream_t st = static_cast<hipStream_t>(stream);
+  ws_begin(ctx, st);
 
   hipEvent_t ev[4];
   for (auto& e : ev) HIP_TRY(hipEventCreate(&e));
@@ -1974,6 +1977,7 @@ int dst_solve_batched(dst_ctx* ctx, int32_t n_problems, const dst_problem* probl
   ctx->err.clear();
   DeviceGuard g(ctx->device);
   hipStream_t st = static_cast<hipStream_t>(stream);
+  ws_begin(ctx, st);
   // groups of problems that share the operator, in order of first appearance
   std::vector<std::vector<int>> groups;
   for (int i = 0; i < n_problems; ++i) {
@@ -2062,6 +2066,7 @@ int dst_pointing_expand(dst_ctx* ctx, const dst_scan* scan, int64_t nside, int64
   ctx->err.clear();
   DeviceGuard g(ctx->device);
   hipStream_t st = static_cast<hipStream_t>(stream);
+  ws_begin(ctx, st);
   std::vector<double> tab;
   dst::scan_period_table(s, n_per, tab);
   double* dtab = nullptr;
@@ -2089,6 +2094,7 @@ int dst_noise_generate(dst_ctx* ctx, uint64_t seed, uint64_t stream_id, int64_t 
   ctx->err.clear();
   DeviceGuard g(ctx->device);
   hipStream_t st = static_cast<hipStream_t>(stream);
+  ws_begin(ctx, st);
   double2* buf = nullptr;
   DST_TRY(ws(ctx, "noise_buf", (size_t)dst::noise_buffer_count(segment), &buf));
   double2* tw = nullptr;

@@ -1,0 +1,82 @@
+// Named device buffers of a context: grown on demand, kept from call to call.
+// Host code only (the allocator is the caller's).
+//
+// A call made while its stream is captured leaves the addresses it was given in
+// the caller's graph, and a replay writes there whenever it comes.  Such a
+// buffer is never freed or moved before the context ends: when a later call
+// needs more, it gets another one.
+#pragma once
+
+#include <cstddef>
+#include <string>
+#include <unordered_map>
+#include <vector>
+
+namespace dst {
+
+class Workspace {
+ public:
+  using Alloc = bool (*)(void** ptr, size_t bytes);
+  using Free = void (*)(void* ptr);
+
+  Workspace(Alloc alloc, Free release) : alloc_(alloc), free_(release) {}
+  Workspace(const Workspace&) = delete;
+  Workspace& operator=(const Workspace&) = delete;
+
+  // Start of a call; captured: what it gets ends up in a graph.
+  void begin(bool captured) { captured_ = captured; }
+  bool captured() const { return captured_; }
+
+  // Buffer `name` of at least `bytes`; nullptr, with nothing held under the
+  // name, when it cannot be had (a buffer in a graph stays).
+  void* get(const std::string& name, size_t bytes) {
+    Buf& b = bufs_[name];
+    if (b.bytes < bytes) {
+      void* p = nullptr;
+      if (captured_ || b.in_graph) {
+        if (!alloc_(&p, bytes)) return nullptr;
+        if (b.ptr) retired_.push_back(b.ptr);
+      } else {
+        drop(b);  // first, so that both need not fit
+        if (!alloc_(&p, bytes)) return nullptr;
+      }
+      b = Buf{p, bytes, false};
+    }
+    b.in_graph |= captured_;
+    return b.ptr;
+  }
+
+  // Bytes held under `name`.
+  size_t held(const std::string& name) const {
+    const auto it = bufs_.find(name);
+    return it == bufs_.end() ? 0 : it->second.bytes;
+  }
+
+  // End of the context: frees everything.
+  void clear() {
+    for (auto& kv : bufs_)
+      if (kv.second.ptr) free_(kv.second.ptr);
+    for (void* p : retired_) free_(p);
+    bufs_.clear();
+    retired_.clear();
+  }
+
+ private:
+  struct Buf {
+    void* ptr = nullptr;
+    size_t bytes = 0;
+    bool in_graph = false;
+  };
+  void drop(Buf& b) {
+    if (b.ptr) free_(b.ptr);
+    b = Buf{};
+  }
+
+  Alloc alloc_;
+  Free free_;
+  bool captured_ = false;
+  std::unordered_map<std::string, Buf> bufs_;
+  std::vector<void*> retired_;  // outgrown buffers that a graph holds
+};
+
+}  // namespace dst
