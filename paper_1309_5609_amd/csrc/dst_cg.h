@@ -17,11 +17,12 @@ namespace dst {
 
 // Workgroups of a grid that finish a reduction for themselves: every one of
 // them reads all partials of the kernel before it, in the same order, so all
-// hold the same bits and no single-workgroup kernel stands between.  What they
-// write for the next kernels (workgroup 0) is not what the others of the same
-// launch read: rz and iter are kept in rz_old and iter_old by the update for
-// the direction, and a `done` seen early stops a workgroup that would have
-// stopped on the same sums.
+// hold the same bits and no single-workgroup kernel stands between.  No field of
+// CgCtl is both read and written in such a launch, since a workgroup (or one
+// wavefront of it, which would leave the others without its share of a sum) may
+// start when workgroup 0 has written already: the update keeps rz, iter and the
+// stop for the direction in rz_old, iter_old and stop, and only the direction
+// sets rz, iter and done, which it does not read.
 //
 // Sums of N rows of n_part partials, valid in every thread, in one order
 // whatever the workgroup's size: partial j belongs to slot j mod 1024, the 64
@@ -101,7 +102,12 @@ __device__ inline void cg_update_body(const View& v, double* __restrict__ a, dou
                                       const double* __restrict__ q, const double* __restrict__ J, CgCtl* ctl,
                                       const double* __restrict__ step, int64_t n_step, double* __restrict__ partials,
                                       int64_t vblock, int64_t vgrid, double* lds) {
-  if (ctl->done) return;
+  const bool first = vblock == 0 && threadIdx.x == 0;
+  const int stopped = ctl->done;
+  if (stopped) {
+    if (first) ctl->stop = stopped;
+    return;
+  }
   const int64_t N = (int64_t)v.n_streams * v.n_b;
   int64_t i = vblock * blockDim.x + threadIdx.x;
   double ji = 0.0, qi = 0.0, pi = 0.0, ai = 0.0, ri = 0.0;
@@ -122,9 +128,9 @@ __device__ inline void cg_update_body(const View& v, double* __restrict__ a, dou
     const double n_e = ctl->n_e;
     mu = n_e > 0.0 ? tot[1] / n_e : 0.0;
     const double pkp = tot[0] - mu * tot[2];
-    const int done = step_outcome(pkp);
-    if (done) {
-      if (vblock == 0 && threadIdx.x == 0) ctl->done = done;
+    const int outcome = step_outcome(pkp);
+    if (outcome) {
+      if (first) ctl->stop = outcome;
       return;
     }
     alpha = ctl->rz / pkp;
@@ -132,9 +138,10 @@ __device__ inline void cg_update_body(const View& v, double* __restrict__ a, dou
     alpha = ctl->alpha;
     mu = ctl->mu;
   }
-  if (vblock == 0 && threadIdx.x == 0) {
+  if (first) {
     ctl->rz_old = ctl->rz;
     ctl->iter_old = ctl->iter;
+    ctl->stop = DONE_RUNNING;
   }
   double acc[2] = {0.0, 0.0};
   while (i < N) {
@@ -200,7 +207,12 @@ __device__ __forceinline__ void store_direction(const View& v, int64_t b, double
 __device__ inline void cg_direction_body(const View& v, double* __restrict__ p, const double* __restrict__ z,
                                          double* __restrict__ pw4, CgCtl* ctl, const double* __restrict__ partials,
                                          int64_t n_part, int dense_t, int64_t vblock, int64_t vgrid, double* lds) {
-  if (ctl->done) return;
+  const bool first = vblock == 0 && threadIdx.x == 0;
+  const int stopped = ctl->stop;
+  if (stopped) {
+    if (first) ctl->done = stopped;
+    return;
+  }
   int64_t b = vblock * blockDim.x + threadIdx.x;
   DirectionPre x;
   load_direction<true>(v, b, p, z, x);
@@ -213,7 +225,7 @@ __device__ inline void cg_direction_body(const View& v, double* __restrict__ p, 
                    : iter >= ctl->max_iter               ? DONE_MAXITER
                                                          : DONE_RUNNING;
   const double beta = rz_new / ctl->rz_old;
-  if (vblock == 0 && threadIdx.x == 0) {
+  if (first) {
     ctl->iter = iter;
     ctl->r_norm = rn;
     if (done)

@@ -40,6 +40,8 @@ struct CgCtl {
   int32_t done;    // 0 running, 1 converged, 2 breakdown, 3 non-finite, 4 max_iter
   int32_t max_iter;
   int32_t iter_old;  // iterations before the current update
+  int32_t stop;      // done as the update leaves it for the direction
+  int32_t pad;
   uint32_t counter[4];  // arrival counters of the last-block reductions
 };
 
