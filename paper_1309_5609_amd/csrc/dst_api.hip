@@ -254,13 +254,18 @@ int setup_pixels(dst_ctx* ctx, const dst_problem* prob, Setup& S, double* blocks
   return DST_OK;
 }
 
-int run_setup(dst_ctx* ctx, const dst_problem* prob, Setup& S, double* blocks_out, hipStream_t st) {
-  const View& v = S.v;
-  DST_TRY(ws(ctx, "hits", v.n_pix, &S.hits));
-  DST_TRY(ws(ctx, "M4", 4 * v.n_pix, &S.M4));
-  DST_TRY(ws(ctx, "Minv4", 4 * v.n_pix, &S.Minv4));
-  DST_TRY(ws(ctx, "valid", v.n_pix, &S.valid));
+// The per-pixel arrays of the atomic form, where dst_bin_noalloc's scratch is not used.
+int hold_atomic(dst_ctx* ctx, int64_t n_pix, Setup& S, double** s4) {
+  DST_TRY(ws(ctx, "hits", n_pix, &S.hits));
+  DST_TRY(ws(ctx, "M4", 4 * n_pix, &S.M4));
+  DST_TRY(ws(ctx, "Minv4", 4 * n_pix, &S.Minv4));
+  DST_TRY(ws(ctx, "valid", n_pix, &S.valid));
   DST_TRY(ws(ctx, "counts", 4, &S.counts));
+  return s4 ? ws(ctx, "s4", 4 * n_pix, s4) : DST_OK;
+}
+
+int run_setup(dst_ctx* ctx, const dst_problem* prob, Setup& S, double* blocks_out, hipStream_t st) {
+  DST_TRY(hold_atomic(ctx, S.v.n_pix, S, nullptr));
   return setup_pixels(ctx, prob, S, blocks_out, st);
 }
 
@@ -293,42 +298,82 @@ hipError_t copy4to3(double* dst3, const double* src4, int64_t n_pix, hipStream_t
                           hipMemcpyDeviceToDevice, st);
 }
 
-// One-shot binning of x = tod + bsign F base (either NULL) into the outputs of
-// `o` through the pixel buckets.  A map beyond their range leaves *done false, and the caller takes the atomic form.
-// The records are held for as much of the timeline as the workspace takes: a
-// stream under capture, where nothing can be allocated, and a full device use
-// what the context has and take more pieces.
-int bucket_pass(dst_ctx* ctx, const dst_problem* prob, const View& v, const void* tod, const double* base,
-                double bsign, const dst::BucketOut& o, hipStream_t st, bool* done) {
-  *done = dst::buckets_fit(v);
-  if (!*done) return DST_OK;
-  dst::BucketWork W;
-  const dst::BucketBytes need = dst::bucket_bytes(v, tod || base);
-  DST_TRY(ws_get(ctx, "bk_acc_hits", need.acc_hits, reinterpret_cast<void**>(&W.acc_hits)));
-  DST_TRY(ws_get(ctx, "bk_acc", need.acc, reinterpret_cast<void**>(&W.acc)));
+// Workspace of the bucket form for v.  Nothing can be allocated under capture,
+// where calls need what an earlier call on a map of as many pixels has left,
+// whatever its timeline, streams and weights were.  So a call that may allocate
+// holds bucket_reserve's sizes at least (and the atomic form's arrays, where
+// other weights would need that), and a captured one takes the pieces they
+// allow; one that does not find them takes the atomic form (*fits false).  A full
+// device gets by with smaller pieces.
+int bucket_space(dst_ctx* ctx, const View& v, bool data, dst::BucketWork& W, bool* fits) {
+  const dst::BucketBytes need = dst::bucket_bytes(v, data);
+  const dst::BucketReserve keep = dst::bucket_reserve(v.n_pix);
   struct Part {
     const char* name;
-    size_t per;
+    size_t per, least;
     void* ptr;
-  } parts[3] = {{"bk_off", need.off, nullptr}, {"bk_rec", need.rec, nullptr}, {"bk_rec2", need.rec2, nullptr}};
+  } parts[3] = {{"bk_off", need.off, keep.off, nullptr},
+                {"bk_rec", need.rec, keep.rec, nullptr},
+                {"bk_rec2", need.rec2, keep.rec2, nullptr}};
+  const bool captured = ctx->ws.captured();
   W.n_chunks = need.best_chunks;
+  *fits = true;
+  if (captured) {
+    for (const Part& p : parts)
+      if (p.per > 0) W.n_chunks = std::min(W.n_chunks, (int64_t)(ctx->ws.held(p.name) / p.per));
+    if (W.n_chunks == 0 || (W.n_chunks < need.n_chunks &&
+                            (ctx->ws.held("bk_acc_hits") < need.acc_hits || ctx->ws.held("bk_acc") < need.acc))) {
+      *fits = false;
+      return DST_OK;
+    }
+  }
+  // the sums carried from piece to piece, which a single piece does without
+  auto sums = [&](size_t hits, size_t acc) {
+    const int rc = ws_get(ctx, "bk_acc_hits", hits, reinterpret_cast<void**>(&W.acc_hits));
+    return rc != DST_OK ? rc : ws_get(ctx, "bk_acc", acc, reinterpret_cast<void**>(&W.acc));
+  };
+  if (!captured && sums(std::max(need.acc_hits, keep.acc_hits), std::max(need.acc, keep.acc)) != DST_OK)
+    W.acc = nullptr;
   for (Part& p : parts) {
-    if (p.per == 0) continue;
-    if (ctx->ws.captured()) {
-      const int64_t held = (int64_t)(ctx->ws.held(p.name) / p.per);
-      W.n_chunks = std::max<int64_t>(1, std::min(W.n_chunks, held));
-    }
-    // at least kBucketReserve bytes, so that a later call on a longer timeline can run in pieces without growing
-    for (;; W.n_chunks = (W.n_chunks + 1) / 2) {
-      const int rc = ws_get(ctx, p.name, std::max((size_t)W.n_chunks * p.per, dst::kBucketReserve), &p.ptr);
+    size_t least = captured ? 0 : p.least;
+    while (p.per > 0 || least > 0) {
+      const size_t bytes = (size_t)W.n_chunks * p.per;
+      const int rc = ws_get(ctx, p.name, std::max(bytes, least), &p.ptr);
       if (rc == DST_OK) break;
+      if (least > bytes) {
+        least = 0;
+        continue;
+      }
       if (W.n_chunks == 1) return rc;
+      W.n_chunks = (W.n_chunks + 1) / 2;
     }
+  }
+  if (W.n_chunks < need.n_chunks && !W.acc) DST_TRY(sums(need.acc_hits, need.acc));
+  if (!captured) {
+    Setup S;
+    double* s4;
+    if (dst::buckets_fit_any(v.n_pix))
+      (void)ws(ctx, "valid", v.n_pix, &S.valid);
+    else
+      (void)hold_atomic(ctx, v.n_pix, S, &s4);
   }
   ctx->err.clear();
   W.off = static_cast<uint16_t*>(parts[0].ptr);
   W.rec = parts[1].ptr;
   W.rec2 = static_cast<double*>(parts[2].ptr);
+  return DST_OK;
+}
+
+// One-shot binning of x = tod + bsign F base (either NULL) into the outputs of
+// `o` through the pixel buckets.  A map beyond their range, or a call that finds
+// no workspace for them, leaves *done false, and the caller takes the atomic form.
+int bucket_pass(dst_ctx* ctx, const dst_problem* prob, const View& v, const void* tod, const double* base,
+                double bsign, const dst::BucketOut& o, hipStream_t st, bool* done) {
+  *done = dst::buckets_fit(v);
+  if (!*done) return DST_OK;
+  dst::BucketWork W;
+  DST_TRY(bucket_space(ctx, v, tod || base, W, done));
+  if (!*done) return DST_OK;
   HIP_TRY(dst::launch_buckets(v, prob->psi_dtype == DST_F32, tod, prob->tod_dtype == DST_F32, base, bsign,
                               prob->rcond_cut, W, o, ctx->err_dev, st));
   return DST_OK;

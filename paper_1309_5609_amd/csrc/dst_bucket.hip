@@ -504,6 +504,27 @@ __global__ void __launch_bounds__(kSumBlock) k_bucket_sum(View v, double rcond_c
   }
 }
 
+// Buckets, and pixels of each.
+struct Deal {
+  int log_b, n_local;
+};
+Deal deal(int64_t n_pix, bool blk) {
+  Deal d;
+  const int64_t n_groups = (n_pix + 63) / 64;
+  d.log_b = kMinLogB;
+  while (((n_groups + ((int64_t)1 << d.log_b) - 1) >> d.log_b) * 64 > bucket_pix(blk)) ++d.log_b;
+  d.n_local = (int)((n_groups + ((int64_t)1 << d.log_b) - 1) >> d.log_b) * 64;
+  return d;
+}
+bool fits(int64_t n_pix, bool blk) { return n_pix <= (int64_t)bucket_pix(blk) << kMaxLogB; }
+
+// Samples per chunk: the records a chunk is writing at a time (all its
+// buckets') should stay in L2, which favours short chunks; the segments of
+// k_bucket_sum get longer with it.  30 days at N_side 256: 1.79 ms with
+// 1024, 1.71 with 2048, 1.87 with 4096, 2.2 with 16384.  Short timelines
+// take the smaller chunk to have more workgroups.
+constexpr int64_t kChunk = 2048, kShortChunk = 1024;
+
 struct Shape {
   int log_b, n_local;
   int64_t chunk, n_chunks;  // samples per chunk, chunks of the timeline
@@ -513,16 +534,10 @@ struct Shape {
 
 Shape shape_of(const View& v, bool data) {
   Shape s;
-  const int64_t n_groups = (v.n_pix + 63) / 64;
-  s.log_b = kMinLogB;
-  while (((n_groups + ((int64_t)1 << s.log_b) - 1) >> s.log_b) * 64 > bucket_pix(has_blocks(v))) ++s.log_b;
-  s.n_local = (int)((n_groups + ((int64_t)1 << s.log_b) - 1) >> s.log_b) * 64;
-  // Samples per chunk: the records a chunk is writing at a time (all its
-  // buckets') should stay in L2, which favours short chunks; the segments of
-  // k_bucket_sum get longer with it.  30 days at N_side 256: 1.79 ms with
-  // 1024, 1.71 with 2048, 1.87 with 4096, 2.2 with 16384.  Short timelines
-  // take the smaller chunk to have more workgroups.
-  s.chunk = v.n_t >= (int64_t)1 << 22 ? 2048 : 1024;
+  const Deal d = deal(v.n_pix, has_blocks(v));
+  s.log_b = d.log_b;
+  s.n_local = d.n_local;
+  s.chunk = v.n_t >= (int64_t)1 << 22 ? kChunk : kShortChunk;
   s.n_chunks = (v.n_t + s.chunk - 1) / s.chunk;
   const bool ht = v.rowT >= 0, hq = v.rowQ >= 0;
   s.n_data = data ? (ht ? 1 : 0) + (hq ? 2 : 0) : 0;
@@ -541,7 +556,8 @@ void by_bool(bool b, F&& f) {
 
 }  // namespace
 
-bool buckets_fit(const View& v) { return v.n_pix <= (int64_t)bucket_pix(has_blocks(v)) << kMaxLogB; }
+bool buckets_fit(const View& v) { return fits(v.n_pix, has_blocks(v)); }
+bool buckets_fit_any(int64_t n_pix) { return fits(n_pix, true); }
 
 BucketBytes bucket_bytes(const View& v, bool data) {
   const Shape s = shape_of(v, data);
@@ -555,6 +571,25 @@ BucketBytes bucket_bytes(const View& v, bool data) {
   b.n_chunks = s.n_chunks;
   b.best_chunks = std::min(s.n_chunks, kPiece / s.chunk);
   return b;
+}
+
+BucketReserve bucket_reserve(int64_t n_pix) {
+  // One record per pixel in a piece: carrying the sums from piece to piece then
+  // moves no more than the records do.
+  const int64_t samples = std::max<int64_t>((int64_t)1 << 19, n_pix);
+  const size_t chunks = (size_t)((samples + kShortChunk - 1) / kShortChunk);
+  BucketReserve r{};
+  r.rec = chunks * kShortChunk * sizeof(Rec3);
+  r.rec2 = chunks * kShortChunk * 3 * sizeof(double);
+  for (bool blk : {false, true}) {
+    if (!fits(n_pix, blk)) continue;
+    const Deal d = deal(n_pix, blk);
+    const size_t px = (size_t)d.n_local << d.log_b;
+    r.off = std::max(r.off, chunks * (((size_t)1 << d.log_b) + 1) * sizeof(uint16_t));
+    r.acc_hits = std::max(r.acc_hits, px * sizeof(uint32_t));
+    r.acc = std::max(r.acc, px * (blk ? 6 : 3) * sizeof(double));
+  }
+  return r;
 }
 
 hipError_t launch_buckets(const View& v, int psi_f32, const void* tod, int tod_f32, const double* base, double bsign,

@@ -68,3 +68,45 @@ def test_longer_calls_after_a_capture(name):
         del guard
     c.close()
     e.close()
+
+
+EQ, NE = (1.0, 3.0, 3.0), (1.0, 3.0, 2.0)
+WIDE = 3_200_000  # fits the buckets with equal q/u weights only
+
+
+# the call before (eager), the captured one: every pair that needs no more than a map of as many pixels
+@pytest.mark.parametrize("before,after", [
+    (("bin", "T", EQ, 901, N_PIX), ("bin", "TQU", EQ, 901, N_PIX)),
+    (("bin", "T", EQ, 901, N_PIX), ("bin", "TQU", NE, 901, N_PIX)),
+    (("bin", "TQU", EQ, 901, N_PIX), ("bin", "QU", NE, 70_001, N_PIX)),
+    (("bin", "T", EQ, 901, N_PIX), ("bin", "TQU", NE, 1_300_001, N_PIX)),      # several pieces
+    (("setup", "T", EQ, 901, N_PIX), ("setup", "TQU", NE, 1_300_001, N_PIX)),
+    (("setup", "TQU", EQ, 901, N_PIX), ("reduce", "TQU", NE, 901, N_PIX)),
+    (("bin", "QU", EQ, 901, N_PIX), ("reduce", "TQU", EQ, 901, N_PIX)),
+    (("residual", "T", EQ, 901, N_PIX), ("bin", "TQU", NE, 901, N_PIX)),
+    (("residual", "QU", EQ, 901, N_PIX), ("residual", "QU", NE, 901, N_PIX)),
+    (("bin", "TQU", EQ, 901, N_PIX), ("bin", "TQU", NE, 901, N_PIX // 9)),     # a smaller map
+    (("bin", "T", EQ, 901, WIDE), ("bin", "TQU", NE, 901, WIDE)),              # buckets, then the atomic form
+    (("residual", "TQU", EQ, 901, WIDE), ("residual", "TQU", NE, 901, WIDE)),
+    (("bin", "TQU", EQ, 901, 7_000_000), ("bin", "TQU", NE, 901, N_PIX)),      # the atomic form, then a small map
+])
+def test_captured_call_is_accepted(before, after):
+    import torch
+    from paper_1309_5609_amd import dst
+    c, e = dst.Context(0), dst.Context(0)
+    name, streams, weights, n, n_pix = before
+    calls(name)(c, problem(n, streams, weights, n_pix))
+    torch.cuda.synchronize()
+    name, streams, weights, n, n_pix = after
+    p = problem(n, streams, weights, n_pix)
+    if n_pix < N_PIX:
+        p.pix %= n_pix
+    g, got = capture(c, calls(name), p)
+    for k in range(3):
+        p.tod.mul_(-1.5)
+        want = calls(name)(e, p)
+        g.replay()
+        torch.cuda.synchronize()
+        assert close(got, want, n)
+    c.close()
+    e.close()
