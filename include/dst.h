@@ -35,7 +35,11 @@
  * baseline vectors are [n_streams][n_b]; maps are [n_pix][3] in (I, Q, U)
  * order.  The library keeps no caller pointer after a call returns and owns
  * only the workspace inside its context (grown on demand, freed by
- * dst_destroy).
+ * dst_destroy; what earlier calls left is given back when a call finds no
+ * memory).  dst_pixel_setup, dst_bin, dst_baseline_reduce and dst_residual keep
+ * run records in it, 30 MB at least and at most 1.1 GiB (1.9 GiB with unequal
+ * q/u weights), and about 110 bytes per pixel.  Under stream capture each of them allocates nothing after a call of it
+ * on a map of as many pixels, and what it uses then stays until dst_destroy.
  *
  * Streams and synchrony.  Work is issued on the caller's `stream` (NULL = the
  * null stream).  dst_pixel_setup, dst_bin, dst_unbin, dst_baseline_reduce and

@@ -834,6 +834,7 @@ int solve_group(dst_ctx* ctx, const dst_problem* problems, const std::vector<int
   const bool use_graph = !(opts.flags & (DST_SOLVE_NO_GRAPH | DST_SOLVE_PROFILE));
   View v{};
   DST_TRY(check_problem(ctx, &p0, true, v));
+  ws_begin(ctx, st);
   EventSet evs;
   hipEvent_t ev[4];
   for (auto& e : ev) HIP_TRY(evs.add(&e));
@@ -1061,6 +1062,7 @@ int solve_uneven(dst_ctx* ctx, const dst_problem* problems, const std::vector<in
     int32_t ncomp = 0;
   };
   std::vector<Member> M(n);
+  ws_begin(ctx, st);
   EventSet evs;
   hipEvent_t ev[4];
   for (auto& e : ev) HIP_TRY(evs.add(&e));

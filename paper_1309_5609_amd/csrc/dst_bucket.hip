@@ -41,7 +41,10 @@ constexpr int kGroupBits = 6;     // pixels dealt together: 64
 constexpr int kMinLogB = 8;       // at least 256 buckets: one workgroup of k_bucket_sum per CU
 constexpr int kMaxLogB = 11;      // at most 2048 buckets (their counters share LDS in k_bucket_fill)
 constexpr int kSumBlock = 1024;
-constexpr int64_t kPiece = (int64_t)1 << 25;  // samples whose records are held at once (at most 1 GiB of them)
+// Samples whose records are held at once: 1 GiB of them at most with equal q/u
+// weights, 1.75 GiB with block sums (64 M samples there: 1.43 ms, 1.50 in pieces
+// of 1 GiB).
+constexpr int64_t kPiece = (int64_t)1 << 25;
 
 // Most pixels of a bucket: what LDS holds of hits and sums (28 bytes a pixel
 // with equal q/u weights, 52 with block sums).  Large buckets make long

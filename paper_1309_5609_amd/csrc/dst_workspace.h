@@ -5,9 +5,15 @@
 // the caller's graph, and a replay writes there whenever it comes.  Such a
 // buffer is never freed or moved before the context ends: when a later call
 // needs more, it gets another one.
+//
+// What a call leaves in a buffer no later call reads, so buffers that the
+// present call has not asked for are given back when memory runs out: a context
+// that has binned a long timeline holds a gigabyte of records, and a solve after
+// it may need that.
 #pragma once
 
 #include <cstddef>
+#include <cstdint>
 #include <string>
 #include <unordered_map>
 #include <vector>
@@ -24,7 +30,10 @@ class Workspace {
   Workspace& operator=(const Workspace&) = delete;
 
   // Start of a call; captured: what it gets ends up in a graph.
-  void begin(bool captured) { captured_ = captured; }
+  void begin(bool captured) {
+    captured_ = captured;
+    ++call_;
+  }
   bool captured() const { return captured_; }
 
   // Buffer `name` of at least `bytes`; nullptr, with nothing held under the
@@ -33,16 +42,20 @@ class Workspace {
     Buf& b = bufs_[name];
     if (b.bytes < bytes) {
       void* p = nullptr;
-      if (captured_ || b.in_graph) {
+      if (captured_) {
         if (!alloc_(&p, bytes)) return nullptr;
+        if (b.ptr) retired_.push_back(b.ptr);
+      } else if (b.in_graph) {
+        if (!alloc_(&p, bytes) && !(give_back() && alloc_(&p, bytes))) return nullptr;
         if (b.ptr) retired_.push_back(b.ptr);
       } else {
         drop(b);  // first, so that both need not fit
-        if (!alloc_(&p, bytes)) return nullptr;
+        if (!alloc_(&p, bytes) && !(give_back() && alloc_(&p, bytes))) return nullptr;
       }
-      b = Buf{p, bytes, false};
+      b = Buf{p, bytes, 0, false};
     }
     b.in_graph |= captured_;
+    b.call = call_;
     return b.ptr;
   }
 
@@ -65,8 +78,21 @@ class Workspace {
   struct Buf {
     void* ptr = nullptr;
     size_t bytes = 0;
+    uint64_t call = 0;  // the last call that asked for it
     bool in_graph = false;
   };
+  // Frees the buffers that no graph holds and the present call has not asked
+  // for; whether there were any.
+  bool give_back() {
+    bool any = false;
+    for (auto& kv : bufs_) {
+      Buf& b = kv.second;
+      if (!b.ptr || b.in_graph || b.call == call_) continue;
+      drop(b);
+      any = true;
+    }
+    return any;
+  }
   void drop(Buf& b) {
     if (b.ptr) free_(b.ptr);
     b = Buf{};
@@ -75,6 +101,7 @@ class Workspace {
   Alloc alloc_;
   Free free_;
   bool captured_ = false;
+  uint64_t call_ = 0;
   std::unordered_map<std::string, Buf> bufs_;
   std::vector<void*> retired_;  // outgrown buffers that a graph holds
 };

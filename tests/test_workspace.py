@@ -22,3 +22,8 @@ def check(tmp_path_factory):
 def test_a_captured_calls_buffers_stay(check):
     """What a call under capture was given is neither freed nor moved by longer calls after it."""
     assert check("graph") == "ok"
+
+
+def test_memory_is_given_back_when_it_runs_out(check):
+    """Buffers of earlier calls make room; those of the present call, and those in a graph, stay."""
+    assert check("give_back") == "ok"

@@ -59,9 +59,35 @@ int graph() {
   return 0;
 }
 
+int give_back() {
+  dst::Workspace w(take, give);
+  room = 10000;
+  w.begin(false);
+  w.get("records", 6000);
+  w.get("small", 256);
+  w.begin(true);
+  w.get("graph", 1000);
+  w.begin(false);  // a call that needs the records' room
+  void* a = w.get("a", 2000);
+  void* small = w.get("small", 256);
+  void* b = w.get("b", 6000);
+  if (!b) return fail("a buffer of an earlier call was not given back");
+  if (!live.count(a) || !live.count(small) || w.held("graph") != 1000) return fail("a buffer in use was given back");
+  if (w.held("records") != 0) return fail("a freed buffer is still held");
+  if (w.get("c", 9000) != nullptr) return fail("no room: nullptr");
+  if (!live.count(a) || !live.count(b)) return fail("the present call's buffers were given back");
+  w.begin(false);
+  if (!w.get("records", 6000) || w.held("b") != 0) return fail("and the other way round");
+  w.begin(true);  // under capture nothing is freed
+  if (w.get("d", 6000) != nullptr || w.held("records") != 6000) return fail("a captured call freed a buffer");
+  w.clear();
+  return live.empty() ? 0 : fail("clear left something");
+}
+
 int main(int argc, char** argv) {
   int rc = 1;
   if (argc == 2 && !std::strcmp(argv[1], "graph")) rc = graph();
+  if (argc == 2 && !std::strcmp(argv[1], "give_back")) rc = give_back();
   if (rc == 0) std::printf("ok\n");
   return rc;
 }
