@@ -2,7 +2,8 @@
 // without global atomics (dst_pixel_setup, dst_bin, dst_baseline_reduce,
 // dst_residual).
 //
-// Pixels are dealt to buckets, 64 neighbouring pixels at a time.  k_bucket_fill splits the timeline into chunks, one
+// Pixels are dealt to buckets round robin, 64 neighbouring pixels at a time (fewer
+// where the map has no 256 such groups).  k_bucket_fill splits the timeline into chunks, one
 // workgroup each: it sums stretches of consecutive samples on one pixel
 // ("runs") and writes each run's record into the chunk's own range,
 // ordered by bucket, with the bucket offsets beside it.  k_bucket_sum, one
@@ -15,6 +16,13 @@
 // samples, about 1 GB moved, and k_bucket_sum 0.15 ms), of 6 hours at N_side
 // 64 79 -> 42 us of kernels.  k_bucket_fill is bound by HBM traffic and its
 // FP64 angle functions, k_bucket_sum by the latency of its short segments.
+//
+// Coarse maps and long stays on one pixel put many records into few buckets, and
+// into few LDS places of them.  There the groups are smaller, a pixel's sums are
+// kept in up to 64 copies, and the stretch of a wavefront's lanes that stay on
+// one pixel is one record.  30 M samples T/q/u FP64 without these, with them, and
+// by the atomic form: stays of 5000 samples on 48 pixels 36.7, 0.27 and 3.6 ms,
+// 48 pixels at random 28.7, 1.2 and 122 ms, one pixel 36.9, 0.35 and 33.8 ms.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -37,10 +45,11 @@ using dev::next_lane;
 using dev::prev_lane;
 using dev::qu_block_inverse;
 
-constexpr int kGroupBits = 6;     // pixels dealt together: 64
+constexpr int kMaxLogG = 6;       // at most 64 pixels dealt together
+constexpr int kMaxLogC = 6;       // at most 64 copies of a pixel's sums
 constexpr int kMinLogB = 8;       // at least 256 buckets: one workgroup of k_bucket_sum per CU
 constexpr int kMaxLogB = 11;      // at most 2048 buckets (their counters share LDS in k_bucket_fill)
-constexpr int kSumBlock = 1024;
+constexpr int kSumBlock = 1024;  // (at most bucket_pix)
 // Samples whose records are held at once: 1 GiB of them at most with equal q/u
 // weights, 1.75 GiB with block sums (64 M samples there: 1.43 ms, 1.50 in pieces
 // of 1 GiB).
@@ -84,11 +93,16 @@ struct RecOf<HQ, false> {
 // there is recorded by the lane where it starts (gives: this lane's first
 // stretch belongs to the previous lane; takes: the next lane's to this one);
 // longer ones are recorded in pieces.
+// Where half of the lanes at least lie, whole, on the pixel of a whole lane before
+// them (joined), such a stretch is one record, of its first lane.
 struct QuadRuns {
   bool brk[4];  // sample k on another pixel than sample k - 1 (brk[0] true)
   bool start[4];
   bool takes;
+  unsigned long long goes_on;  // lanes whose stretch began before them (0: none are joined)
 };
+// JOIN: false where no group of the wavefront is known to have joined lanes.
+template <bool JOIN>
 __device__ __forceinline__ QuadRuns quad_runs(const int (&p)[4]) {
   QuadRuns q;
   q.brk[0] = true;
@@ -96,12 +110,22 @@ __device__ __forceinline__ QuadRuns quad_runs(const int (&p)[4]) {
   for (int k = 1; k < 4; ++k) q.brk[k] = p[k] != p[k - 1];
   const int lane = lane_id();
   const int before = prev_lane(p[3]);
-  const bool gives = lane > 0 && p[0] >= 0 && before == p[0] && (q.brk[1] || q.brk[2] || q.brk[3]);
+  const bool same = lane > 0 && p[0] >= 0 && before == p[0];
+  const bool whole = !(q.brk[1] || q.brk[2] || q.brk[3]);
+  const bool gives = same && !whole;
   const int from_next = next_lane((int)gives);  // on every lane: a lane masked off by a branch gives no data
   q.takes = lane < 63 && from_next != 0;
 #pragma unroll
   for (int k = 0; k < 4; ++k) q.start[k] = q.brk[k] && p[k] >= 0;
   q.start[0] = q.start[0] && !gives;
+  q.goes_on = 0;
+  if (JOIN) {
+    const unsigned long long wholes = __ballot(whole), on = __ballot(same) & wholes & wholes << 1;
+    if (__popcll(on) >= 32) {
+      q.goes_on = on;
+      if (on >> lane & 1ull) q.start[0] = false;
+    }
+  }
   return q;
 }
 
@@ -118,6 +142,25 @@ __device__ __forceinline__ void quad_sums(const QuadRuns& q, T (&x)[4]) {
     if (!q.brk[k + 1]) x[k] += x[k + 1];
 }
 
+// Joined lanes: n and x[j][0] of a stretch's first lane become the sums over it.
+template <int N>
+__device__ __forceinline__ void join_sums(const QuadRuns& q, int& n, double (&x)[N][4]) {
+  const int lane = lane_id();
+  const unsigned long long ends = lane < 63 ? ~q.goes_on >> (lane + 1) : 0ull;
+  const int end = ends ? lane + __ffsll(ends) : 64;  // first lane past this lane's stretch
+#pragma unroll 1
+  for (int off = 1; off < 64; off <<= 1) {
+    const bool in = lane + off < end;
+    const int m = __shfl_down(n, off, 64);
+    n += in ? m : 0;
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      const double o = __shfl_down(x[j][0], off, 64);
+      x[j][0] += in ? o : 0.0;
+    }
+  }
+}
+
 // One chunk [lo, hi) per workgroup.  DATA: the data sums of x = tod + bsign F
 // base (either may be NULL) as T: w_T x; q/u: the rotated, weighted pair.
 // Four consecutive samples per lane: 16-byte loads, and the run sums inside a
@@ -129,7 +172,7 @@ __device__ __forceinline__ void quad_sums(const QuadRuns& q, T (&x)[4]) {
 template <typename PT, typename TT, bool HT, bool HQ, bool DATA, bool EQ>
 __global__ void __launch_bounds__(kBlock) k_bucket_fill(View v, const TT* __restrict__ tod,
                                                         const double* __restrict__ base, double bsign, int64_t t_lo,
-                                                        int64_t t_hi, int64_t chunk, int log_b,
+                                                        int64_t t_hi, int64_t chunk, int log_b, int log_g,
                                                         uint16_t* __restrict__ off,
                                                         typename RecOf<HQ, DATA>::type* __restrict__ rec,
                                                         double* __restrict__ rec2, int* __restrict__ err) {
@@ -154,7 +197,7 @@ __global__ void __launch_bounds__(kBlock) k_bucket_fill(View v, const TT* __rest
     }
   };
   // runs per bucket
-  bool bad = false;
+  bool bad = false, joined = false;
   int ahead[4];
   load(pix, 256 * wave + 4 * lane, -1, ahead);
   for (int g = wave; g < groups; g += kWaves) {
@@ -168,10 +211,11 @@ __global__ void __launch_bounds__(kBlock) k_bucket_fill(View v, const TT* __rest
       }
     }
     load(pix, 256 * (g + kWaves) + 4 * lane, -1, ahead);
-    const QuadRuns q = quad_runs(p);
+    const QuadRuns q = quad_runs<true>(p);
+    joined |= q.goes_on != 0;
 #pragma unroll
     for (int k = 0; k < 4; ++k)
-      if (q.start[k]) atomicAdd(&cur[((uint32_t)p[k] >> kGroupBits) & bmask], 1u);
+      if (q.start[k]) atomicAdd(&cur[((uint32_t)p[k] >> log_g) & bmask], 1u);
   }
   if (__ballot(bad) != 0ull && lane == 0) atomicOr(err, 1);
   __syncthreads();
@@ -240,10 +284,11 @@ __global__ void __launch_bounds__(kBlock) k_bucket_fill(View v, const TT* __rest
     }
   };
   In now;
-  for (int g = wave; g < groups; g += kWaves) {
+  auto write = [&](int g, auto join) {
+    constexpr bool JOIN = decltype(join)::value;
     fetch(g, now);
     int p[4], cnt[4];
-    double x[N > 0 ? N : 1][4];
+    double x[N > 0 ? N : 1][4] = {};
 #pragma unroll
     for (int k = 0; k < 4; ++k) p[k] = now.p[k] >= v.n_pix ? -1 : now.p[k];
     double a2[4], sin4[4] = {0.0, 0.0, 0.0, 0.0}, cos4[4] = {0.0, 0.0, 0.0, 0.0};
@@ -275,7 +320,7 @@ __global__ void __launch_bounds__(kBlock) k_bucket_fill(View v, const TT* __rest
     for (int k = 0; k < 4; ++k) {
       cnt[k] = 1;
       a2[k] = HQ ? 2.0 * (double)now.ps[k] : 0.0;
-      if (HQ && EQ && !isfinite(a2[k])) cnt[k] |= 1 << 8;
+      if (HQ && EQ && !isfinite(a2[k])) cnt[k] |= 1 << 16;  // (a record holds 259 samples at most)
     }
     if (HQ && (DATA || BLK)) fast_sincos4(a2, sin4, cos4);
 #pragma unroll
@@ -307,17 +352,18 @@ __global__ void __launch_bounds__(kBlock) k_bucket_fill(View v, const TT* __rest
         x[N - 1][k] = wq * s * s + wu * c * c;
       }
     }
-    const QuadRuns q = quad_runs(p);
+    const QuadRuns q = quad_runs<JOIN>(p);
     quad_sums(q, cnt);
 #pragma unroll
     for (int j = 0; j < N; ++j) quad_sums(q, x[j]);
+    if (JOIN && q.goes_on) join_sums(q, cnt[0], x);
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       if (!q.start[k]) continue;
-      const uint32_t grp = (uint32_t)p[k] >> kGroupBits;
-      const uint32_t local = ((grp >> log_b) << kGroupBits) | ((uint32_t)p[k] & ((1u << kGroupBits) - 1u));
+      const uint32_t grp = (uint32_t)p[k] >> log_g;
+      const uint32_t local = ((grp >> log_b) << log_g) | ((uint32_t)p[k] & ((1u << log_g) - 1u));
       const uint32_t at = atomicAdd(&cur[grp & bmask], 1u);
-      const uint32_t key = local | ((uint32_t)(cnt[k] & 0xff) << 16) | (cnt[k] >> 8 ? kBadAngle : 0u);
+      const uint32_t key = local | ((uint32_t)(cnt[k] & 0xffff) << 16) | (cnt[k] >> 16 ? kBadAngle : 0u);
       if constexpr (!DATA) {
         out[at] = key;
       } else if constexpr (!HQ) {
@@ -348,6 +394,12 @@ __global__ void __launch_bounds__(kBlock) k_bucket_fill(View v, const TT* __rest
         gr -= n * L;
       }
     }
+  };
+  // (the test for joined lanes in the way of every group: 30 days 1.75 ms, 1.72 without)
+  if (joined) {
+    for (int g = wave; g < groups; g += kWaves) write(g, std::true_type{});
+  } else {
+    for (int g = wave; g < groups; g += kWaves) write(g, std::false_type{});
   }
 }
 
@@ -358,7 +410,8 @@ template <bool HT, bool HQ, bool DATA, bool EQ>
 __global__ void __launch_bounds__(kSumBlock) k_bucket_sum(View v, double rcond_cut, const uint16_t* __restrict__ off,
                                                           const typename RecOf<HQ, DATA>::type* __restrict__ rec,
                                                           const double* __restrict__ rec2, int n_chunks, int64_t chunk,
-                                                          int log_b, int n_local, int first, int last,
+                                                          int log_b, int log_g, int log_c, int n_local, int first,
+                                                          int last,
                                                           uint32_t* __restrict__ acc_hits, double* __restrict__ acc,
                                                           BucketOut o) {
   using Rec = typename RecOf<HQ, DATA>::type;
@@ -372,10 +425,14 @@ __global__ void __launch_bounds__(kSumBlock) k_bucket_sum(View v, double rcond_c
   // runs on XCD i mod 8) takes B / 8 neighbours
   const int B = 1 << log_b;
   const int b = (int)((blockIdx.x & 7u) << (log_b - 3) | blockIdx.x >> 3);
-  for (int l = threadIdx.x; l < n_local; l += kSumBlock) {
-    hits[l] = first ? 0u : acc_hits[(int64_t)b * n_local + l];
+  // pixel l's copies are at l << log_c and the places after it; a lane adds into its own
+  const int cmask = (1 << log_c) - 1;
+  for (int i = threadIdx.x; i < n_local << log_c; i += kSumBlock) {
+    const int l = i >> log_c;
+    const bool carried = !first && (i & cmask) == 0;
+    hits[i] = carried ? acc_hits[(int64_t)b * n_local + l] : 0u;
 #pragma unroll
-    for (int k = 0; k < NA; ++k) sum[k][l] = first ? 0.0 : acc[((int64_t)b * NA + k) * n_local + l];
+    for (int k = 0; k < NA; ++k) sum[k][i] = carried ? acc[((int64_t)b * NA + k) * n_local + l] : 0.0;
   }
   __syncthreads();
   // A wavefront takes the segments of 64 chunks and deals their records to its
@@ -390,7 +447,7 @@ __global__ void __launch_bounds__(kSumBlock) k_bucket_sum(View v, double rcond_c
       key = r.key;
     else
       key = r;
-    const int l = (int)(key & 0xffffu);
+    const int l = (int)((key & 0xffffu) << log_c) | (lane & cmask);
     atomicAdd(&hits[l], (key >> 16) & 0x7fffu);
     if (HQ && EQ && (key & kBadAngle)) atomicOr(&hits[l], kBadAngle);
     if constexpr (DATA) {
@@ -444,15 +501,25 @@ __global__ void __launch_bounds__(kSumBlock) k_bucket_sum(View v, double rcond_c
     __builtin_amdgcn_wave_barrier();
   }
   __syncthreads();
-  for (int l = threadIdx.x; l < n_local; l += kSumBlock) {
-    if (!last) {
-      acc_hits[(int64_t)b * n_local + l] = hits[l];
+  for (int h = log_c - 1; h >= 0; --h) {
+    for (int i = threadIdx.x; i < n_local << h; i += kSumBlock) {
+      const int to = (i >> h << log_c) + (i & ((1 << h) - 1)), from = to + (1 << h);
+      const uint32_t x = hits[to], y = hits[from];
+      hits[to] = ((x & ~kBadAngle) + (y & ~kBadAngle)) | ((x | y) & kBadAngle);
 #pragma unroll
-      for (int k = 0; k < NA; ++k) acc[((int64_t)b * NA + k) * n_local + l] = sum[k][l];
+      for (int k = 0; k < NA; ++k) sum[k][to] += sum[k][from];
+    }
+    __syncthreads();
+  }
+  for (int pl = threadIdx.x; pl < n_local; pl += kSumBlock) {
+    const int l = pl << log_c;
+    if (!last) {
+      acc_hits[(int64_t)b * n_local + pl] = hits[l];
+#pragma unroll
+      for (int k = 0; k < NA; ++k) acc[((int64_t)b * NA + k) * n_local + pl] = sum[k][l];
       continue;
     }
-    const int64_t p = ((int64_t)(((uint32_t)l >> kGroupBits) << log_b | (uint32_t)b) << kGroupBits) |
-                      (l & ((1 << kGroupBits) - 1));
+    const int64_t p = ((int64_t)(((uint32_t)pl >> log_g) << log_b | (uint32_t)b) << log_g) | (pl & ((1 << log_g) - 1));
     if (p >= v.n_pix) continue;
     const int h = (int)(hits[l] & ~kBadAngle);
     uint8_t f = 0;
@@ -507,16 +574,20 @@ __global__ void __launch_bounds__(kSumBlock) k_bucket_sum(View v, double rcond_c
   }
 }
 
-// Buckets, and pixels of each.
+// Buckets, pixels dealt together, and pixels of each bucket: groups of 64 keep a
+// scan's neighbours together, smaller ones give every bucket of a coarse map some.
 struct Deal {
-  int log_b, n_local;
+  int log_b, log_g, n_local;
 };
 Deal deal(int64_t n_pix, bool blk) {
   Deal d;
-  const int64_t n_groups = (n_pix + 63) / 64;
+  d.log_g = kMaxLogG;
+  while (d.log_g > 0 && (n_pix + ((int64_t)1 << d.log_g) - 1) >> d.log_g < (int64_t)1 << kMinLogB) --d.log_g;
+  const int64_t n_groups = (n_pix + ((int64_t)1 << d.log_g) - 1) >> d.log_g;
+  auto local = [&]() { return (n_groups + ((int64_t)1 << d.log_b) - 1) >> d.log_b << d.log_g; };
   d.log_b = kMinLogB;
-  while (((n_groups + ((int64_t)1 << d.log_b) - 1) >> d.log_b) * 64 > bucket_pix(blk)) ++d.log_b;
-  d.n_local = (int)((n_groups + ((int64_t)1 << d.log_b) - 1) >> d.log_b) * 64;
+  while (local() > bucket_pix(blk)) ++d.log_b;
+  d.n_local = (int)local();
   return d;
 }
 bool fits(int64_t n_pix, bool blk) { return n_pix <= (int64_t)bucket_pix(blk) << kMaxLogB; }
@@ -529,7 +600,7 @@ bool fits(int64_t n_pix, bool blk) { return n_pix <= (int64_t)bucket_pix(blk) <<
 constexpr int64_t kChunk = 2048, kShortChunk = 1024;
 
 struct Shape {
-  int log_b, n_local;
+  int log_b, log_g, log_c, n_local;
   int64_t chunk, n_chunks;  // samples per chunk, chunks of the timeline
   int n_data, n_blk;        // data and block sums per record
   size_t rec_bytes;
@@ -539,7 +610,13 @@ Shape shape_of(const View& v, bool data) {
   Shape s;
   const Deal d = deal(v.n_pix, has_blocks(v));
   s.log_b = d.log_b;
+  s.log_g = d.log_g;
   s.n_local = d.n_local;
+  s.log_c = 0;
+  // Copies: one place per thread at most, and 16 samples per place (a thousand
+  // samples 33.7 us with all copies, 31.5 with one; 100,000 of 192 pixels 34 and
+  // 74 us).
+  while (s.log_c < kMaxLogC && s.n_local << (s.log_c + 1) <= kSumBlock && v.n_pix << (s.log_c + 5) <= v.n_t) ++s.log_c;
   s.chunk = v.n_t >= (int64_t)1 << 22 ? kChunk : kShortChunk;
   s.n_chunks = (v.n_t + s.chunk - 1) / s.chunk;
   const bool ht = v.rowT >= 0, hq = v.rowQ >= 0;
@@ -616,7 +693,7 @@ hipError_t launch_buckets(const View& v, int psi_f32, const void* tod, int tod_f
                 using PT = decltype(pt);
                 using TT = decltype(tt);
                 hipLaunchKernelGGL((k_bucket_fill<PT, TT, HT, HQ, DA, EQ>), dim3(n_chunks), dim3(kBlock), 0, st, v,
-                                   static_cast<const TT*>(tod), base, bsign, t0, t1, s.chunk, s.log_b, W.off,
+                                   static_cast<const TT*>(tod), base, bsign, t0, t1, s.chunk, s.log_b, s.log_g, W.off,
                                    static_cast<Rec*>(W.rec), W.rec2, err);
               };
               const bool pf = HQ && psi_f32, tf = DA && tod_f32;
@@ -630,7 +707,7 @@ hipError_t launch_buckets(const View& v, int psi_f32, const void* tod, int tod_f
                 fill(double{}, double{});
               hipLaunchKernelGGL((k_bucket_sum<HT, HQ, DA, EQ>), dim3(1u << s.log_b), dim3(kSumBlock), 0, st, v,
                                  rcond_cut, W.off, static_cast<const Rec*>(W.rec), W.rec2, n_chunks, s.chunk, s.log_b,
-                                 s.n_local, first, last, W.acc_hits, W.acc, o);
+                                 s.log_g, s.log_c, s.n_local, first, last, W.acc_hits, W.acc, o);
             }
           });
         });
