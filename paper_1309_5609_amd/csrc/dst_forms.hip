@@ -45,6 +45,10 @@ constexpr double kSparse = 32.0;  // most runs per pixel of BIN_PIPE
 constexpr unsigned kPipeBlocks = 4096;  // 1024 to 16384: 101, 100, 97, 110 us at 8 runs per pixel
 constexpr int kPipeThreads = 256, kPipeWaves = kPipeThreads / 64;
 constexpr int kU = 4;  // runs per lane whose loads are issued together (twice that without angles)
+// A pixel of more steps than this is finished by the whole wavefront.  20 M
+// samples FP32, 1000 pixels with 30 % of them: T/q/u 647 -> 136 us a launch (the
+// plain form 436), intensity 289 -> 68 (149).
+constexpr int kDeepSteps = 16;
 
 // LDS values per baseline.
 int columns_of(const View& v) { return v.iqu ? 1 : (v.rowT >= 0 ? 1 : 0) + (v.rowQ >= 0 ? 2 : 0); }
@@ -121,10 +125,11 @@ __device__ __forceinline__ void bin_body(double* p_lds, const BinRuns& B, const 
     uint32_t key[U];
     CS2<RT> ang[U];
   };
-  auto fetch = [&](uint32_t j, uint32_t j1, Fetched& f) {
+  auto fetch = [&](auto lanes, uint32_t j, uint32_t j1, Fetched& f) {
+    constexpr int N = decltype(lanes)::value;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const uint32_t jj = j + LPP * u < j1 ? j + LPP * u : 0u;
+      const uint32_t jj = j + N * u < j1 ? j + N * u : 0u;
       f.key[u] = B.key[jj];
       if (ANG) f.ang[u] = cs[jj];
     }
@@ -145,7 +150,6 @@ __device__ __forceinline__ void bin_body(double* p_lds, const BinRuns& B, const 
       if (IQU) x.i45 = ip[2];  // (00, 01), (02, 11), (12, 22)
     }
   };
-  double acc[3];
   struct Gathered {
     double2 x[LDS ? 1 : U];
     double u[LDS ? 1 : U];
@@ -165,10 +169,11 @@ __device__ __forceinline__ void bin_body(double* p_lds, const BinRuns& B, const 
       }
     }
   };
-  auto add = [&](const Fetched& f, const Gathered& g, uint32_t j, uint32_t j1) {
+  auto add = [&](auto lanes, const Fetched& f, const Gathered& g, uint32_t j, uint32_t j1, double (&acc)[3]) {
+    constexpr int N = decltype(lanes)::value;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const bool in = j + LPP * u < j1;
+      const bool in = j + N * u < j1;
       const int i = in ? (int)(f.key[u] >> nb) : 0;
       const double n = in ? (double)((f.key[u] & nmask) + 1u) : 0.0;
       const double C = ANG && in ? (double)f.ang[u].x : 0.0, S = ANG && in ? (double)f.ang[u].y : 0.0;
@@ -187,28 +192,47 @@ __device__ __forceinline__ void bin_body(double* p_lds, const BinRuns& B, const 
       }
     }
   };
+  // runs j, j + N, ... of a pixel past its first step
+  auto more = [&](auto lanes, uint32_t j, uint32_t j1, double (&acc)[3]) {
+    constexpr int N = decltype(lanes)::value;
+    for (; j < j1; j += N * U) {
+      Fetched f;
+      fetch(lanes, j, j1, f);
+      Gathered h;
+      gather(f, h);
+      add(lanes, f, h, j, j1, acc);
+    }
+  };
+  const std::integral_constant<int, LPP> group{};
   uint32_t a0, a1, n0, n1;
   Fetched now, next;
   Side s_now, s_next;
   range(cfirst, a0, a1);
   range(cfirst + step, n0, n1);
   side(cfirst, s_now);
-  fetch(a0 + sub, a1, now);
+  fetch(group, a0 + sub, a1, now);
   for (int64_t c = cfirst; c - grp < c1; c += step) {
     Gathered g;
     gather(now, g);
     side(c + step, s_next);
-    fetch(n0 + sub, n1, next);
+    fetch(group, n0 + sub, n1, next);
     uint32_t f0, f1;
     range(c + 2 * step, f0, f1);
-    acc[0] = acc[1] = acc[2] = 0.0;
-    add(now, g, a0 + sub, a1);
-    for (uint32_t j = a0 + sub + LPP * U; j < a1; j += LPP * U) {  // more runs than a step holds
-      Fetched f;
-      fetch(j, a1, f);
-      Gathered h;
-      gather(f, h);
-      add(f, h, j, a1);
+    double acc[3] = {0.0, 0.0, 0.0};
+    add(group, now, g, a0 + sub, a1, acc);
+    const bool deep = a1 - a0 > (uint32_t)(kDeepSteps * LPP * U);
+    if (!deep) more(group, a0 + sub + LPP * U, a1, acc);
+    for (unsigned long long m = __ballot(deep && sub == 0); m != 0; m &= m - 1) {
+      const int src = __ffsll(m) - 1;
+      const uint32_t j = __shfl(a0, src, 64) + LPP * U, j1 = __shfl(a1, src, 64);
+      double t[3] = {0.0, 0.0, 0.0};
+      more(std::integral_constant<int, 64>{}, j + lane, j1, t);
+      // the group's lanes add a part each
+      for (int i = 0; i < 3; ++i) {
+#pragma unroll
+        for (int off = 32; off >= LPP; off >>= 1) t[i] += __shfl_xor(t[i], off, 64);
+        acc[i] += grp == src / LPP ? t[i] : 0.0;
+      }
     }
     const Side x = s_now;
     now = next;
