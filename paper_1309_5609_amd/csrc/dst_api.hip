@@ -656,29 +656,29 @@ int build_bin(dst_ctx* ctx, Plan& P, hipStream_t st) {
   return DST_OK;
 }
 
-// The staged form of the rescan where it pays.  rec_bytes > 0: in buffers of the
-// setup that are done with, the sort's keys [R] for the staged keys and the
-// runs' records (rec_bytes each) for the lists, left out where these do not
-// hold them; 0 (another problem's setup uses those next): in buffers of its
-// own, left out where there is no memory for them.
-int build_stage(dst_ctx* ctx, Plan& P, size_t rec_bytes, hipStream_t st) {
-  const View& vc = P.S.v;
-  const dst::Runs& W = P.W;
+// Whether the plan's rescan is to be the staged one.
+bool stage_wanted(const dst_ctx* ctx, const Plan& P) {
+  if (ctx->unbin_bpw) return ctx->unbin_bpw == kStageBpw && dst::stage_can(P.S.v, P.W);
+  return dst::stage_pays(P.S.v, P.W);
+}
+
+// Entries of a staged plan's lists, and words they and their counts take.
+size_t stage_words(const Plan& P, size_t* all) {
+  const size_t blocks = (size_t)dst::stage_blocks(P.S.v), words = blocks * (size_t)dst::stage_cap(P.S.v);
+  *all = words + blocks;
+  return words;
+}
+
+// The staged form of the rescan with its keys [R] and lists in the buffers given.
+int build_stage(dst_ctx* ctx, Plan& P, uint32_t* key, uint32_t* list, hipStream_t st) {
   dst::Stage& S = P.stage;
-  if (ctx->unbin_bpw ? ctx->unbin_bpw != kStageBpw || !dst::stage_can(vc, W) : !dst::stage_pays(vc, W)) return DST_OK;
-  S.blocks = dst::stage_blocks(vc);
-  const size_t words = (size_t)S.blocks * (size_t)dst::stage_cap(vc);
-  if (rec_bytes > 0) {
-    if ((words + S.blocks) * sizeof(uint32_t) > (size_t)W.R * rec_bytes) return DST_OK;
-    S.key = W.keys[0];
-    S.list = static_cast<uint32_t*>(W.rec);
-  } else if (ws(ctx, "st_key", W.R, &S.key) != DST_OK || ws(ctx, "st_list", words + S.blocks, &S.list) != DST_OK) {
-    (void)hipGetLastError();
-    return DST_OK;
-  }
+  size_t all = 0;
+  S.blocks = dst::stage_blocks(P.S.v);
+  S.key = key;
+  S.list = list;
+  S.count = list + stage_words(P, &all);
   S.on = true;
-  S.count = S.list + words;
-  HIP_TRY(dst::stage_build(vc, W, S, st));
+  HIP_TRY(dst::stage_build(P.S.v, P.W, S, st));
   return DST_OK;
 }
 
@@ -1041,10 +1041,10 @@ int group_bpw(const dst_ctx* ctx, int kind) {
 
 // Independent problems with different pointing (the channels of a survey)
 // solved together: each problem gets its own run setup, right-hand side and
-// PCG state (workspace slots under its own prefix; the setup-only arrays are
-// freed once built), then every iteration advances all of them with one
-// launch per phase (bin, rescan, step length, update, beta, p) over one
-// list of workgroups, replayed from one captured graph; a problem that has
+// PCG state (workspace slots under its own prefix; one set of the setup-only
+// arrays serves all in turn), then every iteration advances all of them with
+// one launch per phase (bin and rescan one per kind, step length, update,
+// direction) over one list of workgroups, replayed from one captured graph; a problem that has
 // stopped leaves its workgroups idle.  Outputs as dst_solve per problem.
 int solve_uneven(dst_ctx* ctx, const dst_problem* problems, const std::vector<int>& idx, const dst_solve_opts& opts,
                  int check_every, const BatchOut& out, hipStream_t st, int* status) {
@@ -1075,9 +1075,14 @@ int solve_uneven(dst_ctx* ctx, const dst_problem* problems, const std::vector<in
     }
   } pg{ctx};
   CgCtl* ctls = nullptr;
+  dst::GroupProblem* gp_dev = nullptr;
+  uint32_t *vec_dev = nullptr, *ranges_dev = nullptr;
   {
     ctx->ws_prefix.clear();
     DST_TRY(ws(ctx, "grp_ctl", kMaxGroup, &ctls));
+    DST_TRY(ws(ctx, "grp_desc", n, &gp_dev));
+    DST_TRY(ws(ctx, "grp_vec", n + 1, &vec_dev));
+    DST_TRY(ws(ctx, "grp_ranges", 2 * (n + 4), &ranges_dev));
   }
   // arrays only the setup reads: one set serves every problem's setup in turn
   for (const char* name : {"r_tcount", "r_toff", "r_rec", "r_raw", "r_keys0", "r_keys1", "r_vals0", "r_vals1",
@@ -1098,7 +1103,6 @@ int solve_uneven(dst_ctx* ctx, const dst_problem* problems, const std::vector<in
     DST_TRY(ws(ctx, "cg_b", N, &m.b));
     DST_TRY(build_runs_plan(ctx, &pr, m.P, pr.tod, &m.sd4, &m.md4, m.b, st));
     DST_TRY(build_bin(ctx, m.P, st));
-    DST_TRY(build_stage(ctx, m.P, 0, st));
     // the closing operator of each problem: its own lanes per pixel (32 for all took 4.2 ms of an 80 ms survey batch)
     m.P.lpp = dst::bin_lanes_for(m.P.W.R, m.P.W.n_obs, m.P.dense_t, v.iqu);
     DST_TRY(ws(ctx, "cg_a", N, &m.a));
@@ -1138,6 +1142,31 @@ int solve_uneven(dst_ctx* ctx, const dst_problem* problems, const std::vector<in
   for (int k = 0; k < n; ++k) order[k] = k;
   std::stable_sort(order.begin(), order.end(),
                    [&](int x, int y) { return kind_of(M[x].P.S.v) < kind_of(M[y].P.S.v); });
+  // Staged rescans, a kind at a time since one launch serves all its problems:
+  // built only where every one of them wants it, after all other arrays, and
+  // given up where there is no memory for the lists of all.
+  for (int K = 0; K < 4; ++K) {
+    bool all = true;
+    for (const Member& m : M) all = all && (kind_of(m.P.S.v) != K || stage_wanted(ctx, m.P));
+    for (Member& m : M) {
+      if (!all || kind_of(m.P.S.v) != K) continue;
+      ctx->ws_prefix = m.prefix;
+      uint32_t *key = nullptr, *list = nullptr;
+      size_t words = 0;
+      (void)stage_words(m.P, &words);
+      all = ws(ctx, "st_key", m.P.W.R, &key) == DST_OK && ws(ctx, "st_list", words, &list) == DST_OK;
+      if (all) DST_TRY(build_stage(ctx, m.P, key, list, st));
+    }
+    if (all) continue;
+    for (Member& m : M) {
+      if (kind_of(m.P.S.v) != K) continue;
+      ctx->ws_prefix = m.prefix;
+      m.P.stage.on = false;
+      for (const char* name : {"st_key", "st_list"}) ctx->ws.release(ws_name(ctx, name));
+    }
+    ctx->err.clear();
+  }
+  ctx->ws_prefix.clear();
   std::vector<dst::GroupProblem> gp(n);
   std::vector<int64_t> n_runs(n);
   std::vector<uint32_t> vec_start(n + 1, 0u);
@@ -1195,9 +1224,8 @@ int solve_uneven(dst_ctx* ctx, const dst_problem* problems, const std::vector<in
     // lanes per pixel of the kind's binning from its runs per observed pixel
     int64_t runs = 0, obs = 0;
     bool lds = true;
-    sl.staged = true;
+    sl.staged = gp[sl.first].stage.on;  // of all its problems or none
     for (int j = 0; j < sl.count; ++j) {
-      sl.staged = sl.staged && gp[sl.first + j].stage.on;
       runs += n_runs[sl.first + j];
       obs += gp[sl.first + j].v.n_pix;
       lds = lds && M[order[sl.first + j]].P.bin.form == dst::BIN_LDS;
@@ -1229,11 +1257,6 @@ int solve_uneven(dst_ctx* ctx, const dst_problem* problems, const std::vector<in
     sl.bin_total = bs[sl.count];
     sl.unbin_total = us[sl.count];
   }
-  dst::GroupProblem* gp_dev = nullptr;
-  uint32_t *vec_dev = nullptr, *ranges_dev = nullptr;
-  DST_TRY(ws(ctx, "grp_desc", n, &gp_dev));
-  DST_TRY(ws(ctx, "grp_vec", n + 1, &vec_dev));
-  DST_TRY(ws(ctx, "grp_ranges", std::max<size_t>(ranges.size(), 1), &ranges_dev));
   HIP_TRY(hipMemcpyAsync(gp_dev, gp.data(), n * sizeof(dst::GroupProblem), hipMemcpyHostToDevice, st));
   HIP_TRY(hipMemcpyAsync(vec_dev, vec_start.data(), (n + 1) * sizeof(uint32_t), hipMemcpyHostToDevice, st));
   HIP_TRY(hipMemcpyAsync(ranges_dev, ranges.data(), ranges.size() * sizeof(uint32_t), hipMemcpyHostToDevice, st));
@@ -1802,7 +1825,12 @@ int dst_solve(dst_ctx* ctx, const dst_problem* prob, const dst_solve_opts* opts_
   DST_TRY(build_plan(ctx, prob, P, prob->tod, &sd4, &md4, b, st));
   if (P.runs) {
     DST_TRY(build_bin(ctx, P, st));
-    DST_TRY(build_stage(ctx, P, dst::run_record_bytes(v.rowQ >= 0, v.iqu, prob->tod != nullptr, v.w[1] == v.w[2]), st));
+    // in buffers of the setup that are done with, where the lists fit: the sort's keys and the runs' records
+    size_t words = 0;
+    (void)stage_words(P, &words);
+    const size_t rec = dst::run_record_bytes(v.rowQ >= 0, v.iqu, prob->tod != nullptr, v.w[1] == v.w[2]);
+    if (stage_wanted(ctx, P) && words * sizeof(uint32_t) <= (size_t)P.W.R * rec)
+      DST_TRY(build_stage(ctx, P, P.W.keys[0], static_cast<uint32_t*>(P.W.rec), st));
   }
   Setup& S = P.S;
   const View& vc = S.v;

@@ -65,6 +65,12 @@ class Workspace {
     return it == bufs_.end() ? 0 : it->second.bytes;
   }
 
+  // Frees buffer `name`, unless a graph holds it.
+  void release(const std::string& name) {
+    const auto it = bufs_.find(name);
+    if (it != bufs_.end() && !it->second.in_graph) drop(it->second);
+  }
+
   // End of the context: frees everything.
   void clear() {
     for (auto& kv : bufs_)
