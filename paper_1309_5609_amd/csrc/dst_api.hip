@@ -69,8 +69,10 @@ struct dst_ctx {
   dst::GmStatus* gm_dev = nullptr;
   hipEvent_t gm_ev[2] = {nullptr, nullptr};
   // instantiated iteration graphs kept between solves (single solve,
-  // shared-pointing batch, problem group), updated in place by each capture
-  hipGraphExec_t graphs[3] = {nullptr, nullptr, nullptr};
+  // shared-pointing batch, problem group, single solve with a kernel for the
+  // step length), updated in place by each capture
+  hipGraphExec_t graphs[4] = {nullptr, nullptr, nullptr, nullptr};
+  bool several = false;       // the last single solve had several components: the next is expected to (graphs[3])
   hipStream_t cap = nullptr;  // private stream on which iteration graphs are captured
   int unbin_bpw = 0;          // launch shape of the run rescan (baselines per wavefront; 0 by size)
   int bin_lpp = 0;            // launch shape of the run binning (lanes per pixel; 0 by size)
@@ -1863,12 +1865,14 @@ int dst_solve(dst_ctx* ctx, const dst_problem* prob, const dst_solve_opts* opts_
   // PCG iterations: pixel-major bin + inverse (m = M^-1 A^T W F p) -> rescan and
   // baseline sums (q = K p) -> a, r, z update with the step length -> p and its
   // copy with beta.  The step length has a kernel of its own when the rescan's
-  // partials are many or several components are projected (known on the host
-  // once the setup has run: until then one is assumed).
+  // partials are many or several components are projected.  Their number is
+  // known on the host once the setup has run; until then the last solve's is
+  // assumed, since a second capture after it leaves the GPU idle (6 hours of two
+  // components, 20 iterations: 1.27 ms with it, 1.16 without).  Either form gives the same bits.
   const int64_t n_step = P.stage.on ? dst::staged_parts(vc)
                          : P.runs      ? dst::unbin_runs_parts(vc, P.bpw)
                                        : vc.n_b;
-  bool own_step = n_step <= dst::kStepParts;
+  bool own_step = n_step <= dst::kStepParts && !ctx->several;
   auto one_iteration = [&](hipStream_t s, bool timed) -> int {
     hipEvent_t e[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};
     if (timed) {
@@ -1897,7 +1901,7 @@ int dst_solve(dst_ctx* ctx, const dst_problem* prob, const dst_solve_opts* opts_
   } gg;
   const bool use_graph = !use_gmres && !(opts.flags & (DST_SOLVE_NO_GRAPH | DST_SOLVE_PROFILE));
   auto capture = [&]() {
-    return capture_graph_kept(ctx, 0, check_every, [&](hipStream_t s) { return one_iteration(s, false); }, &gg.exec);
+    return capture_graph_kept(ctx, own_step ? 0 : 3, check_every, [&](hipStream_t s) { return one_iteration(s, false); }, &gg.exec);
   };
   if (use_graph) DST_TRY(capture());
   HIP_TRY(hipEventRecord(ev[1], st));
@@ -1909,8 +1913,9 @@ int dst_solve(dst_ctx* ctx, const dst_problem* prob, const dst_solve_opts* opts_
   DST_TRY(finish(ctx, &S, st));
   const int ncomp = ctx->rb_host->ncomp[0];
   if (info) info->n_components = ncomp;
-  if (ncomp > 1 && own_step) {
-    own_step = false;
+  ctx->several = ncomp > 1;
+  if (const bool own = n_step <= dst::kStepParts && !ctx->several; own != own_step) {
+    own_step = own;
     if (use_graph) DST_TRY(capture());
   }
   {
