@@ -94,6 +94,24 @@ __device__ __forceinline__ double next_lane(double v) {
   return __hiloint2double(next_lane(__double2hiint(v)), next_lane(__double2loint(v)));
 }
 
+// A wavefront's groups of LPP lanes, one list of `len` entries each (the same on
+// every lane of a group, every lane active): whether lists marked `deep` are
+// better swept by all 64 lanes one after another.  They are unless the groups'
+// lists are about equally long (30 M samples on 768 pixels, all deep: setup +0.1
+// ms when swept so).
+template <int LPP>
+__device__ __forceinline__ bool share_deep(bool deep, uint32_t len) {
+  if (__ballot(deep) == 0ull) return false;
+  uint32_t most = len, all = deep ? len : 0u;  // all: LPP times the deep lists' sum, in units of 64 entries
+  all = (all + 63u) / 64u;
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    most = max(most, (uint32_t)__shfl_xor((int)most, off, 64));
+    all += (uint32_t)__shfl_xor((int)all, off, 64);
+  }
+  return deep && (uint64_t)all * 4u < (uint64_t)most * 3u;
+}
+
 // Inverse (QQ, QU, UU) of a pixel's QU block [[a, b], [b, d]]; false, with inv
 // untouched, unless its smaller eigenvalue is positive and at least rcond_cut
 // times the larger.

@@ -220,7 +220,7 @@ __device__ __forceinline__ void bin_body(double* p_lds, const BinRuns& B, const 
     range(c + 2 * step, f0, f1);
     double acc[3] = {0.0, 0.0, 0.0};
     add(group, now, g, a0 + sub, a1, acc);
-    const bool deep = a1 - a0 > (uint32_t)(kDeepSteps * LPP * U);
+    const bool deep = dev::share_deep<LPP>(a1 - a0 > (uint32_t)(kDeepSteps * LPP * U), a1 - a0);
     if (!deep) more(group, a0 + sub + LPP * U, a1, acc);
     for (unsigned long long m = __ballot(deep && sub == 0); m != 0; m &= m - 1) {
       const int src = __ffsll(m) - 1;

@@ -480,7 +480,7 @@ __global__ void __launch_bounds__(kBlock) k_compact(const uint32_t* __restrict__
 // samples T/q/u, a pixel with 2 % of them: setup 4.9 -> 2.5 ms.
 constexpr int kDeepSteps = 16;
 template <typename RT, bool HAS_T, bool HAS_QU, bool IQU, bool TOD, bool EQ, int LPP>
-__global__ void __launch_bounds__(kBlock) k_pixels_from_runs(
+__global__ void __launch_bounds__(kBlock, IQU ? 1 : 4) k_pixels_from_runs(
     View v, int64_t n_obs, const uint32_t* __restrict__ order, const int64_t* __restrict__ seg,
     const uint32_t* __restrict__ rperm, const void* __restrict__ rec_, const RT* __restrict__ tcs, double rcond_cut,
     int nb, uint32_t* __restrict__ pkey, RT* __restrict__ pcs, const int64_t* __restrict__ pstart,
@@ -515,21 +515,21 @@ __global__ void __launch_bounds__(kBlock) k_pixels_from_runs(
     for (int i = 0; i < NA; ++i) acc[i] = 0.0;
     // runs first, first + N, ... of [j0, j1), pixel-order places from d0 on, into acc
     auto sweep = [&](auto lanes, int64_t j0, int64_t j1, int64_t d0, int64_t first, double (&acc)[NA]) {
-      constexpr int N = decltype(lanes)::value;
-      for (int64_t jb = first; jb < j1; jb += N * U) {
-        uint32_t q[U];
+      constexpr int N = decltype(lanes)::value, K = N == 64 ? U / 2 : U;  // (fewer registers for the rare sweep)
+      for (int64_t jb = first; jb < j1; jb += N * K) {
+        uint32_t q[K];
 #pragma unroll
-        for (int u = 0; u < U; ++u) q[u] = jb + N * u < j1 ? rperm[jb + N * u] : 0u;
-        Rec xs[U];
-        CS2<RT> ang[U];
+        for (int u = 0; u < K; ++u) q[u] = jb + N * u < j1 ? rperm[jb + N * u] : 0u;
+        Rec xs[K];
+        CS2<RT> ang[K];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
+        for (int u = 0; u < K; ++u) {
           if (jb + N * u >= j1) continue;
           xs[u] = rec[q[u]];
           if (ANG) ang[u] = reinterpret_cast<const CS2<RT>*>(tcs)[q[u]];
         }
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
+        for (int u = 0; u < K; ++u) {
           const int64_t j = jb + N * u;
           if (j >= j1) break;
           const Rec& x = xs[u];
@@ -564,7 +564,7 @@ __global__ void __launch_bounds__(kBlock) k_pixels_from_runs(
         }
       }
     };
-    const bool deep = !IQU && j1 - j0 > (int64_t)kDeepSteps * LPP * U;
+    const bool deep = !IQU && dev::share_deep<LPP>(j1 - j0 > (int64_t)kDeepSteps * LPP * U, (uint32_t)(j1 - j0));
     if (!deep) sweep(std::integral_constant<int, LPP>{}, j0, j1, d0, j0 + sub, acc);
 #pragma unroll
     for (int off = LPP / 2; off > 0; off >>= 1) {
