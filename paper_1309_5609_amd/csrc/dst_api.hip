@@ -72,6 +72,8 @@ struct dst_ctx {
   // shared-pointing batch, problem group, single solve with a kernel for the
   // step length), updated in place by each capture
   hipGraphExec_t graphs[4] = {nullptr, nullptr, nullptr, nullptr};
+  int64_t bk_pix = 0;         // pixels that the one-shot calls' reserve holds, when given_back() was bk_given
+  uint64_t bk_given = 0;
   bool several = false;       // the last single solve had several components: the next is expected to (graphs[3])
   hipStream_t cap = nullptr;  // private stream on which iteration graphs are captured
   int unbin_bpw = 0;          // launch shape of the run rescan (baselines per wavefront; 0 by size)
@@ -134,10 +136,11 @@ int ws_get(dst_ctx* ctx, const char* name, size_t bytes, void** out) {
   return DST_OK;
 }
 
-// Start of a call's work on `st`.
-void ws_begin(dst_ctx* ctx, hipStream_t st) {
+// Start of a call's work on `st`; one that waits for its stream cannot be captured.
+enum { CALL_WAITS, CALL_ASYNC };
+void ws_begin(dst_ctx* ctx, hipStream_t st, int kind) {
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(st, &cap) != hipSuccess) {
+  if (kind == CALL_ASYNC && hipStreamIsCapturing(st, &cap) != hipSuccess) {
     (void)hipGetLastError();
     cap = hipStreamCaptureStatusNone;
   }
@@ -309,7 +312,10 @@ hipError_t copy4to3(double* dst3, const double* src4, int64_t n_pix, hipStream_t
 // device gets by with smaller pieces.
 int bucket_space(dst_ctx* ctx, const View& v, bool data, dst::BucketWork& W, bool* fits) {
   const dst::BucketBytes need = dst::bucket_bytes(v, data);
-  const dst::BucketReserve keep = dst::bucket_reserve(v.n_pix);
+  const bool captured = ctx->ws.captured();
+  // whether the reserve has to be looked after (2 us otherwise)
+  const bool reserve = !captured && (v.n_pix > ctx->bk_pix || ctx->ws.given_back() != ctx->bk_given);
+  const dst::BucketReserve keep = reserve ? dst::bucket_reserve(v.n_pix) : dst::BucketReserve{};
   struct Part {
     const char* name;
     size_t per, least;
@@ -317,7 +323,6 @@ int bucket_space(dst_ctx* ctx, const View& v, bool data, dst::BucketWork& W, boo
   } parts[3] = {{"bk_off", need.off, keep.off, nullptr},
                 {"bk_rec", need.rec, keep.rec, nullptr},
                 {"bk_rec2", need.rec2, keep.rec2, nullptr}};
-  const bool captured = ctx->ws.captured();
   W.n_chunks = need.best_chunks;
   *fits = true;
   if (captured) {
@@ -334,14 +339,18 @@ int bucket_space(dst_ctx* ctx, const View& v, bool data, dst::BucketWork& W, boo
     const int rc = ws_get(ctx, "bk_acc_hits", hits, reinterpret_cast<void**>(&W.acc_hits));
     return rc != DST_OK ? rc : ws_get(ctx, "bk_acc", acc, reinterpret_cast<void**>(&W.acc));
   };
-  if (!captured && sums(std::max(need.acc_hits, keep.acc_hits), std::max(need.acc, keep.acc)) != DST_OK)
+  bool held = true;  // the reserve is
+  if (reserve && sums(keep.acc_hits, keep.acc) != DST_OK) {
     W.acc = nullptr;
+    held = false;
+  }
   for (Part& p : parts) {
-    size_t least = captured ? 0 : p.least;
+    size_t least = p.least;
     while (p.per > 0 || least > 0) {
       const size_t bytes = (size_t)W.n_chunks * p.per;
       const int rc = ws_get(ctx, p.name, std::max(bytes, least), &p.ptr);
       if (rc == DST_OK) break;
+      held = false;
       if (least > bytes) {
         least = 0;
         continue;
@@ -351,14 +360,16 @@ int bucket_space(dst_ctx* ctx, const View& v, bool data, dst::BucketWork& W, boo
     }
   }
   if (W.n_chunks < need.n_chunks && !W.acc) DST_TRY(sums(need.acc_hits, need.acc));
-  if (!captured) {
+  if (reserve) {
     Setup S;
     double* s4;
-    if (dst::buckets_fit_any(v.n_pix))
-      (void)ws(ctx, "valid", v.n_pix, &S.valid);
-    else
-      (void)hold_atomic(ctx, v.n_pix, S, &s4);
+    const int rc = dst::buckets_fit_any(v.n_pix) ? ws(ctx, "valid", v.n_pix, &S.valid)
+                                                 : hold_atomic(ctx, v.n_pix, S, &s4);
+    held = held && rc == DST_OK;
+    ctx->bk_pix = std::max(ctx->bk_pix, v.n_pix);
+    ctx->bk_given = ctx->ws.given_back();
   }
+  if (!held) ctx->bk_pix = 0;
   ctx->err.clear();
   W.off = static_cast<uint16_t*>(parts[0].ptr);
   W.rec = parts[1].ptr;
@@ -836,7 +847,7 @@ int solve_group(dst_ctx* ctx, const dst_problem* problems, const std::vector<int
   const bool use_graph = !(opts.flags & (DST_SOLVE_NO_GRAPH | DST_SOLVE_PROFILE));
   View v{};
   DST_TRY(check_problem(ctx, &p0, true, v));
-  ws_begin(ctx, st);
+  ws_begin(ctx, st, CALL_WAITS);
   EventSet evs;
   hipEvent_t ev[4];
   for (auto& e : ev) HIP_TRY(evs.add(&e));
@@ -1064,7 +1075,7 @@ int solve_uneven(dst_ctx* ctx, const dst_problem* problems, const std::vector<in
     int32_t ncomp = 0;
   };
   std::vector<Member> M(n);
-  ws_begin(ctx, st);
+  ws_begin(ctx, st, CALL_WAITS);
   EventSet evs;
   hipEvent_t ev[4];
   for (auto& e : ev) HIP_TRY(evs.add(&e));
@@ -1643,7 +1654,7 @@ int dst_pixel_setup(dst_ctx* ctx, const dst_problem* prob, int32_t* hits_out, do
   ctx->err.clear();
   DeviceGuard g(ctx->device);
   hipStream_t st = static_cast<hipStream_t>(stream);
-  ws_begin(ctx, st);
+  ws_begin(ctx, st, CALL_ASYNC);
   dst::BucketOut o;
   o.hits = hits_out;
   o.blocks = blocks_out;
@@ -1666,7 +1677,7 @@ int dst_bin(dst_ctx* ctx, const dst_problem* prob, const double* baselines, uint
   ctx->err.clear();
   DeviceGuard g(ctx->device);
   hipStream_t st = static_cast<hipStream_t>(stream);
-  ws_begin(ctx, st);
+  ws_begin(ctx, st, CALL_ASYNC);
   dst::BucketOut o;
   o.hits = hits_out;
   ((flags & DST_BIN_MAP) ? o.map3 : o.sum3) = map_out;
@@ -1692,7 +1703,6 @@ int dst_bin_noalloc(dst_ctx* ctx, const dst_problem* prob, const double* baselin
   ctx->err.clear();
   DeviceGuard g(ctx->device);
   hipStream_t st = static_cast<hipStream_t>(stream);
-  ws_begin(ctx, st);
   Setup S;
   S.v = v;
   double* s4 = nullptr;
@@ -1709,7 +1719,6 @@ int dst_unbin(dst_ctx* ctx, const dst_problem* prob, const double* map, double* 
   ctx->err.clear();
   DeviceGuard g(ctx->device);
   hipStream_t st = static_cast<hipStream_t>(stream);
-  ws_begin(ctx, st);
   HIP_TRY(dst::launch_scan(v, prob->psi_dtype == DST_F32, map, tod_out, ctx->err_dev, st));
   return issued(ctx);
 }
@@ -1723,7 +1732,7 @@ int dst_baseline_reduce(dst_ctx* ctx, const dst_problem* prob, const void* x, do
   ctx->err.clear();
   DeviceGuard g(ctx->device);
   hipStream_t st = static_cast<hipStream_t>(stream);
-  ws_begin(ctx, st);
+  ws_begin(ctx, st, CALL_ASYNC);
   Setup S;
   S.v = v;
   dst::BucketOut o;
@@ -1745,7 +1754,7 @@ int dst_residual(dst_ctx* ctx, const dst_problem* prob, const double* a, double*
   ctx->err.clear();
   DeviceGuard g(ctx->device);
   hipStream_t st = static_cast<hipStream_t>(stream);
-  ws_begin(ctx, st);
+  ws_begin(ctx, st, CALL_ASYNC);
   Setup S;
   S.v = v;
   double* m4 = nullptr;
@@ -1769,7 +1778,7 @@ int dst_apply_operator(dst_ctx* ctx, const dst_problem* prob, const double* vin,
   ctx->err.clear();
   DeviceGuard g(ctx->device);
   hipStream_t st = static_cast<hipStream_t>(stream);
-  ws_begin(ctx, st);
+  ws_begin(ctx, st, CALL_WAITS);
   Plan P;
   P.full = v;
   DST_TRY(build_plan(ctx, prob, P, nullptr, nullptr, nullptr, nullptr, st));
@@ -1801,7 +1810,7 @@ int dst_solve(dst_ctx* ctx, const dst_problem* prob, const dst_solve_opts* opts_
   ctx->err.clear();
   DeviceGuard g(ctx->device);
   hipStream_t st = static_cast<hipStream_t>(stream);
-  ws_begin(ctx, st);
+  ws_begin(ctx, st, CALL_WAITS);
 
   hipEvent_t ev[4];
   for (auto& e : ev) HIP_TRY(hipEventCreate(&e));
@@ -1867,7 +1876,7 @@ int dst_solve(dst_ctx* ctx, const dst_problem* prob, const dst_solve_opts* opts_
   // copy with beta.  The step length has a kernel of its own when the rescan's
   // partials are many or several components are projected.  Their number is
   // known on the host once the setup has run; until then the last solve's is
-  // assumed, since a second capture after it leaves the GPU idle (6 hours of two
+  // assumed, since a second capture after it leaves the GPU idle (600,000 samples of two
   // components, 20 iterations: 1.27 ms with it, 1.16 without).  Either form gives the same bits.
   const int64_t n_step = P.stage.on ? dst::staged_parts(vc)
                          : P.runs      ? dst::unbin_runs_parts(vc, P.bpw)
@@ -2057,7 +2066,7 @@ int dst_solve_batched(dst_ctx* ctx, int32_t n_problems, const dst_problem* probl
   ctx->err.clear();
   DeviceGuard g(ctx->device);
   hipStream_t st = static_cast<hipStream_t>(stream);
-  ws_begin(ctx, st);
+  ws_begin(ctx, st, CALL_WAITS);
   // groups of problems that share the operator, in order of first appearance
   std::vector<std::vector<int>> groups;
   for (int i = 0; i < n_problems; ++i) {
@@ -2146,7 +2155,7 @@ int dst_pointing_expand(dst_ctx* ctx, const dst_scan* scan, int64_t nside, int64
   ctx->err.clear();
   DeviceGuard g(ctx->device);
   hipStream_t st = static_cast<hipStream_t>(stream);
-  ws_begin(ctx, st);
+  ws_begin(ctx, st, CALL_WAITS);
   std::vector<double> tab;
   dst::scan_period_table(s, n_per, tab);
   double* dtab = nullptr;
@@ -2174,7 +2183,7 @@ int dst_noise_generate(dst_ctx* ctx, uint64_t seed, uint64_t stream_id, int64_t 
   ctx->err.clear();
   DeviceGuard g(ctx->device);
   hipStream_t st = static_cast<hipStream_t>(stream);
-  ws_begin(ctx, st);
+  ws_begin(ctx, st, CALL_WAITS);
   double2* buf = nullptr;
   DST_TRY(ws(ctx, "noise_buf", (size_t)dst::noise_buffer_count(segment), &buf));
   double2* tw = nullptr;

@@ -35,6 +35,8 @@ class Workspace {
     ++call_;
   }
   bool captured() const { return captured_; }
+  // Times that memory ran out and buffers were given back.
+  uint64_t given_back() const { return given_back_; }
 
   // Buffer `name` of at least `bytes`; nullptr, with nothing held under the
   // name, when it cannot be had (a buffer in a graph stays).
@@ -97,6 +99,7 @@ class Workspace {
       drop(b);
       any = true;
     }
+    given_back_ += any;
     return any;
   }
   void drop(Buf& b) {
@@ -107,7 +110,7 @@ class Workspace {
   Alloc alloc_;
   Free free_;
   bool captured_ = false;
-  uint64_t call_ = 0;
+  uint64_t call_ = 0, given_back_ = 0;
   std::unordered_map<std::string, Buf> bufs_;
   std::vector<void*> retired_;  // outgrown buffers that a graph holds
 };
