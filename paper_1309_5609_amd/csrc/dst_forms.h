@@ -19,8 +19,9 @@ struct BinShape {
   int lpp = 0;
   uint32_t blocks = 0;
 };
-// mode: a form (BIN_LDS wherever the baselines fit, BIN_PIPE wherever there are
-// q/u streams, else plain), or -1: the fastest for the problem's sizes.
+// mode: a form (BIN_LDS wherever the baselines fit and BIN_PIPE wherever there are
+// q/u streams, else plain; radiometers: plain), or -1: the fastest for the
+// problem's sizes.
 BinShape bin_shape(const View& vc, const Runs& W, int mode);
 // Lanes per pixel for `runs` runs over n_obs pixels (a lane takes four runs
 // per step, eight without angles); whether that is sparse enough for BIN_PIPE;

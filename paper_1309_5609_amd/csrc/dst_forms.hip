@@ -12,7 +12,8 @@
 // N_side 512 (18 M runs, 6,720 baselines): solve 10.6 -> 9.3 ms; per launch, 4
 // days there 67 us less, 7 days FP64 at N_side 256 26 us less, 10 and 25 days of
 // intensity at N_side 512 17 and 21 us less; no gain below 2 M runs or 65,536
-// pixels (7 days at N_side 64: 3 us more), nor with radiometer rows.
+// pixels (7 days at N_side 64: 3 us more), nor for radiometers, which keep the
+// plain form.
 // Baselines beyond one LDS were tried in bands (the runs copied band by band, a
 // pixel's sums going through the map): 30 days FP64 in 7 bands 0.24 against
 // 0.215 ms, 90 days of intensity in 4 bands 0.40 against 0.50 ms a launch but
@@ -51,7 +52,7 @@ constexpr int kU = 4;  // runs per lane whose loads are issued together (twice t
 constexpr int kDeepSteps = 16;
 
 // LDS values per baseline.
-int columns_of(const View& v) { return v.iqu ? 1 : (v.rowT >= 0 ? 1 : 0) + (v.rowQ >= 0 ? 2 : 0); }
+int columns_of(const View& v) { return (v.rowT >= 0 ? 1 : 0) + (v.rowQ >= 0 ? 2 : 0); }
 
 // Sum over groups of LPP lanes (every lane gets it), by DPP moves up to 16.
 template <int LPP, int N>
@@ -76,12 +77,11 @@ __device__ __forceinline__ void group_sum(double (&v)[N]) {
 }
 
 // block of grid: the workgroup's place in its problem's launch.
-template <typename RT, bool HT, bool HQ, bool IQU, int LPP, bool LDS>
+template <typename RT, bool HT, bool HQ, int LPP, bool LDS>
 __device__ __forceinline__ void bin_body(double* p_lds, const BinRuns& B, const double* __restrict__ pw4,
                                          const double* __restrict__ Minv4, const uint8_t* __restrict__ valid,
                                          double* __restrict__ m4, uint32_t block, uint32_t grid) {
-  constexpr bool TONLY = HT && !HQ && !IQU;
-  constexpr bool ANG = HQ || IQU;
+  constexpr bool TONLY = HT && !HQ;
   constexpr int PPW = 64 / LPP, U = TONLY ? 2 * kU : kU;
   const int lane = lane_id(), wave = threadIdx.x >> 6;
   const int grp = lane / LPP, sub = lane % LPP;
@@ -95,7 +95,7 @@ __device__ __forceinline__ void bin_body(double* p_lds, const BinRuns& B, const 
       } else {
         const double2* q = reinterpret_cast<const double2*>(pw4 + 4 * (int64_t)i);
         const double2 x = q[0];
-        if (HT || IQU) p_lds[i] = x.x;
+        if (HT) p_lds[i] = x.x;
         if (HQ) {
           p_lds[(HT ? 1 : 0) * n_b + i] = x.y;
           p_lds[(HT ? 2 : 1) * n_b + i] = q[1].x;
@@ -131,23 +131,22 @@ __device__ __forceinline__ void bin_body(double* p_lds, const BinRuns& B, const 
     for (int u = 0; u < U; ++u) {
       const uint32_t jj = j + N * u < j1 ? j + N * u : 0u;
       f.key[u] = B.key[jj];
-      if (ANG) f.ang[u] = cs[jj];
+      if (HQ) f.ang[u] = cs[jj];
     }
   };
   struct Side {
     uint8_t ok;
-    double2 i01, i23, i45;
+    double2 i01, i23;
   };
   auto side = [&](int64_t c, Side& x) {
     const int64_t cc = c < c1 ? c : c1 - 1;
     x.ok = valid[cc];
-    const double2* ip = reinterpret_cast<const double2*>(Minv4 + (IQU ? 8 : 4) * cc);
+    const double2* ip = reinterpret_cast<const double2*>(Minv4 + 4 * cc);
     if (TONLY) {
       x.i01.x = ip[0].x;
     } else {
       x.i01 = ip[0];
       x.i23 = ip[1];
-      if (IQU) x.i45 = ip[2];  // (00, 01), (02, 11), (12, 22)
     }
   };
   struct Gathered {
@@ -176,14 +175,7 @@ __device__ __forceinline__ void bin_body(double* p_lds, const BinRuns& B, const 
       const bool in = j + N * u < j1;
       const int i = in ? (int)(f.key[u] >> nb) : 0;
       const double n = in ? (double)((f.key[u] & nmask) + 1u) : 0.0;
-      const double C = ANG && in ? (double)f.ang[u].x : 0.0, S = ANG && in ? (double)f.ang[u].y : 0.0;
-      if (IQU) {
-        const double x = LDS ? pT[i] : g.x[u].x;
-        acc[0] += n * x;
-        acc[1] += C * x;
-        acc[2] += S * x;
-        continue;
-      }
+      const double C = HQ && in ? (double)f.ang[u].x : 0.0, S = HQ && in ? (double)f.ang[u].y : 0.0;
       if (HT) acc[0] += n * (LDS ? pT[i] : g.x[u].x);
       if (HQ) {
         const double xq = LDS ? pq[i] : g.x[u].y, xu = LDS ? pu[i] : g.u[u];
@@ -247,52 +239,41 @@ __device__ __forceinline__ void bin_body(double* p_lds, const BinRuns& B, const 
       m4[c] = x.i01.x * acc[0];
       continue;
     }
-    double2 r0, r1;
-    if (IQU) {
-      r0.x = x.i01.x * acc[0] + x.i01.y * acc[1] + x.i23.x * acc[2];
-      r0.y = x.i01.y * acc[0] + x.i23.y * acc[1] + x.i45.x * acc[2];
-      r1.x = x.i23.x * acc[0] + x.i45.x * acc[1] + x.i45.y * acc[2];
-    } else {
-      r0.x = x.i01.x * acc[0];
-      r0.y = x.i01.y * acc[1] + x.i23.x * acc[2];
-      r1.x = x.i23.x * acc[1] + x.i23.y * acc[2];
-    }
-    r1.y = 0.0;
     double2* mp = reinterpret_cast<double2*>(m4 + 4 * c);
-    mp[0] = r0;
-    mp[1] = r1;
+    mp[0] = make_double2(x.i01.x * acc[0], x.i01.y * acc[1] + x.i23.x * acc[2]);
+    mp[1] = make_double2(x.i23.x * acc[1] + x.i23.y * acc[2], 0.0);
   }
 }
 
-template <typename RT, bool HT, bool HQ, bool IQU, int LPP>
+template <typename RT, bool HT, bool HQ, int LPP>
 __global__ void __launch_bounds__(kThreads) k_bin_lds(BinRuns B, const double* __restrict__ pw4,
                                                        const double* __restrict__ Minv4,
                                                        const uint8_t* __restrict__ valid, double* __restrict__ m4,
                                                        const CgCtl* __restrict__ gate) {
   __shared__ double p_lds[kLdsDoubles];
   if (gate && gate->done) return;
-  bin_body<RT, HT, HQ, IQU, LPP, true>(p_lds, B, pw4, Minv4, valid, m4, blockIdx.x, gridDim.x);
+  bin_body<RT, HT, HQ, LPP, true>(p_lds, B, pw4, Minv4, valid, m4, blockIdx.x, gridDim.x);
 }
 
-template <typename RT, bool HT, bool HQ, bool IQU, int LPP>
+template <typename RT, bool HT, bool HQ, int LPP>
 __global__ void __launch_bounds__(kPipeThreads, 4) k_bin_pipe(BinRuns B, const double* __restrict__ pw4,
                                                        const double* __restrict__ Minv4,
                                                        const uint8_t* __restrict__ valid, double* __restrict__ m4,
                                                        const CgCtl* __restrict__ gate) {
   if (gate && gate->done) return;
-  bin_body<RT, HT, HQ, IQU, LPP, false>(nullptr, B, pw4, Minv4, valid, m4, blockIdx.x, gridDim.x);
+  bin_body<RT, HT, HQ, LPP, false>(nullptr, B, pw4, Minv4, valid, m4, blockIdx.x, gridDim.x);
 }
 
 template <typename RT, int KIND, int LPP>
 __global__ void __launch_bounds__(kThreads) k_group_bin_lds(GroupLaunch G) {
-  constexpr bool HT = KIND == GK_T || KIND == GK_TQU, HQ = KIND == GK_QU || KIND == GK_TQU, HI = KIND == GK_IQU;
+  constexpr bool HT = KIND == GK_T || KIND == GK_TQU, HQ = KIND == GK_QU || KIND == GK_TQU;
   __shared__ double p_lds[kLdsDoubles];
   const GroupSlice& S = G.kind[KIND];
   const uint32_t b = blockIdx.x;
   const int j = group_of(S.bin_start, S.count, b);
   const GroupProblem& P = G.prob[S.first + j];
   if (P.ctl->done) return;
-  bin_body<RT, HT, HQ, HI, LPP, true>(p_lds, P.bin, P.pw4, P.Minv4, P.valid, P.m4, b - S.bin_start[j],
+  bin_body<RT, HT, HQ, LPP, true>(p_lds, P.bin, P.pw4, P.Minv4, P.valid, P.m4, b - S.bin_start[j],
                                                 S.bin_start[j + 1] - S.bin_start[j]);
 }
 
@@ -304,7 +285,7 @@ __global__ void __launch_bounds__(kPipeThreads, 4) k_group_bin_pipe(GroupLaunch 
   const int j = group_of(S.bin_start, S.count, b);
   const GroupProblem& P = G.prob[S.first + j];
   if (P.ctl->done) return;
-  bin_body<RT, HT, HQ, false, LPP, false>(nullptr, P.bin, P.pw4, P.Minv4, P.valid, P.m4, b - S.bin_start[j],
+  bin_body<RT, HT, HQ, LPP, false>(nullptr, P.bin, P.pw4, P.Minv4, P.valid, P.m4, b - S.bin_start[j],
                                           S.bin_start[j + 1] - S.bin_start[j]);
 }
 
@@ -365,9 +346,9 @@ uint32_t bin_pipe_blocks(int64_t n_obs, int lpp) {
 BinShape bin_shape(const View& vc, const Runs& W, int mode) {
   BinShape s;
   if (mode == BIN_PLAIN || W.n_obs <= 0) return s;
-  const bool fits = vc.n_b * columns_of(vc) <= kLdsDoubles, pipe = vc.rowQ >= 0;
+  const bool fits = !vc.iqu && vc.n_b * columns_of(vc) <= kLdsDoubles, pipe = vc.rowQ >= 0;
   if (mode < 0) {
-    if (fits && !vc.iqu && W.R >= kMinRuns && W.n_obs >= kMinPix)
+    if (fits && W.R >= kMinRuns && W.n_obs >= kMinPix)
       s.form = BIN_LDS;
     else if (bin_sparse(W.R, W.n_obs, vc.rowQ >= 0))
       s.form = BIN_PIPE;
@@ -405,17 +386,15 @@ hipError_t launch_bin_form(const View& vc, const BinRuns& B, const BinShape& s, 
       };
       const bool t = vc.rowT >= 0;
       if (s.form == BIN_PIPE && t)
-        launch(k_bin_pipe<RT, true, true, false, LPP>, kPipeThreads);
+        launch(k_bin_pipe<RT, true, true, LPP>, kPipeThreads);
       else if (s.form == BIN_PIPE)
-        launch(k_bin_pipe<RT, false, true, false, LPP>, kPipeThreads);
-      else if (vc.iqu)
-        launch(k_bin_lds<RT, false, false, true, LPP>, kThreads);
+        launch(k_bin_pipe<RT, false, true, LPP>, kPipeThreads);
       else if (t && vc.rowQ >= 0)
-        launch(k_bin_lds<RT, true, true, false, LPP>, kThreads);
+        launch(k_bin_lds<RT, true, true, LPP>, kThreads);
       else if (vc.rowQ >= 0)
-        launch(k_bin_lds<RT, false, true, false, LPP>, kThreads);
+        launch(k_bin_lds<RT, false, true, LPP>, kThreads);
       else
-        launch(k_bin_lds<RT, true, false, false, LPP>, kThreads);
+        launch(k_bin_lds<RT, true, false, LPP>, kThreads);
     });
   });
   return hipGetLastError();
@@ -438,10 +417,8 @@ hipError_t launch_group_bin_form(const GroupLaunch& G, int kind, hipStream_t st)
         launch(k_group_bin_lds<RT, GK_T, LPP>, kThreads);
       else if (kind == GK_QU)
         launch(k_group_bin_lds<RT, GK_QU, LPP>, kThreads);
-      else if (kind == GK_TQU)
-        launch(k_group_bin_lds<RT, GK_TQU, LPP>, kThreads);
       else
-        launch(k_group_bin_lds<RT, GK_IQU, LPP>, kThreads);
+        launch(k_group_bin_lds<RT, GK_TQU, LPP>, kThreads);
     });
   });
   return hipGetLastError();
