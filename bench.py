@@ -41,7 +41,9 @@ METRIC = "samples x CG-iters/s per GPU (FP64 plain vs FP32-mixed batched); HBM G
 HBM_PEAK_GBS = 8000.0
 SIGMA = 1e-3
 TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "runs_30day_nside256_hbm_traffic.md")
-RUN_KERNELS_SRC = os.path.join(ROOT, "paper_1309_5609_amd", "csrc", "dst_runs.hip")
+# sources of the iteration kernels that the 30-day workload runs
+ITERATION_SRC = [os.path.join(ROOT, "paper_1309_5609_amd", "csrc", f)
+                 for f in ("dst_runs.hip", "dst_stage.hip", "dst_forms.hip")]
 
 # Uneven survey batch: 8 polarimeter channels (days, baseline length, f_k in Hz,
 # alpha) with spin-axis phase az0 = 45 deg x c and angle offset psi0 = 22.5 deg x c,
@@ -55,19 +57,23 @@ def log(msg: str) -> None:
     print(f"[bench {time.strftime('%H:%M:%S')}] {msg}", file=sys.stderr, flush=True)
 
 
-def measured_traffic(kernel: str):
+def measured_traffic(kernel: str, workload: int):
     """HBM bytes per dispatch of ``kernel`` from the committed rocprofv3 FETCH_SIZE / WRITE_SIZE summary.
 
-    None when the summary is missing, has no row for the kernel, or was taken
-    on a different kernel source than the one built now.
+    None for the 6-hour workload (the counters are the 30-day one's), and when
+    the summary is missing, has no row for the kernel, or was taken on other
+    kernel sources than those built now.
     """
     import hashlib
+    if workload == 0:
+        return None
     try:
         text = open(TRAFFIC_PROFILE).read()
-        sha = hashlib.sha256(open(RUN_KERNELS_SRC, "rb").read()).hexdigest()
+        for path in ITERATION_SRC:
+            sha = hashlib.sha256(open(path, "rb").read()).hexdigest()
+            if f"{os.path.basename(path)} sha256 {sha}" not in text:
+                return None
     except OSError:
-        return None
-    if f"sha256 {sha}" not in text:
         return None
     for line in text.splitlines():
         if line.startswith(f"| `{kernel}` |"):
@@ -525,9 +531,12 @@ def main() -> int:
     k_ms = {k: float(np.mean([r[f"t_{k}_ms"] for r in runs])) for k in ("bin", "apply", "unbin", "update")}
     dom = max(("bin", "unbin"), key=lambda k: k_ms[k])
     rt = "float" if args.workload == 2 else "double"
-    dom_kernel = {"bin": f"k_bin_runs<{rt}, true, true, false, 32>",
-                  "unbin": f"k_unbin_staged<{rt}, true, true>"}[dom]
-    traffic = measured_traffic(dom_kernel)
+    if args.workload == 0:  # launch shapes by size
+        dom_kernel = {"bin": "k_bin_runs", "unbin": "k_unbin_runs"}[dom]
+    else:
+        dom_kernel = {"bin": f"k_bin_runs<{rt}, true, true, false, 32>",
+                      "unbin": f"k_unbin_staged<{rt}, true, true>"}[dom]
+    traffic = measured_traffic(dom_kernel, args.workload)
     launch_s = k_ms[dom] * 1e-3
     achieved = mb[dom] / launch_s / 1e9
     iter_ms = float(np.mean([r["t_iter_ms"] for r in plain]))
