@@ -119,10 +119,12 @@ int dst_version(void);
 
 /* Create a context on HIP device `device`.  *ctx receives the handle.
  * Launch shapes of the run-form iteration kernels may be overridden by the
- * environment at creation: DST_BIN_LPP (lanes per pixel in the binning: 64,
- * 32 = default, 16, or -64 for 64 with a software pipeline over pixels),
+ * environment at creation: DST_BIN_LPP (lanes per pixel in the plain binning:
+ * 64, 32, 16, 8, 4, or -64 for 64 with a software pipeline over pixels; by
+ * default by the runs per pixel; a value forces the plain form),
  * DST_BIN_FORM (form of the binning: 0 plain, 1 baseline values in LDS where
- * they fit, 2 pipelined gathers; by default by the problem's sizes) and
+ * they fit, 2 pipelined gathers; by default by the problem's sizes; radiometers
+ * plain) and
  * DST_UNBIN_BPW (baselines per wavefront in the rescan: 1, 2, 4 or 8, or 16
  * per workgroup with the map staged through LDS; by default by their number
  * and the runs per pixel).  DST_RUN_SPLIT_BITS = k splits runs of consecutive
@@ -205,9 +207,10 @@ enum {
   DST_SOLVE_NO_GRAPH = 4u,    /* launch iterations one by one instead of a captured graph */
   DST_SOLVE_PER_SAMPLE = 8u,  /* iterate on per-sample pointing (recomputing cos 2psi, sin 2psi)
                                  instead of the default run-compressed pointing */
-  DST_SOLVE_AUTOTUNE = 16u,   /* time the launch shapes of the run-form binning and rescan on this
-                                 problem once (a few operator applications) and use the fastest;
-                                 the choice is kept in the context per problem shape */
+  DST_SOLVE_AUTOTUNE = 16u,   /* time the launch shapes of the plain binning and rescan (and the other
+                                 forms of them, where the sizes had chosen one) on this problem once
+                                 (a few operator applications) and use the fastest; the choice is kept
+                                 in the context per problem shape */
   DST_SOLVE_GMRES = 32u       /* restarted GMRES (Saad & Schultz 1986, the solver of the paper's
                                  implementation) with the same Jacobi diagonal as right
                                  preconditioner, instead of PCG; tol applies to the GMRES
@@ -324,7 +327,8 @@ int dst_noise_generate(dst_ctx* ctx, uint64_t seed, uint64_t stream_id, int64_t 
  * from FP32 copies (sums, CG scalars and outputs stay FP64): the operator
  * then carries a relative error near 1e-8, so the true residual levels off
  * near 1e-9 while the recurrence residual meets tol.  Problems that share the operator with no
- * other are solved one after another as by dst_solve.
+ * other advance together too, up to 64 per group: each has its own setup and
+ * CG state, and an iteration of all of them takes a few launches.
  *   n_problems     >= 1
  *   problems       host array [n_problems]
  *   opts           as for dst_solve, shared by every problem; a0 must be NULL

@@ -221,8 +221,9 @@ __device__ __forceinline__ void fft_tile(double2 (&v)[kPer], double2* L, const d
     column<LOGR>(i, c, j);
     if constexpr (LOGNS > 0) {
       // powers s^q of the butterfly's factor: 1, 2 and 4 from the table, the
-      // others at most two products deep (as many roundings as a product of two
-      // table entries for every power)
+      // others at most two products deep (table entries for all seven: errors 4.78e-16
+      // for 4.94e-16 of the RMS at 512 points, but 43 M samples in segments of 4096
+      // 0.82 ms for 0.46)
       const int e = (j & ((1 << LOGNS) - 1)) << (kLogElems - LR - LOGNS);
       double2 w[8];
       w[1] = toward<DIR>(W[e]);
